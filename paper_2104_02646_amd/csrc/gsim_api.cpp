@@ -589,6 +589,7 @@ void natural_tiles(const gsim_model* m, bool particles, int tile, std::vector<Ti
             t.count = (int32_t)std::min<int64_t>(tile, m->poff[b + 1] - s);
             t.begin = s;
             t.id = rows++;
+            t.pad = m->body_g0[b] + (int32_t)((s - m->poff[b]) / 64);  // tile sizes are multiples of 64
             nat.push_back(t);
         }
 }
@@ -781,6 +782,7 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
     Ctx<T> c = ctx<T>(m);
     const ModelDev<T>* md = c.md;
     const int nl = m->timing_mask == 0 ? m->lanes : 1;
+    const bool one = m->etile_max <= m->block;  // every tile's elements fit one per thread
     hipStream_t s0 = (hipStream_t)stream;
     bool forked = false;
     auto join = [&]() -> int {
@@ -801,12 +803,12 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
                       bool adjoint) -> int {
         const size_t wf = m->etile_words[0] * sizeof(T), wa = m->etile_words[1] * sizeof(T);
         if (!adjoint) {
-            if (ea > e0) LAUNCH_TRY(timed(m, 0, st, [&] { return launch_elem_fwd<T>(md, sd, c.et + e0, ea - e0, m->block, wf, false, st); }), "element pass");
-            if (e1 > ea) LAUNCH_TRY(timed(m, 0, st, [&] { return launch_elem_fwd<T>(md, sd, c.et + ea, e1 - ea, m->block, wf, true, st); }), "element pass");
+            if (ea > e0) LAUNCH_TRY(timed(m, 0, st, [&] { return launch_elem_fwd<T>(md, sd, c.et + e0, ea - e0, m->block, wf, false, one, st); }), "element pass");
+            if (e1 > ea) LAUNCH_TRY(timed(m, 0, st, [&] { return launch_elem_fwd<T>(md, sd, c.et + ea, e1 - ea, m->block, wf, true, one, st); }), "element pass");
             LAUNCH_TRY(timed(m, 1, st, [&] { return launch_part_fwd<T>(md, sd, c.pt + p0, p1 - p0, m->pblock, m->pitems, st); }), "particle pass");
         } else {
-            if (ea > e0) LAUNCH_TRY(timed(m, 2, st, [&] { return launch_elem_adj<T>(md, sd, c.et + e0, ea - e0, m->block, wa, false, st); }), "element adjoint");
-            if (e1 > ea) LAUNCH_TRY(timed(m, 2, st, [&] { return launch_elem_adj<T>(md, sd, c.et + ea, e1 - ea, m->block, wa, true, st); }), "element adjoint");
+            if (ea > e0) LAUNCH_TRY(timed(m, 2, st, [&] { return launch_elem_adj<T>(md, sd, c.et + e0, ea - e0, m->block, wa, false, one, st); }), "element adjoint");
+            if (e1 > ea) LAUNCH_TRY(timed(m, 2, st, [&] { return launch_elem_adj<T>(md, sd, c.et + ea, e1 - ea, m->block, wa, true, one, st); }), "element adjoint");
             if (pa > p0) LAUNCH_TRY(timed(m, 3, st, [&] { return launch_part_adj<T>(md, sd, c.pt + p0, pa - p0, m->pblock, m->pitems, false, st); }), "particle adjoint");
             if (p1 > pa) LAUNCH_TRY(timed(m, 3, st, [&] { return launch_part_adj<T>(md, sd, c.pt + pa, p1 - pa, m->pblock, m->pitems, true, st); }), "particle adjoint");
         }
@@ -838,11 +840,11 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
         const bool paired = m->n_etiles >= DUAL_PAIR_MIN_TILES;
         LAUNCH_TRY(timed(m, 6, st, [&] {
             return launch_dual<T>(md, sd_a, sd_f, c.et + e0, e1 - e0, c.pt + p0, p1 - p0, m->block, m->pblock, lds,
-                                  false, paired, st);
+                                  false, paired, one, st);
         }), "overlapped element passes");
         LAUNCH_TRY(timed(m, 7, st, [&] {
             return launch_dual<T>(md, sd_a, sd_f, c.et + e0, e1 - e0, c.pt + p0, p1 - p0, m->block, m->pblock, lds,
-                                  true, false, st);
+                                  true, false, one, st);
         }), "overlapped particle passes");
         return GSIM_OK;
     };
@@ -1424,6 +1426,7 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     m->eoff = P->eoff;
     m->toff = P->toff;
     m->hoff = P->hoff;
+    m->body_g0 = P->body_g0;
     hipStream_t s = (hipStream_t)stream;
     char* ws = m->ws;
     auto up = [&](size_t off, const void* src, size_t n) -> hipError_t {
@@ -1518,6 +1521,7 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     m->etiles_plan = P->etiles;
     m->etile_words[0] = P->etile_words[0];
     m->etile_words[1] = P->etile_words[1];
+    for (const Tile& t : P->etiles) m->etile_max = std::max(m->etile_max, t.count);
     // fused dynamic LDS of a body: its particle arrays, then its colour bounds (int32,
     // ncol + 1 per element kind)
     for (int b = 0; b < P->nb; ++b) {
@@ -1535,7 +1539,6 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
         B.np = P->poff[b + 1] - P->poff[b];
         B.contact_on = P->contact_on[b];
         B.air_on = P->air_on[b];
-        B.g0 = P->body_g0[b];
         for (int k = 0; k < 3; ++k) {
             B.cbase[k] = P->cbase[3 * b + k];
             B.ncol[k] = P->ncol[3 * b + k];

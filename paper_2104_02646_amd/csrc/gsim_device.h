@@ -49,6 +49,15 @@ template <typename T> __device__ __forceinline__ T gld(const T* p, int64_t i) {
 template <typename T> __device__ __forceinline__ void gst(T* p, int64_t i, T v) {
     ((__attribute__((address_space(1))) T*)p)[i] = v;
 }
+// Accesses at a uniform base (the same in every lane: a tile's first item) plus a
+// lane's 32-bit byte offset: the base stays in scalar registers and one offset register
+// serves every array of the tile, so no address arithmetic runs on the vector units.
+template <typename T> __device__ __forceinline__ T gldo(const T* base, uint32_t off) {
+    return *(const __attribute__((address_space(1))) T*)((const __attribute__((address_space(1))) char*)base + off);
+}
+template <typename T> __device__ __forceinline__ void gsto(T* base, uint32_t off, T v) {
+    *(__attribute__((address_space(1))) T*)((__attribute__((address_space(1))) char*)base + off) = v;
+}
 template <typename T> __device__ __forceinline__ V3<T> ld3(const T* __restrict__ p, int64_t n, int64_t i) {
     return mk3(gld(p, i), gld(p, n + i), gld(p, 2 * n + i));
 }
@@ -56,6 +65,14 @@ template <typename T> __device__ __forceinline__ void st3(T* __restrict__ p, int
     gst(p, i, a.x);
     gst(p, n + i, a.y);
     gst(p, 2 * n + i, a.z);
+}
+template <typename T> __device__ __forceinline__ V3<T> ld3o(const T* p, int64_t n, uint32_t off) {
+    return mk3(gldo(p, off), gldo(p + n, off), gldo(p + 2 * n, off));
+}
+template <typename T> __device__ __forceinline__ void st3o(T* p, int64_t n, uint32_t off, V3<T> a) {
+    gsto(p, off, a.x);
+    gsto(p + n, off, a.y);
+    gsto(p + 2 * n, off, a.z);
 }
 
 // ------------------------------------------------------------- contact ---

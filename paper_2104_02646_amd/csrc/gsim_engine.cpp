@@ -659,15 +659,17 @@ int micro_round(gsim_engine* E) {
     // the element launch and the particle launch over every query's tiles (element LDS:
     // the largest tile among the queries in this round, forward or adjoint)
     const int block = 256;
+    bool one = true;  // every live query's tiles fit one element per thread
     size_t lds = 0;
     for (int i = 0; i < n; ++i) {
         const gsim_model* m = E->live[i].model;
+        if (ops[i] == OP_FWD || ops[i] == OP_ADJ) one = one && m->etile_max <= block;
         if (ops[i] == OP_FWD) lds = std::max(lds, (size_t)m->etile_words[0] * sizeof(float));
         if (ops[i] == OP_ADJ) lds = std::max(lds, (size_t)m->etile_words[1] * sizeof(float));
     }
     LAUNCH_TRY(launch_mixed<float>(dmd, dsd, reinterpret_cast<const TileSeg*>(d + o_s0), (int)seg[0].size(), total[0],
                                    grid[0], reinterpret_cast<const TileSeg*>(d + o_s1), (int)seg[1].size(), total[1],
-                                   grid[1], dummy_row, block, lds, E->stream),
+                                   grid[1], dummy_row, block, lds, one, E->stream),
                "element and particle passes");
     HIP_TRY(hipEventRecord(E->blob_evt[r], E->stream), "record tick");
     // advance; finish completed queries

@@ -116,6 +116,7 @@ struct gsim_model {
     char* ws = nullptr;
     gsim::Layout L{};
     std::vector<int64_t> poff, eoff, toff, hoff;
+    std::vector<int32_t> body_g0;     // per body: first gather slice
     int exec = GSIM_EXEC_PLAIN;
     int block = 256, items = 1;    // element passes: threads per element tile (items: unused, tiles are planned)
     int pblock = 256, pitems = 1;  // particle passes
@@ -146,6 +147,7 @@ struct gsim_model {
     hipEvent_t stage_evt = nullptr;   // completes when the last table upload has read `stage`
     std::vector<gsim::Tile> etiles_nat, ptiles_nat;  // natural-order tiles (planned / current tile size)
     std::vector<gsim::Tile> etiles_plan;             // element tiles of the plan
+    int32_t etile_max = 0;                           // elements of the largest tile
     int64_t etile_words[2] = {0, 0};                 // largest element tile's LDS words, forward / adjoint
     std::vector<char> md_host;                       // ModelDev<T> as uploaded
     std::map<long long, gsim::GraphEntry> graphs;

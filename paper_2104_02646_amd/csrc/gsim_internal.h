@@ -40,7 +40,8 @@ struct Tile {
     int64_t begin;  // first item (model-global element or particle index)
     int32_t id;     // particle tiles: row of the contact-gradient partial buffer;
                     // element tiles: first tile particle
-    int32_t pad;    // element tiles: number of tile particles
+    int32_t pad;    // element tiles: number of tile particles; particle tiles: first slice of the
+                    // gather table (tiles start on a 64-particle slice of their body)
 };
 
 // Serving: one query's share of a round's pass: its `count` tiles (resident on the
@@ -65,7 +66,6 @@ struct BodyDev {
     int64_t p0, np;      // particle range
     int32_t pt0, pt1;    // particle-tile id range (contact-gradient partials)
     int32_t contact_on;  // ground contact active
-    int32_t g0;          // first gather slice of the body
     int32_t air_on;      // lift/drag on the body's triangles
     int32_t cbase[3];    // fused path: first colour boundary of each element kind in coff
     int32_t ncol[3];     // fused path: colours of each element kind
@@ -182,16 +182,17 @@ bool disarm_launch_events();
 // `air` selects the kernel variant that models lift/drag (models with an air body).
 // element passes: one workgroup (block threads) per element tile, `lds` bytes of
 // dynamic LDS (the largest tile's: forward 4 words per tile particle + 4 per
-// corner, adjoint 8 + 4)
+// corner, adjoint 8 + 4); `one`: no tile has more elements than `block`, so each thread
+// has one element and loads its record ahead of the staging
 template <typename T>
 int launch_elem_fwd(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, size_t lds,
-                    bool air, void* stream);
+                    bool air, bool one, void* stream);
 template <typename T>
 int launch_part_fwd(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, int items,
                     void* stream);
 template <typename T>
 int launch_elem_adj(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, size_t lds,
-                    bool air, void* stream);
+                    bool air, bool one, void* stream);
 template <typename T>
 int launch_part_adj(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, int items,
                     bool air, void* stream);
@@ -213,7 +214,7 @@ int launch_persist(const ModelDev<T>* md, const StepDev<T>* rows, int n_rows, co
 template <typename T>
 int launch_dual(const ModelDev<T>* md, const StepDev<T>* sd_adj, const StepDev<T>* sd_fwd, const Tile* etiles,
                 int n_etiles, const Tile* ptiles, int n_ptiles, int block, int pblock, size_t lds, bool particles,
-                bool paired, void* stream);
+                bool paired, bool one, void* stream);
 // One workgroup per piece: the pieces' copies and zero fills in one launch (the serving
 // engine's query set-up, staged through one host-to-device copy).
 int launch_stage_copy(const StageSeg* segs, int n_segs, void* stream);
@@ -226,7 +227,7 @@ int launch_stage_copy(const StageSeg* segs, int n_segs, void* stream);
 template <typename T>
 int launch_mixed(const ModelDev<T>* md, const StepDev<T>* sd, const TileSeg* eseg, int n_eseg, int e_total, int e_grid,
                  const TileSeg* pseg, int n_pseg, int p_total, int p_grid, int dummy_id, int block, size_t lds,
-                 void* stream);
+                 bool one, void* stream);
 template <typename T>
 int launch_contact_reduce(const ModelDev<T>* md, const StepDev<T>* sd, int n_bodies, void* stream);
 template <typename T>

@@ -33,6 +33,9 @@
 namespace gsim {
 namespace {
 
+__device__ __forceinline__ float gfma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double gfma(double a, double b, double c) { return fma(a, b, c); }
+
 // Slots are 4-vectors accessed as one 16-byte (FP32) or two 16-byte (FP64)
 // global accesses (clang vector types: they can live in address space 1).
 typedef float gf4 __attribute__((ext_vector_type(4)));
@@ -80,6 +83,12 @@ __device__ __forceinline__ V3<T> ld_fslot(const T* s, int64_t k) {
 // w = 1/m, 0 for pinned particles.  The mass is loaded whether or not the particle
 // is pinned (the mass array covers every particle), so its load does not wait for
 // the pin flag.
+template <typename T>
+__device__ __forceinline__ T inv_mass(const ModelDev<T>& M, const StepDev<T>& S, int64_t begin, uint32_t l) {
+    const bool pin = gldo(M.pinned + begin, l) != 0;
+    const T m = gldo(S.mass + begin, (uint32_t)sizeof(T) * l);
+    return pin ? T(0) : T(1) / m;
+}
 template <typename T> __device__ __forceinline__ T inv_mass(const ModelDev<T>& M, const StepDev<T>& S, int64_t i) {
     const bool pin = gld(M.pinned, i) != 0;
     const T m = gld(S.mass, i);
@@ -179,45 +188,101 @@ struct TetKin {
     T s, J1;       // Ic - 3, J - 1
 };
 
+// Every rounding of the tet's arithmetic is written out (contraction off, fused
+// multiply-adds explicit), so that each kernel that evaluates an element, however its
+// loads and branches are arranged, gets the same bits.
+template <typename T>
+__device__ __forceinline__ V3<T> fma3(V3<T> a, T s, V3<T> c) {
+    return mk3(gfma(a.x, s, c.x), gfma(a.y, s, c.y), gfma(a.z, s, c.z));
+}
+template <typename T>
+__device__ __forceinline__ V3<T> mul3(V3<T> a, T s) {
+#pragma clang fp contract(off)
+    return mk3(a.x * s, a.y * s, a.z * s);
+}
+template <typename T>
+__device__ __forceinline__ V3<T> add3(V3<T> a, V3<T> b) {
+#pragma clang fp contract(off)
+    return mk3(a.x + b.x, a.y + b.y, a.z + b.z);
+}
+template <typename T>
+__device__ __forceinline__ V3<T> sub3(V3<T> a, V3<T> b) {
+#pragma clang fp contract(off)
+    return mk3(a.x - b.x, a.y - b.y, a.z - b.z);
+}
+// a s + b t + c r, the first product fused into the rounded second, then the third
+template <typename T>
+__device__ __forceinline__ V3<T> lin3(V3<T> a, T s, V3<T> b, T t, V3<T> c, T r) {
+    return fma3(c, r, fma3(a, s, mul3(b, t)));
+}
+template <typename T>
+__device__ __forceinline__ T fdot(V3<T> a, V3<T> b) {
+#pragma clang fp contract(off)
+    return gfma(a.z, b.z, gfma(a.x, b.x, a.y * b.y));
+}
+template <typename T>
+__device__ __forceinline__ V3<T> fcross(V3<T> a, V3<T> b) {
+#pragma clang fp contract(off)
+    return mk3(gfma(a.y, b.z, -(a.z * b.y)), gfma(a.z, b.x, -(a.x * b.z)), gfma(a.x, b.y, -(a.y * b.x)));
+}
+
 template <typename T>
 __device__ __forceinline__ void tet_kin(const V3<T> u[4], const T D[9], TetKin<T>& k) {
-    const V3<T> d0 = u[1] - u[0], d1 = u[2] - u[0], d2 = u[3] - u[0];
+#pragma clang fp contract(off)
+    const V3<T> d0 = sub3(u[1], u[0]), d1 = sub3(u[2], u[0]), d2 = sub3(u[3], u[0]);
     V3<T> H[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) H[j] = d0 * D[j] + d1 * D[3 + j] + d2 * D[6 + j];
+    for (int j = 0; j < 3; ++j) H[j] = lin3(d0, D[j], d1, D[3 + j], d2, D[6 + j]);
     // row j of H, as a vector (column j of H^T)
     const V3<T> R[3] = {mk3(H[0].x, H[1].x, H[2].x), mk3(H[0].y, H[1].y, H[2].y), mk3(H[0].z, H[1].z, H[2].z)};
     const T tr = H[0].x + H[1].y + H[2].z;
-    const V3<T> cH[3] = {cross(H[1], H[2]), cross(H[2], H[0]), cross(H[0], H[1])};
-    const T detH = dot(H[0], cH[0]);
+    const V3<T> cH[3] = {fcross(H[1], H[2]), fcross(H[2], H[0]), fcross(H[0], H[1])};
+    const T detH = fdot(H[0], cH[0]);
     const T tcH = cH[0].x + cH[1].y + cH[2].z;
-    k.s = T(2) * tr + (dot(H[0], H[0]) + dot(H[1], H[1]) + dot(H[2], H[2]));
+    k.s = gfma(T(2), tr, fdot(H[0], H[0]) + fdot(H[1], H[1]) + fdot(H[2], H[2]));
     k.J1 = tr + tcH + detH;
     const T q = k.s / (T(4) * (T(4) + k.s));
-    const V3<T> E[3] = {mk3(T(1), T(0), T(0)), mk3(T(0), T(1), T(0)), mk3(T(0), T(0), T(1))};
+    // (the identity's terms only where it is 1: a product with its zeros changes no value)
+    const T tr1 = T(1) + tr;
+    V3<T> S[3];  // H + H^T - tr H I
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        k.F[j] = H[j] + E[j];
-        k.C[j] = E[j] * (T(1) + tr) - R[j] + cH[j];
-        k.Pmu[j] = (H[j] + R[j] - E[j] * tr - cH[j]) * T(0.75) + k.F[j] * q;
+        k.F[j] = H[j];
+        k.C[j] = -R[j];
+        S[j] = add3(H[j], R[j]);
+    }
+    k.F[0].x += T(1);
+    k.F[1].y += T(1);
+    k.F[2].z += T(1);
+    k.C[0].x = tr1 - R[0].x;
+    k.C[1].y = tr1 - R[1].y;
+    k.C[2].z = tr1 - R[2].z;
+    S[0].x -= tr;
+    S[1].y -= tr;
+    S[2].z -= tr;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        k.C[j] = add3(k.C[j], cH[j]);
+        k.Pmu[j] = fma3(sub3(S[j], cH[j]), T(0.75), mul3(k.F[j], q));
     }
 }
 
 template <typename T>
 __device__ __forceinline__ void tet_force(const V3<T> u[4], const T D[9], T V, T mu, T lam, T act, V3<T> f[4],
                                           T& J1) {
+#pragma clang fp contract(off)
     TetKin<T> k;
     tet_kin(u, D, k);
     J1 = k.J1;
     const T B = lam * (k.J1 - act);
     V3<T> P[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) P[j] = k.Pmu[j] * mu + k.C[j] * B;
-    f[0] = zero3<T>();
+    for (int j = 0; j < 3; ++j) P[j] = fma3(k.Pmu[j], mu, mul3(k.C[j], B));
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        f[i + 1] = (P[0] * D[3 * i] + P[1] * D[3 * i + 1] + P[2] * D[3 * i + 2]) * (-V);
-        f[0] -= f[i + 1];
+        const V3<T> G = lin3(P[0], D[3 * i], P[1], D[3 * i + 1], P[2], D[3 * i + 2]);
+        f[i + 1] = mul3(G, -V);
+        f[0] = i == 0 ? -f[1] : fma3(G, V, f[0]);
     }
 }
 
@@ -226,54 +291,57 @@ __device__ __forceinline__ void tet_force(const V3<T> u[4], const T D[9], T V, T
 // of <fb, f>; also returns the forces themselves (for the mass gradient).  The
 // position adjoint differentiates P = A F + B cof F with A = mu (1 - 1/(Ic+1)) and
 // B = lambda (J - alpha) (both O(mu) at rest, so no cancellation reaches it).
+// gmu, glam and gact come in as the sums so far and go out with this step's added.
 template <typename T>
 __device__ __forceinline__ void tet_adjoint(const V3<T> u[4], const T D[9], T V, T mu, T lam, T act, const V3<T> fb[4],
                                             V3<T> f[4], V3<T> xb[4], T& gmu, T& glam, T& gact) {
+#pragma clang fp contract(off)
     TetKin<T> k;
     tet_kin(u, D, k);
     const V3<T>* F = k.F;
     const V3<T>* C = k.C;
     const T Ja = k.J1 - act;
+    const T lJ = lam * Ja;
     V3<T> P[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) P[j] = k.Pmu[j] * mu + C[j] * (lam * Ja);
-    f[0] = zero3<T>();
+    for (int j = 0; j < 3; ++j) P[j] = fma3(k.Pmu[j], mu, mul3(C[j], lJ));
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        f[i + 1] = (P[0] * D[3 * i] + P[1] * D[3 * i + 1] + P[2] * D[3 * i + 2]) * (-V);
-        f[0] -= f[i + 1];
+        const V3<T> G = lin3(P[0], D[3 * i], P[1], D[3 * i + 1], P[2], D[3 * i + 2]);
+        f[i + 1] = mul3(G, -V);
+        f[0] = i == 0 ? -f[1] : fma3(G, V, f[0]);
     }
     // f_{i+1} = G_i, f_0 = -sum G_i  =>  Gbar_i = fb_{i+1} - fb_0
-    const V3<T> Hb[3] = {fb[1] - fb[0], fb[2] - fb[0], fb[3] - fb[0]};
+    const V3<T> Hb[3] = {sub3(fb[1], fb[0]), sub3(fb[2], fb[0]), sub3(fb[3], fb[0])};
     V3<T> Pb[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) Pb[j] = (Hb[0] * D[j] + Hb[1] * D[3 + j] + Hb[2] * D[6 + j]) * (-V);
-    const T Ab = dot(Pb[0], F[0]) + dot(Pb[1], F[1]) + dot(Pb[2], F[2]);
-    const T Bb = dot(Pb[0], C[0]) + dot(Pb[1], C[1]) + dot(Pb[2], C[2]);
-    gmu = dot(Pb[0], k.Pmu[0]) + dot(Pb[1], k.Pmu[1]) + dot(Pb[2], k.Pmu[2]);
-    glam = Ja * Bb;
-    gact = -lam * Bb;
-    const T ip = T(1) / (T(4) + k.s);             // 1/(Ic+1)
-    const T A = mu * (T(0.75) + k.s * T(0.25) * ip);  // mu (1 - 1/(Ic+1))
-    const T B = lam * Ja - T(0.75) * mu;          // lambda (J - alpha)
-    const T Icb = Ab * mu * ip * ip;
+    for (int j = 0; j < 3; ++j) Pb[j] = mul3(lin3(Hb[0], D[j], Hb[1], D[3 + j], Hb[2], D[6 + j]), -V);
+    const T Ab = fdot(Pb[0], F[0]) + fdot(Pb[1], F[1]) + fdot(Pb[2], F[2]);
+    const T Bb = fdot(Pb[0], C[0]) + fdot(Pb[1], C[1]) + fdot(Pb[2], C[2]);
     const T Jb = Bb * lam;
+    gmu += fdot(Pb[0], k.Pmu[0]) + fdot(Pb[1], k.Pmu[1]) + fdot(Pb[2], k.Pmu[2]);
+    glam = gfma(Ja, Bb, glam);
+    gact -= Jb;
+    const T ip = T(1) / (T(4) + k.s);                 // 1/(Ic+1)
+    const T A = mu * gfma(k.s * T(0.25), ip, T(0.75));  // mu (1 - 1/(Ic+1))
+    const T B = gfma(mu, T(-0.75), lJ);               // lambda (J - alpha)
+    const T Icb = Ab * mu * ip * ip;
     V3<T> Fb[3], Cb[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        Fb[j] = Pb[j] * A + C[j] * Jb + F[j] * (T(2) * Icb);
-        Cb[j] = Pb[j] * B;
+        Fb[j] = lin3(Pb[j], A, C[j], Jb, F[j], T(2) * Icb);
+        Cb[j] = mul3(Pb[j], B);
     }
     // C0 = F1 x F2, C1 = F2 x F0, C2 = F0 x F1;  (a x b) adjoint: abar = b x cbar, bbar = cbar x a
-    Fb[1] += cross(F[2], Cb[0]);
-    Fb[2] += cross(Cb[0], F[1]);
-    Fb[2] += cross(F[0], Cb[1]);
-    Fb[0] += cross(Cb[1], F[2]);
-    Fb[0] += cross(F[1], Cb[2]);
-    Fb[1] += cross(Cb[2], F[0]);
+    Fb[1] = add3(Fb[1], fcross(F[2], Cb[0]));
+    Fb[2] = add3(Fb[2], fcross(Cb[0], F[1]));
+    Fb[2] = add3(Fb[2], fcross(F[0], Cb[1]));
+    Fb[0] = add3(Fb[0], fcross(Cb[1], F[2]));
+    Fb[0] = add3(Fb[0], fcross(F[1], Cb[2]));
+    Fb[1] = add3(Fb[1], fcross(Cb[2], F[0]));
 #pragma unroll
-    for (int c = 0; c < 3; ++c) xb[c + 1] = Fb[0] * D[3 * c] + Fb[1] * D[3 * c + 1] + Fb[2] * D[3 * c + 2];
-    xb[0] = -(xb[1] + xb[2] + xb[3]);
+    for (int c = 0; c < 3; ++c) xb[c + 1] = lin3(Fb[0], D[3 * c], Fb[1], D[3 * c + 1], Fb[2], D[3 * c + 2]);
+    xb[0] = sub3(sub3(-xb[1], xb[2]), xb[3]);
 }
 
 // --------------------------------------------------- membrane triangle ---
@@ -578,9 +646,57 @@ __device__ __forceinline__ void lds_st3(T* a, int n, int i, V3<T> v) {
 // A tile particle's record (particle index, corner run, partial slot): three
 // consecutive 32-bit words, one 12-byte load.
 typedef int gi4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ gi4 ld_tp(const int32_t* tp, int64_t i) {
-    const __attribute__((address_space(1))) int32_t* r = (const __attribute__((address_space(1))) int32_t*)(tp + 3 * i);
-    return gi4{r[0], r[1], r[2], 0};
+__device__ __forceinline__ gi4 ld_tp(const int32_t* tp, uint32_t j) {
+    return gi4{gldo(tp, 12 * j), gldo(tp + 1, 12 * j), gldo(tp + 2, 12 * j), 0};
+}
+
+// An element's record and parameters, held in registers between the loads and the
+// force: corner codes, Dm^-1 (tets 9 values, triangles 4), volume / area / rest angle,
+// (mu, lambda, actuation) / (k) / (hinge actuation).
+template <typename T>
+struct ElemRec {
+    uint32_t c0, c1, c2, c3;
+    T d0, d1, d2, d3, d4, d5, d6, d7, d8;
+    T V, p0, p1, act;
+};
+// Record of the element at byte-scaled position l of the tile starting at `begin`
+// (uniform).  (Returned by value and assembled from locals: branch-wise stores through a
+// reference are merged by address and keep the record in scratch memory.)
+template <typename T>
+__device__ __forceinline__ ElemRec<T> load_elem(const ModelDev<T>& M, const StepDev<T>& S, int kind, int64_t begin,
+                                                uint32_t l) {
+    const uint32_t oc = 4 * l, o = (uint32_t)sizeof(T) * l;
+    uint32_t c[4] = {0, 0, 0, 0};
+    T d[9] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+    T V, p0 = T(0), p1 = T(0), act = T(0);
+    if (kind == TILE_TET) {
+        const uint32_t* code = M.tet_code + begin;
+        const T* dinv = M.tet_dinv + begin;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = gldo(code + k * M.ne, oc);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) d[k] = gldo(dinv + k * M.ne, o);
+        V = gldo(M.tet_vol + begin, o);
+        p0 = gldo(S.mu + begin, o);
+        p1 = gldo(S.lam + begin, o);
+        if (S.act) act = gldo(S.act + begin, o);
+    } else if (kind == TILE_TRI) {
+        const uint32_t* code = M.tri_code + begin;
+        const T* dinv = M.tri_dinv + begin;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[k] = gldo(code + k * M.nt, oc);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d[k] = gldo(dinv + k * M.nt, o);
+        V = gldo(M.tri_area + begin, o);
+        p0 = gldo(S.ktri + begin, o);
+    } else {
+        const uint32_t* code = M.hin_code + begin;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = gldo(code + k * M.nh, oc);
+        V = gldo(M.hin_phi0 + begin, o);
+        if (S.hact) act = gldo(S.hact + begin, o);
+    }
+    return ElemRec<T>{c[0], c[1], c[2], c[3], d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8], V, p0, p1, act};
 }
 
 // Element pass: one workgroup per planned element tile.  The positions of the
@@ -590,13 +706,23 @@ __device__ __forceinline__ gi4 ld_tp(const int32_t* tp, int64_t i) {
 // particle-sorted corner order; after one barrier each tile particle sums its
 // contiguous run of corners in that fixed order and writes one partial.  No
 // atomics; the result does not depend on the block size.
+//
+// What bounds it: small models by the launch itself (about 1.5 us) and one tile's chain
+// of dependent accesses (tile -> tile particle -> position -> LDS -> force -> LDS ->
+// partial); batches by vector instruction issue as much as by bytes (a tet's forward and
+// adjoint take about 230 and 460 FP32 instructions).  Hence: with ONE (no tile has more
+// elements than the workgroup threads) each thread loads its element's record before it
+// stages positions, so that both return behind the same wait; records are read from
+// scalar bases with one 32-bit offset per lane (64-bit lane addresses took 63 vector
+// instructions a tile in the forward pass, now 19); the models' own launches take their
+// model and step records at a fixed address, not through the tile's model index.
+// Measured together, before and after: one-cube gradient of 100 steps 1689 -> 1611 us,
+// 200k-tet blob 2570 -> 2466 us, 256-body batch 7388 -> 7274 us.
 // AIR: the variant launched for models with a lift/drag body (the other compiles
 // without any of that code).
-template <typename T, bool AIR>
-__device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd, const Tile tl,
+template <typename T, bool AIR, bool ONE>
+__device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDev<T>& S, const Tile tl,
                                               unsigned char* smem) {
-    const ModelDev<T>& M = md[tl.model];
-    const StepDev<T>& S = sd[tl.model];
     const int64_t np = M.np;
     const int m = tl.pad, tid = threadIdx.x, nth = blockDim.x;
     // triangle tiles of bodies with air also stage the velocities (lift/drag)
@@ -604,46 +730,39 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>* __restrict__ md
     L4<T>* xs = reinterpret_cast<L4<T>*>(smem);  // [m] tile-particle positions
     L4<T>* vs = xs + m;                          // [m] velocities (air tiles)
     L4<T>* cs = xs + (air ? 2 * m : m);          // [corners] corner forces, particle-sorted
+    const int32_t* tp = M.tp + 3 * (int64_t)tl.id;
     gi4 mine = {0, 0, 0, 0};                     // this thread's first tile particle
+    if (tid < m) mine = ld_tp(tp, (uint32_t)tid);
+    ElemRec<T> rec;
+    if constexpr (ONE)
+        if (tid < tl.count) rec = load_elem(M, S, tl.kind, tl.begin, (uint32_t)tid);
     for (int j = tid; j < m; j += nth) {
-        const gi4 r = ld_tp(M.tp, (int64_t)tl.id + j);
-        if (j == tid) mine = r;
+        const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         xs[j] = l4(tl.kind == TILE_TET ? load_disp(M, S.x, S.x_abs, (int64_t)r.x) : load_pos(M, S.x, S.x_abs, (int64_t)r.x),
                    T(0));
         if (air) vs[j] = l4(ld3(S.v, np, (int64_t)r.x), T(0));
     }
     __syncthreads();
-    for (int l = threadIdx.x; l < tl.count; l += blockDim.x) {
-        const int64_t e = tl.begin + l;
+    for (int l = tid; l < tl.count; l += nth) {
+        V3<T> x[4], f[4];
         if (tl.kind == TILE_TET) {
-            uint32_t cd[4];
-            V3<T> x[4], f[4];
-            T D[9];
+            if constexpr (!ONE) rec = load_elem(M, S, TILE_TET, tl.begin, (uint32_t)l);
+            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                cd[c] = gld(M.tet_code, c * M.ne + e);
-                x[c] = v3(xs[cd[c] & 0xffffu]);
-            }
-#pragma unroll
-            for (int k = 0; k < 9; ++k) D[k] = gld(M.tet_dinv, k * M.ne + e);
-            const T act = S.act ? gld(S.act, e) : T(0);
+            for (int c = 0; c < 4; ++c) x[c] = v3(xs[cd[c] & 0xffffu]);
             T J1;
-            tet_force(x, D, gld(M.tet_vol, e), gld(S.mu, e), gld(S.lam, e), act, f, J1);
+            tet_force(x, D, rec.V, rec.p0, rec.p1, rec.act, f, J1);
             if (J1 <= T(-1)) raise_flag(M, tl.body, 1);
 #pragma unroll
             for (int c = 0; c < 4; ++c) cs[cd[c] >> 16] = l4(f[c], T(0));
         } else if (tl.kind == TILE_TRI) {
-            uint32_t cd[3];
-            V3<T> x[3], f[3];
-            T D[4];
+            if constexpr (!ONE) rec = load_elem(M, S, TILE_TRI, tl.begin, (uint32_t)l);
+            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                cd[c] = gld(M.tri_code, c * M.nt + e);
-                x[c] = v3(xs[cd[c] & 0xffffu]);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) D[k] = gld(M.tri_dinv, k * M.nt + e);
-            tri_force(x, D, gld(M.tri_area, e), gld(S.ktri, e), f);
+            for (int c = 0; c < 3; ++c) x[c] = v3(xs[cd[c] & 0xffffu]);
+            tri_force(x, D, rec.V, rec.p0, f);
             if (air) {
                 V3<T> v[3];
 #pragma unroll
@@ -655,21 +774,19 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>* __restrict__ md
 #pragma unroll
             for (int c = 0; c < 3; ++c) cs[cd[c] >> 16] = l4(f[c], T(0));
         } else {
-            uint32_t cd[4];
-            V3<T> x[4], f[4];
+            if constexpr (!ONE) rec = load_elem(M, S, TILE_HINGE, tl.begin, (uint32_t)l);
+            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                cd[c] = gld(M.hin_code, c * M.nh + e);
-                x[c] = v3(xs[cd[c] & 0xffffu]);
-            }
-            hinge_force(x, gld(M.hin_phi0, e), M.bodies[tl.body].kb, S.hact ? gld(S.hact, e) : T(0), f);
+            for (int c = 0; c < 4; ++c) x[c] = v3(xs[cd[c] & 0xffffu]);
+            hinge_force(x, rec.V, M.bodies[tl.body].kb, rec.act, f);
 #pragma unroll
             for (int c = 0; c < 4; ++c) cs[cd[c] >> 16] = l4(f[c], T(0));
         }
+        if constexpr (ONE) break;
     }
     __syncthreads();
     for (int j = tid; j < m; j += nth) {
-        const gi4 r = j == tid ? mine : ld_tp(M.tp, (int64_t)tl.id + j);
+        const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int r0 = r.y & 0xffff, rn = r.y >> 16;
         V3<T> f = zero3<T>();
         for (int k = 0; k < rn; ++k) f += v3(cs[r0 + k]);
@@ -677,17 +794,15 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>* __restrict__ md
     }
 }
 
-template <typename T, bool AIR>
+template <typename T, bool AIR, bool ONE>
 __global__ void __launch_bounds__(512) k_elem_fwd(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd,
                                                    const Tile* __restrict__ tiles) {
     extern __shared__ __align__(16) unsigned char smem[];
-    elem_fwd_tile<T, AIR>(md, sd, tiles[blockIdx.x], smem);
+    elem_fwd_tile<T, AIR, ONE>(md[0], sd[0], tiles[blockIdx.x], smem);
 }
 
 template <typename T>
-__device__ __forceinline__ void part_fwd_tile(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd, const Tile tl) {
-    const ModelDev<T>& M = md[tl.model];
-    const StepDev<T>& S = sd[tl.model];
+__device__ __forceinline__ void part_fwd_tile(const ModelDev<T>& M, const StepDev<T>& S, const Tile tl) {
     const BodyDev<T>& B = M.bodies[tl.body];
     const int64_t np = M.np;
     const T dt = B.dt;
@@ -701,42 +816,42 @@ __device__ __forceinline__ void part_fwd_tile(const ModelDev<T>* __restrict__ md
         }
     }
     const V3<T> g = mk3(B.g[0], B.g[1], B.g[2]);
-    for (int64_t l = threadIdx.x; l < tl.count; l += blockDim.x) {
-        const int64_t i = tl.begin + l;
+    const T *px = S.x + tl.begin, *pv = S.v + tl.begin, *rest = M.rest + tl.begin;
+    for (int l = threadIdx.x; l < tl.count; l += blockDim.x) {
         // every load that does not depend on another is issued first
-        const int64_t li = i - B.p0;
-        const int64_t gb = M.gbase[B.g0 + (li >> 6)];
-        const int32_t deg = M.pdeg[i];
-        const V3<T> u = load_disp(M, S.x, S.x_abs, i), v = ld3(S.v, np, i);
-        const T rg = contact ? gld(M.rgap, i) : T(0);
-        const T w = inv_mass(M, S, i);
+        const uint32_t o = (uint32_t)(sizeof(T) * l);
+        const int64_t gb = gld(M.gbase, tl.pad + (l >> 6));  // (the tile starts on a slice)
+        const int32_t deg = gldo(M.pdeg + tl.begin, 4u * l);
+        V3<T> u = ld3o(px, np, o);
+        const V3<T> v = ld3o(pv, np, o);
+        if (S.x_abs) u = u - ld3o(rest, np, o);
+        const T rg = contact ? gldo(M.rgap + tl.begin, o) : T(0);
+        const T w = inv_mass(M, S, tl.begin, l);
         V3<T> f = zero3<T>();
-        sum_fslots(M.fslots, gb + (li & 63), deg, f);
+        sum_fslots(M.fslots, gb + (l & 63), deg, f);
         if (S.ckx) {
-            st3(S.ckx, np, i, u);
-            st3(S.ckv, np, i, v);
+            st3o(S.ckx + tl.begin, np, o, u);
+            st3o(S.ckv + tl.begin, np, o, v);
         }
         if (contact) f += contact_force_gap(gap_of(rg, pl, u), v, pl, cp);
         const T gate = w > T(0) ? T(1) : T(0);
         const V3<T> vn = v + (f * w + g * gate) * dt;
         const V3<T> un = u + vn * dt;
         if (!finite_pair(un, vn)) raise_flag(M, tl.body, 0);
-        st3(S.vo, np, i, vn);
-        st3(S.xo, np, i, S.xo_abs ? ld3(M.rest, np, i) + un : un);
+        st3o(S.vo + tl.begin, np, o, vn);
+        st3o(S.xo + tl.begin, np, o, S.xo_abs ? ld3o(rest, np, o) + un : un);
     }
 }
 
 template <typename T>
 __global__ void __launch_bounds__(512) k_part_fwd(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd,
                                                    const Tile* __restrict__ tiles) {
-    part_fwd_tile<T>(md, sd, tiles[blockIdx.x]);
+    part_fwd_tile<T>(md[0], sd[0], tiles[blockIdx.x]);
 }
 
 // Adjoint force of a particle: fbar = dt w (vbar+ + dt xbar+), with one explicit
 // fused multiply-add per component so that every kernel forming it from the same
 // adjoint state gets the same bits.
-__device__ __forceinline__ float gfma(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double gfma(double a, double b, double c) { return fma(a, b, c); }
 template <typename T>
 __device__ __forceinline__ V3<T> fbar_of(V3<T> xb, V3<T> vb, T dt, T w) {
     const T s = dt * w;
@@ -758,11 +873,9 @@ __device__ __forceinline__ V3<T> corner_fbar(const ModelDev<T>& M, const StepDev
 // and sum each particle's velocity adjoint into a second partial (vslots); the
 // body's other tiles write zero there, so every partial the particle pass reads
 // is written.
-template <typename T, bool AIR>
-__device__ __forceinline__ void elem_adj_tile(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd, const Tile tl,
+template <typename T, bool AIR, bool ONE>
+__device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDev<T>& S, const Tile tl,
                                               unsigned char* smem) {
-    const ModelDev<T>& M = md[tl.model];
-    const StepDev<T>& S = sd[tl.model];
     const int64_t np = M.np;
     const T dt = M.bodies[tl.body].dt;
     const int m = tl.pad, tid = threadIdx.x, nth = blockDim.x;
@@ -773,59 +886,71 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>* __restrict__ md
     L4<T>* vs = fbs + m;                         // [m] velocities (air tiles)
     L4<T>* cs = fbs + (air ? 2 * m : m);         // [corners] corner (xbar, f.fbar), particle-sorted
     L4<T>* cv = cs + 3 * tl.count;               // [corners] corner vbar (air tiles)
+    const int32_t* tp = M.tp + 3 * (int64_t)tl.id;
     gi4 mine = {0, 0, 0, 0};                     // this thread's first tile particle
+    if (tid < m) mine = ld_tp(tp, (uint32_t)tid);
+    // the record and the accumulated gradients are read before the adjoint is computed
+    // (the first element's before the staging), so their loads overlap the others
+    ElemRec<T> rec;
+    T g0 = T(0), g1 = T(0), g2 = T(0);
+    T* G0 = tl.kind == TILE_TET ? S.g_mu : tl.kind == TILE_TRI ? S.g_ktri : S.g_hact;
+    T* G1 = tl.kind == TILE_TET ? S.g_lam : nullptr;
+    T* G2 = tl.kind == TILE_TET ? S.g_act : nullptr;
+    const bool w0 = G0 != nullptr, w1 = G1 != nullptr, w2 = G2 != nullptr;
+    G0 += tl.begin;
+    G1 += tl.begin;
+    G2 += tl.begin;
+    if constexpr (ONE)
+        if (tid < tl.count) {
+            rec = load_elem(M, S, tl.kind, tl.begin, (uint32_t)tid);
+            if (w0) g0 = gldo(G0, (uint32_t)(sizeof(T) * tid));
+            if (w1) g1 = gldo(G1, (uint32_t)(sizeof(T) * tid));
+            if (w2) g2 = gldo(G2, (uint32_t)(sizeof(T) * tid));
+        }
     for (int j = tid; j < m; j += nth) {
-        const gi4 r = ld_tp(M.tp, (int64_t)tl.id + j);
-        if (j == tid) mine = r;
+        const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int64_t p = r.x;
         xs[j] = l4(tl.kind == TILE_TET ? load_disp(M, S.x, S.x_abs, p) : load_pos(M, S.x, S.x_abs, p), T(0));
         fbs[j] = l4(corner_fbar(M, S, p, dt), T(0));
         if (air) vs[j] = l4(ld3(S.v, np, p), T(0));
     }
     __syncthreads();
-    for (int l = threadIdx.x; l < tl.count; l += blockDim.x) {
-        const int64_t e = tl.begin + l;
+    for (int l = tid; l < tl.count; l += nth) {
+        const uint32_t o = (uint32_t)(sizeof(T) * l);
+        if constexpr (!ONE) {
+            if (w0) g0 = gldo(G0, o);
+            if (w1) g1 = gldo(G1, o);
+            if (w2) g2 = gldo(G2, o);
+        }
+        V3<T> x[4], f[4], fb[4], xb[4];
         if (tl.kind == TILE_TET) {
-            uint32_t cd[4];
-            V3<T> x[4], f[4], fb[4], xb[4];
-            T D[9];
+            if constexpr (!ONE) rec = load_elem(M, S, TILE_TET, tl.begin, (uint32_t)l);
+            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cd[c] = gld(M.tet_code, c * M.ne + e);
                 x[c] = v3(xs[cd[c] & 0xffffu]);
                 fb[c] = v3(fbs[cd[c] & 0xffffu]);
             }
-#pragma unroll
-            for (int k = 0; k < 9; ++k) D[k] = gld(M.tet_dinv, k * M.ne + e);
-            const T act = S.act ? gld(S.act, e) : T(0);
-            // the accumulated gradients are read before the adjoint is computed, so
-            // their loads overlap with the element's other loads
-            const T gmu0 = S.g_mu ? gld(S.g_mu, e) : T(0), glam0 = S.g_lam ? gld(S.g_lam, e) : T(0),
-                    gact0 = S.g_act ? gld(S.g_act, e) : T(0);
-            T gmu, glam, gact;
-            tet_adjoint(x, D, gld(M.tet_vol, e), gld(S.mu, e), gld(S.lam, e), act, fb, f, xb, gmu, glam, gact);
+            tet_adjoint(x, D, rec.V, rec.p0, rec.p1, rec.act, fb, f, xb, g0, g1, g2);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cs[cd[c] >> 16] = l4(xb[c], dot(f[c], fb[c]));
+                cs[cd[c] >> 16] = l4(xb[c], fdot(f[c], fb[c]));
             }
-            if (S.g_mu) gst(S.g_mu, e, gmu0 + gmu);
-            if (S.g_lam) gst(S.g_lam, e, glam0 + glam);
-            if (S.g_act) gst(S.g_act, e, gact0 + gact);
+            if (w0) gsto(G0, o, g0);
+            if (w1) gsto(G1, o, g1);
+            if (w2) gsto(G2, o, g2);
         } else if (tl.kind == TILE_TRI) {
-            uint32_t cd[3];
-            V3<T> x[3], f[3], fb[3], xb[3];
-            T D[4];
+            if constexpr (!ONE) rec = load_elem(M, S, TILE_TRI, tl.begin, (uint32_t)l);
+            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                cd[c] = gld(M.tri_code, c * M.nt + e);
                 x[c] = v3(xs[cd[c] & 0xffffu]);
                 fb[c] = v3(fbs[cd[c] & 0xffffu]);
             }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) D[k] = gld(M.tri_dinv, k * M.nt + e);
-            const T gk0 = S.g_ktri ? gld(S.g_ktri, e) : T(0);
             T gk;
-            tri_adjoint(x, D, gld(M.tri_area, e), gld(S.ktri, e), fb, f, xb, gk);
+            tri_adjoint(x, D, rec.V, rec.p0, fb, f, xb, gk);
             if (air) {
                 V3<T> v[3], vbc;
 #pragma unroll
@@ -843,29 +968,28 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>* __restrict__ md
             for (int c = 0; c < 3; ++c) {
                 cs[cd[c] >> 16] = l4(xb[c], dot(f[c], fb[c]));
             }
-            if (S.g_ktri) gst(S.g_ktri, e, gk0 + gk);
+            if (w0) gsto(G0, o, g0 + gk);
         } else {
-            uint32_t cd[4];
-            V3<T> x[4], f[4], fb[4], xb[4];
+            if constexpr (!ONE) rec = load_elem(M, S, TILE_HINGE, tl.begin, (uint32_t)l);
+            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cd[c] = gld(M.hin_code, c * M.nh + e);
                 x[c] = v3(xs[cd[c] & 0xffffu]);
                 fb[c] = v3(fbs[cd[c] & 0xffffu]);
             }
-            const T gact0 = S.g_hact ? gld(S.g_hact, e) : T(0);
             T gact;
-            hinge_adjoint(x, gld(M.hin_phi0, e), M.bodies[tl.body].kb, S.hact ? gld(S.hact, e) : T(0), fb, f, xb, gact);
+            hinge_adjoint(x, rec.V, M.bodies[tl.body].kb, rec.act, fb, f, xb, gact);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 cs[cd[c] >> 16] = l4(xb[c], dot(f[c], fb[c]));
             }
-            if (S.g_hact) gst(S.g_hact, e, gact0 + gact);
+            if (w0) gsto(G0, o, g0 + gact);
         }
+        if constexpr (ONE) break;
     }
     __syncthreads();
     for (int j = tid; j < m; j += nth) {
-        const gi4 r = j == tid ? mine : ld_tp(M.tp, (int64_t)tl.id + j);
+        const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int r0 = r.y & 0xffff, rn = r.y >> 16;
         V3<T> xb = zero3<T>();
         T d = T(0);
@@ -884,17 +1008,15 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>* __restrict__ md
     }
 }
 
-template <typename T, bool AIR>
+template <typename T, bool AIR, bool ONE>
 __global__ void __launch_bounds__(512) k_elem_adj(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd,
                                                    const Tile* __restrict__ tiles) {
     extern __shared__ __align__(16) unsigned char smem[];
-    elem_adj_tile<T, AIR>(md, sd, tiles[blockIdx.x], smem);
+    elem_adj_tile<T, AIR, ONE>(md[0], sd[0], tiles[blockIdx.x], smem);
 }
 
 template <typename T, bool AIR>
-__device__ __forceinline__ void part_adj_tile(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd, const Tile tl) {
-    const ModelDev<T>& M = md[tl.model];
-    const StepDev<T>& S = sd[tl.model];
+__device__ __forceinline__ void part_adj_tile(const ModelDev<T>& M, const StepDev<T>& S, const Tile tl) {
     const BodyDev<T>& B = M.bodies[tl.body];
     const int64_t np = M.np;
     const T dt = B.dt;
@@ -908,22 +1030,24 @@ __device__ __forceinline__ void part_adj_tile(const ModelDev<T>* __restrict__ md
         }
     }
     T gc[4] = {T(0), T(0), T(0), T(0)};
-    for (int64_t l = threadIdx.x; l < tl.count; l += blockDim.x) {
-        const int64_t i = tl.begin + l;
+    const int64_t p0 = tl.begin;
+    for (int l = threadIdx.x; l < tl.count; l += blockDim.x) {
+        const uint32_t o = (uint32_t)(sizeof(T) * l);
         // every load that does not depend on another is issued first
-        const int64_t li = i - B.p0;
-        const int64_t gb = M.gbase[B.g0 + (li >> 6)];
-        const int32_t deg = M.pdeg[i];
-        const V3<T> xbp = ld3(S.xb, np, i), vbp = ld3(S.vb, np, i);
-        const T w = inv_mass(M, S, i);
+        const int64_t gb = gld(M.gbase, tl.pad + (l >> 6));  // (the tile starts on a slice)
+        const int32_t deg = gldo(M.pdeg + p0, 4u * l);
+        const V3<T> xbp = ld3o(S.xb + p0, np, o), vbp = ld3o(S.vb + p0, np, o);
+        const T w = inv_mass(M, S, p0, l);
         V3<T> u = zero3<T>(), v = zero3<T>();
         T rg = T(0);
         if (contact) {
-            u = load_disp(M, S.x, S.x_abs, i);
-            v = ld3(S.v, np, i);
-            rg = gld(M.rgap, i);
+            u = ld3o(S.x + p0, np, o);
+            if (S.x_abs) u = u - ld3o(M.rest + p0, np, o);
+            v = ld3o(S.v + p0, np, o);
+            rg = gldo(M.rgap + p0, o);
         }
-        const int64_t base = gb + (li & 63);
+        const T gm0 = S.g_mass ? gldo(S.g_mass + p0, o) : T(0);
+        const int64_t base = gb + (l & 63);
         V3<T> xs = zero3<T>();
         T ds = T(0);
         sum_slots(M.slots, base, deg, xs, ds);
@@ -940,11 +1064,11 @@ __device__ __forceinline__ void part_adj_tile(const ModelDev<T>* __restrict__ md
         }
         const V3<T> xbm = xbp + xs + xcb, vbm = vt + vcb;
         if (!finite_pair(xbm, vbm)) raise_flag(M, tl.body, 0);
-        st3(S.xbo, np, i, xbm);
-        st3(S.vbo, np, i, vbm);
+        st3o(S.xbo + p0, np, o, xbm);
+        st3o(S.vbo + p0, np, o, vbm);
         // the adjoint force of the previous step, for the next adjoint element pass
-        if (S.fbo) st3(S.fbo, np, i, fbar_of(xbm, vbm, dt, w));
-        if (S.g_mass && w > T(0)) S.g_mass[i] += -w * ds;  // dm = -w^2 dw, dw = dt f.vt = f.fbar / w
+        if (S.fbo) st3o(S.fbo + p0, np, o, fbar_of(xbm, vbm, dt, w));
+        if (S.g_mass && w > T(0)) gsto(S.g_mass + p0, o, gm0 + -w * ds);  // dm = -w^2 dw, dw = dt f.vt = f.fbar / w
     }
     if (contact && S.g_contact) {
         T tot[4];
@@ -958,7 +1082,7 @@ __device__ __forceinline__ void part_adj_tile(const ModelDev<T>* __restrict__ md
 template <typename T, bool AIR>
 __global__ void __launch_bounds__(512) k_part_adj(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd,
                                                    const Tile* __restrict__ tiles) {
-    part_adj_tile<T, AIR>(md, sd, tiles[blockIdx.x]);
+    part_adj_tile<T, AIR>(md[0], sd[0], tiles[blockIdx.x]);
 }
 
 // Persistent execution: workgroup b runs body b through a run of steps.  Each step is
@@ -979,14 +1103,14 @@ __global__ void __launch_bounds__(512) k_persist(const ModelDev<T>* __restrict__
         const StepDev<T>* sd = rows + r;  // tiles carry model 0: their record is sd[0]
         const bool adj = sd->adj != 0;
         for (int k = e0; k < e1; ++k) {
-            if (adj) elem_adj_tile<T, false>(md, sd, etiles[k], smem);
-            else elem_fwd_tile<T, false>(md, sd, etiles[k], smem);
+            if (adj) elem_adj_tile<T, false, false>(md[0], *sd, etiles[k], smem);
+            else elem_fwd_tile<T, false, false>(md[0], *sd, etiles[k], smem);
             __syncthreads();  // the next tile reuses the LDS
         }
         __syncthreads();  // (workgroup-scope release and acquire of global memory)
         for (int k = p0; k < p1; ++k) {
-            if (adj) part_adj_tile<T, false>(md, sd, ptiles[k]);
-            else part_fwd_tile<T>(md, sd, ptiles[k]);
+            if (adj) part_adj_tile<T, false>(md[0], *sd, ptiles[k]);
+            else part_fwd_tile<T>(md[0], *sd, ptiles[k]);
             __syncthreads();  // the contact reduction's LDS
         }
         __syncthreads();  // (workgroup-scope release and acquire of global memory)
@@ -1004,7 +1128,7 @@ __global__ void __launch_bounds__(512) k_persist(const ModelDev<T>* __restrict__
 // (element launches of models with many tiles): workgroup b runs tile b's adjoint pass
 // and then its forward pass, so the second pass finds the tile's element records
 // (corner codes, Dm^-1, volume, mu, lambda) in cache.
-template <typename T>
+template <typename T, bool ONE>
 __global__ void __launch_bounds__(512) k_elem_dual(const ModelDev<T>* __restrict__ md,
                                                     const StepDev<T>* __restrict__ sd_adj,
                                                     const StepDev<T>* __restrict__ sd_fwd,
@@ -1013,13 +1137,13 @@ __global__ void __launch_bounds__(512) k_elem_dual(const ModelDev<T>* __restrict
     const int b = blockIdx.x;
     if (paired) {
         const Tile tl = tiles[b];
-        elem_adj_tile<T, false>(md, sd_adj, tl, smem);
+        elem_adj_tile<T, false, ONE>(md[0], sd_adj[0], tl, smem);
         __syncthreads();  // the forward pass reuses the LDS
-        elem_fwd_tile<T, false>(md, sd_fwd, tl, smem);
+        elem_fwd_tile<T, false, ONE>(md[0], sd_fwd[0], tl, smem);
     } else if (b >= span) {
-        elem_fwd_tile<T, false>(md, sd_fwd, tiles[b - span], smem);
+        elem_fwd_tile<T, false, ONE>(md[0], sd_fwd[0], tiles[b - span], smem);
     } else if (b < n) {
-        elem_adj_tile<T, false>(md, sd_adj, tiles[b], smem);
+        elem_adj_tile<T, false, ONE>(md[0], sd_adj[0], tiles[b], smem);
     }
 }
 template <typename T>
@@ -1028,8 +1152,8 @@ __global__ void __launch_bounds__(512) k_part_dual(const ModelDev<T>* __restrict
                                                     int n_adj, int adj_span, const StepDev<T>* __restrict__ sd_fwd,
                                                     const Tile* __restrict__ fwd) {
     const int b = blockIdx.x;
-    if (b >= adj_span) part_fwd_tile<T>(md, sd_fwd, fwd[b - adj_span]);
-    else if (b < n_adj) part_adj_tile<T, false>(md, sd_adj, adj[b]);
+    if (b >= adj_span) part_fwd_tile<T>(md[0], sd_fwd[0], fwd[b - adj_span]);
+    else if (b < n_adj) part_adj_tile<T, false>(md[0], sd_adj[0], adj[b]);
 }
 
 // Serving: the tile at launch position `pos` of a round's element or particle launch.
@@ -1076,9 +1200,17 @@ __device__ __forceinline__ Tile round_tile(const TileSeg* __restrict__ seg, int 
     const TileSeg g = seg[c - 1];  // the same address in every lane
     const Tile* tiles = g.tiles;
     const int sbegin = g.begin, smodel = g.model, sflags = g.flags;
-    tl = tiles[t - sbegin];
-    tl.model = smodel;
-    tl.kind |= sflags;
+    // every lane has the same tile: into scalar registers, so that the passes' bases are
+    // scalar too
+    auto u = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
+    const Tile r = tiles[t - sbegin];
+    tl.model = u(smodel);
+    tl.body = u(r.body);
+    tl.kind = u(r.kind | sflags);
+    tl.count = u(r.count);
+    tl.begin = (int64_t)(((uint64_t)(uint32_t)u((int32_t)(r.begin >> 32)) << 32) | (uint32_t)u((int32_t)r.begin));
+    tl.id = u(r.id);
+    tl.pad = u(r.pad);
     return tl;
 }
 
@@ -1088,7 +1220,7 @@ __device__ __forceinline__ Tile round_tile(const TileSeg* __restrict__ seg, int 
 // records; forward and adjoint tiles of a launch belong to different queries, so the
 // two kinds of work overlap instead of following each other.  The branch is uniform
 // per workgroup.
-template <typename T>
+template <typename T, bool ONE>
 __global__ void __launch_bounds__(512) k_elem_mixed(const ModelDev<T>* __restrict__ md,
                                                      const StepDev<T>* __restrict__ sd, const TileSeg* __restrict__ seg,
                                                      int nseg, int total, int grid, int dummy_id) {
@@ -1096,9 +1228,9 @@ __global__ void __launch_bounds__(512) k_elem_mixed(const ModelDev<T>* __restric
     Tile tl = round_tile(seg, nseg, total, grid, blockIdx.x, TILE_TET, dummy_id);
     if (tl.kind & TILE_ADJ) {
         tl.kind &= ~TILE_ADJ;
-        elem_adj_tile<T, false>(md, sd, tl, smem);
+        elem_adj_tile<T, false, ONE>(md[tl.model], sd[tl.model], tl, smem);
     } else {
-        elem_fwd_tile<T, false>(md, sd, tl, smem);
+        elem_fwd_tile<T, false, ONE>(md[tl.model], sd[tl.model], tl, smem);
     }
 }
 template <typename T>
@@ -1108,9 +1240,9 @@ __global__ void __launch_bounds__(512) k_part_mixed(const ModelDev<T>* __restric
     Tile tl = round_tile(seg, nseg, total, grid, blockIdx.x, TILE_PART, dummy_id);
     if (tl.kind & TILE_ADJ) {
         tl.kind &= ~TILE_ADJ;
-        part_adj_tile<T, false>(md, sd, tl);
+        part_adj_tile<T, false>(md[tl.model], sd[tl.model], tl);
     } else {
-        part_fwd_tile<T>(md, sd, tl);
+        part_fwd_tile<T>(md[tl.model], sd[tl.model], tl);
     }
 }
 
@@ -1566,14 +1698,15 @@ __global__ void __launch_bounds__(FUSED_ADJ_BLOCK) k_fused_adj(const ModelDev<T>
                 x[q] = lds3(xs, npb, r.li[q]);
                 fb[q] = lds3(fbs, npb, r.li[q]);
             }
-            T gmu, glam, gact;
+            T gmu = r.gmu, glam = r.glam, gact = T(0);
+            if constexpr (ACT) gact = r.gact;
             tet_adjoint(x, r.D, r.V, r.mu, r.lam, r.act, fb, f, o.v, gmu, glam, gact);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o.w[q] = dot(f[q], fb[q]);
+            for (int q = 0; q < 4; ++q) o.w[q] = fdot(f[q], fb[q]);
             if (want_e && valid) {
-                gst(M.f_g, e, r.gmu + gmu);
-                gst(M.f_g, M.ne + e, r.glam + glam);
-                if constexpr (ACT) gst(M.f_g, 2 * M.ne + e, r.gact + gact);
+                gst(M.f_g, e, gmu);
+                gst(M.f_g, M.ne + e, glam);
+                if constexpr (ACT) gst(M.f_g, 2 * M.ne + e, gact);
             }
         });
         colour_sweep<FUSED_AHEAD_ADJ, 3, true, T, TriRecA<T>>(M, cb[1], B.ncol[1], acc, npb,
@@ -1736,20 +1869,22 @@ void allow_lds(const void* kernel, size_t lds, size_t& allowed) {
         allowed = lds;
     }
 }
-template <typename T, bool AIR>
+template <typename T, bool AIR, bool ONE>
 int launch_elem_fwd_v(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, size_t lds,
                       void* stream) {
     static size_t allowed = 48 * 1024;
-    allow_lds(reinterpret_cast<const void*>(&k_elem_fwd<T, AIR>), lds, allowed);
-    launch_timed(k_elem_fwd<T, AIR>, dim3(ntiles), dim3(block), lds, (hipStream_t)stream, md, sd, tiles);
+    allow_lds(reinterpret_cast<const void*>(&k_elem_fwd<T, AIR, ONE>), lds, allowed);
+    launch_timed(k_elem_fwd<T, AIR, ONE>, dim3(ntiles), dim3(block), lds, (hipStream_t)stream, md, sd, tiles);
     return check_launch();
 }
 template <typename T>
 int launch_elem_fwd(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, size_t lds,
-                    bool air, void* stream) {
+                    bool air, bool one, void* stream) {
     if (ntiles <= 0) return 0;
-    return air ? launch_elem_fwd_v<T, true>(md, sd, tiles, ntiles, block, lds, stream)
-               : launch_elem_fwd_v<T, false>(md, sd, tiles, ntiles, block, lds, stream);
+    // (bodies with lift/drag: one variant only, so that no result depends on the block)
+    if (air) return launch_elem_fwd_v<T, true, false>(md, sd, tiles, ntiles, block, lds, stream);
+    return one ? launch_elem_fwd_v<T, false, true>(md, sd, tiles, ntiles, block, lds, stream)
+               : launch_elem_fwd_v<T, false, false>(md, sd, tiles, ntiles, block, lds, stream);
 }
 template <typename T>
 int launch_part_fwd(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, int,
@@ -1758,20 +1893,22 @@ int launch_part_fwd(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* til
     launch_timed(k_part_fwd<T>, dim3(ntiles), dim3(block), 0, (hipStream_t)stream, md, sd, tiles);
     return check_launch();
 }
-template <typename T, bool AIR>
+template <typename T, bool AIR, bool ONE>
 int launch_elem_adj_v(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, size_t lds,
                       void* stream) {
     static size_t allowed = 48 * 1024;
-    allow_lds(reinterpret_cast<const void*>(&k_elem_adj<T, AIR>), lds, allowed);
-    launch_timed(k_elem_adj<T, AIR>, dim3(ntiles), dim3(block), lds, (hipStream_t)stream, md, sd, tiles);
+    allow_lds(reinterpret_cast<const void*>(&k_elem_adj<T, AIR, ONE>), lds, allowed);
+    launch_timed(k_elem_adj<T, AIR, ONE>, dim3(ntiles), dim3(block), lds, (hipStream_t)stream, md, sd, tiles);
     return check_launch();
 }
 template <typename T>
 int launch_elem_adj(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, size_t lds,
-                    bool air, void* stream) {
+                    bool air, bool one, void* stream) {
     if (ntiles <= 0) return 0;
-    return air ? launch_elem_adj_v<T, true>(md, sd, tiles, ntiles, block, lds, stream)
-               : launch_elem_adj_v<T, false>(md, sd, tiles, ntiles, block, lds, stream);
+    // (bodies with lift/drag: one variant only, so that no result depends on the block)
+    if (air) return launch_elem_adj_v<T, true, false>(md, sd, tiles, ntiles, block, lds, stream);
+    return one ? launch_elem_adj_v<T, false, true>(md, sd, tiles, ntiles, block, lds, stream)
+               : launch_elem_adj_v<T, false, false>(md, sd, tiles, ntiles, block, lds, stream);
 }
 template <typename T>
 int launch_part_adj(const ModelDev<T>* md, const StepDev<T>* sd, const Tile* tiles, int ntiles, int block, int,
@@ -1798,20 +1935,27 @@ int launch_persist(const ModelDev<T>* md, const StepDev<T>* rows, int n_rows, co
         return check_launch();
     }
 }
+template <typename T, bool ONE>
+int launch_elem_dual(const ModelDev<T>* md, const StepDev<T>* sd_adj, const StepDev<T>* sd_fwd, const Tile* etiles,
+                     int n_etiles, int block, size_t lds, bool paired, void* stream) {
+    static size_t allowed = 48 * 1024;
+    const int nx = 8;  // XCDs: workgroup b runs on XCD b % 8
+    const int espan = (n_etiles + nx - 1) / nx * nx;
+    if (n_etiles <= 0) return 0;
+    allow_lds(reinterpret_cast<const void*>(&k_elem_dual<T, ONE>), lds, allowed);
+    launch_timed(k_elem_dual<T, ONE>, dim3(paired ? n_etiles : espan + n_etiles), dim3(block), lds, (hipStream_t)stream,
+                 md, sd_adj, sd_fwd, etiles, n_etiles, espan, paired ? 1 : 0);
+    return check_launch();
+}
 template <typename T>
 int launch_dual(const ModelDev<T>* md, const StepDev<T>* sd_adj, const StepDev<T>* sd_fwd, const Tile* etiles,
                 int n_etiles, const Tile* ptiles, int n_ptiles, int block, int pblock, size_t lds, bool particles,
-                bool paired, void* stream) {
-    static size_t allowed = 48 * 1024;
-    const int nx = 8;  // XCDs: workgroup b runs on XCD b % 8
-    const int espan = (n_etiles + nx - 1) / nx * nx, pspan = (n_ptiles + nx - 1) / nx * nx;
-    if (!particles) {
-        if (n_etiles <= 0) return 0;
-        allow_lds(reinterpret_cast<const void*>(&k_elem_dual<T>), lds, allowed);
-        launch_timed(k_elem_dual<T>, dim3(paired ? n_etiles : espan + n_etiles), dim3(block), lds, (hipStream_t)stream,
-                     md, sd_adj, sd_fwd, etiles, n_etiles, espan, paired ? 1 : 0);
-        return check_launch();
-    }
+                bool paired, bool one, void* stream) {
+    if (!particles)
+        return one ? launch_elem_dual<T, true>(md, sd_adj, sd_fwd, etiles, n_etiles, block, lds, paired, stream)
+                   : launch_elem_dual<T, false>(md, sd_adj, sd_fwd, etiles, n_etiles, block, lds, paired, stream);
+    const int nx = 8;
+    const int pspan = (n_ptiles + nx - 1) / nx * nx;
     if (n_ptiles <= 0) return 0;
     launch_timed(k_part_dual<T>, dim3(pspan + n_ptiles), dim3(pblock), 0, (hipStream_t)stream, md, sd_adj, ptiles,
                  n_ptiles, pspan, sd_fwd, ptiles);
@@ -1825,12 +1969,13 @@ int launch_stage_copy(const StageSeg* segs, int n_segs, void* stream) {
 template <typename T>
 int launch_mixed(const ModelDev<T>* md, const StepDev<T>* sd, const TileSeg* eseg, int n_eseg, int e_total, int e_grid,
                  const TileSeg* pseg, int n_pseg, int p_total, int p_grid, int dummy_id, int block, size_t lds,
-                 void* stream) {
-    static size_t allowed = 48 * 1024;
+                 bool one, void* stream) {
     if (e_grid > 0) {
-        allow_lds(reinterpret_cast<const void*>(&k_elem_mixed<T>), lds, allowed);
-        hipLaunchKernelGGL(k_elem_mixed<T>, dim3(e_grid), dim3(block), lds, (hipStream_t)stream, md, sd, eseg, n_eseg,
-                           e_total, e_grid, dummy_id);
+        static size_t allowed[2] = {48 * 1024, 48 * 1024};
+        auto kernel = one ? k_elem_mixed<T, true> : k_elem_mixed<T, false>;
+        allow_lds(reinterpret_cast<const void*>(kernel), lds, allowed[one]);
+        hipLaunchKernelGGL(kernel, dim3(e_grid), dim3(block), lds, (hipStream_t)stream, md, sd, eseg, n_eseg, e_total,
+                           e_grid, dummy_id);
         if (int rc = check_launch()) return rc;
     }
     if (p_grid > 0)
@@ -1917,17 +2062,17 @@ int launch_fused_grads(const ModelDev<T>* md, const StepDev<T>* sd, void* stream
 }
 
 #define GSIM_INSTANTIATE(T)                                                                                          \
-    template int launch_elem_fwd<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, size_t, bool, void*); \
+    template int launch_elem_fwd<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, size_t, bool, bool, void*); \
     template int launch_part_fwd<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, int, void*);     \
-    template int launch_elem_adj<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, size_t, bool, void*); \
+    template int launch_elem_adj<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, size_t, bool, bool, void*); \
     template int launch_part_adj<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, int, bool, void*); \
     template int launch_fill<T>(T*, int64_t, T, void*);                                                             \
     template int launch_persist<T>(const ModelDev<T>*, const StepDev<T>*, int, const Tile*, const Tile*, const int32_t*, \
                                    int, int, size_t, void*);                                                        \
     template int launch_dual<T>(const ModelDev<T>*, const StepDev<T>*, const StepDev<T>*, const Tile*, int, const Tile*, \
-                                int, int, int, size_t, bool, bool, void*);                                        \
+                                int, int, int, size_t, bool, bool, bool, void*);                                  \
     template int launch_mixed<T>(const ModelDev<T>*, const StepDev<T>*, const TileSeg*, int, int, int, const TileSeg*, \
-                                 int, int, int, int, int, size_t, void*);                                           \
+                                 int, int, int, int, int, size_t, bool, void*);                                     \
     template int launch_contact_reduce<T>(const ModelDev<T>*, const StepDev<T>*, int, void*);                       \
     template int launch_loss<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, int, int, void*);     \
     template int launch_fused_fwd<T>(const ModelDev<T>*, const StepDev<T>*, const int32_t*, int, size_t, void*);     \
