@@ -12,11 +12,26 @@
 //   r+ = normalise(r + dt/2 [0, omega+] (x) r)
 //
 // One wavefront per body: each lane holds up to RIGID_VPL of the body's vertices in
-// registers, the vertex sums F and tau are wave butterfly reductions (every lane ends
-// with bitwise the same totals, so every lane integrates the same state and no lane
-// waits on another), and the whole rollout is one launch: the forward walks the steps
-// storing every state (13 values per body per step), the adjoint walks them back.
-// Nothing is shared between waves, so there are no barriers.
+// registers, the vertex sums are wave reductions whose totals every lane receives (so
+// every lane integrates the same state and no lane waits on another), and the whole
+// rollout is one launch: the forward walks the steps storing every state (13 values per
+// body per step), the adjoint walks them back.  Nothing is shared between waves, so
+// there are no barriers.
+//
+// What bounds it: the latency of one step's dependent chain, not bytes (104 bytes a
+// body-step in FP32) and not arithmetic (1024 bodies are one wavefront per SIMD).  So
+// the chain is kept short:
+//   - a step in which no vertex touches the ground (known from one ballot) skips the
+//     vertex forces and the reduction;
+//   - the reductions run in the vector units' lane network (half-wave and row swaps that
+//     also pack two values into one register, then row rotations), four values per
+//     register after two exchanges: no trip through the LDS crossbar per value and stage;
+//   - the adjoint takes omega+ from the next stored state instead of running the step
+//     forward again, which leaves one vertex loop and one reduction per step; it works in
+//     the body frame, where the inertia is constant (matrix-vector products with I^-1 made
+//     once per launch, in place of R I R^T and its inverse every step); it loads the next
+//     state while it works and keeps its parameter sums in registers.
+// 1024 bodies, 150 steps, FP64: forward 245 -> 154 us, adjoint 850 -> 308 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -63,12 +78,78 @@ struct RigidArgs {
     T* g_contact;
 };
 
+// Lane exchanges in the vector units, by 32-bit halves for doubles.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// a + (a of the other half-wave) in lanes 0-31 and the same of b in lanes 32-63.
+template <bool HALF>
+__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
+    if constexpr (HALF) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    }
+}
+template <bool HALF>
+__device__ __forceinline__ float swap_add(float a, float b) {
+    uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+    swap_rows<HALF>(x, y);
+    return __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+}
+template <bool HALF>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const uint64_t p = __builtin_bit_cast(uint64_t, a), q = __builtin_bit_cast(uint64_t, b);
+    uint32_t xl = (uint32_t)p, xh = (uint32_t)(p >> 32), yl = (uint32_t)q, yh = (uint32_t)(q >> 32);
+    swap_rows<HALF>(xl, yl);
+    swap_rows<HALF>(xh, yh);
+    return __builtin_bit_cast(double, ((uint64_t)xh << 32) | xl) + __builtin_bit_cast(double, ((uint64_t)yh << 32) | yl);
+}
+__device__ __forceinline__ float lane_of(float x, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+__device__ __forceinline__ double lane_of(double x, int lane) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Sums of N values over the wavefront's 64 lanes; every lane gets every total.  All
+// lanes must be active.  Four values share a register after the half-wave and the row
+// exchange (value 4k in row 0, 4k + 2 in row 1, 4k + 1 in row 2, 4k + 3 in row 3); the
+// sum over a row's 16 lanes is a fixed tree (lanes 8, 4, 2, 1 apart).
 template <typename T, int N>
 __device__ __forceinline__ void wave_sum(T v[N]) {
+    constexpr int H = (N + 1) / 2, Q = (N + 3) / 4;
+    T h[2 * Q];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
+    for (int i = 0; i < H; ++i) h[i] = swap_add<true>(v[2 * i], 2 * i + 1 < N ? v[2 * i + 1] : T(0));
+    if constexpr (H < 2 * Q) h[2 * Q - 1] = T(0);
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], off, 64);
+    for (int i = 0; i < Q; ++i) {
+        T r = swap_add<false>(h[2 * i], h[2 * i + 1]);
+        r += dpp<0x128>(r);  // row_ror:8
+        r += dpp<0x124>(r);  // row_ror:4 (lanes 8 apart are equal by now)
+        r += dpp<0x4e>(r);   // quad_perm [2, 3, 0, 1]
+        r += dpp<0xb1>(r);   // quad_perm [1, 0, 3, 2]
+        const int row[4] = {0, 32, 16, 48};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (4 * i + k < N) v[4 * i + k] = lane_of(r, row[k]);
+    }
 }
 
 template <typename T>
@@ -103,50 +184,68 @@ __device__ __forceinline__ V3<T> mtv(const T M[9], V3<T> v) {  // M^T v
                M[2] * v.x + M[5] * v.y + M[8] * v.z);
 }
 
-// Per-body quantities of one step that both the forward and the adjoint use.
+// A body-frame inertia as [xx, yy, zz, xy, xz, yz] times a vector, and its inverse.
 template <typename T>
-struct RigidFwd {
-    T R[9], T1[9], Iw[9], inv[9];
-    V3<T> F, tau, L, alpha, vn, wn;
-    T q0, qn;
-    V3<T> qv;
-};
+__device__ __forceinline__ V3<T> sym(const T I[6], V3<T> v) {
+    return mk3(I[0] * v.x + I[3] * v.y + I[4] * v.z, I[3] * v.x + I[1] * v.y + I[5] * v.z,
+               I[4] * v.x + I[5] * v.y + I[2] * v.z);
+}
+template <typename T>
+__device__ __forceinline__ void sym_inverse(const T I[6], T J[6]) {
+    const T c0 = I[1] * I[2] - I[5] * I[5], c3 = I[4] * I[5] - I[3] * I[2], c4 = I[3] * I[5] - I[4] * I[1];
+    const T id = T(1) / (I[0] * c0 + I[3] * c3 + I[4] * c4);
+    J[0] = c0 * id;
+    J[1] = (I[0] * I[2] - I[4] * I[4]) * id;
+    J[2] = (I[0] * I[1] - I[3] * I[3]) * id;
+    J[3] = c3 * id;
+    J[4] = c4 * id;
+    J[5] = (I[3] * I[4] - I[0] * I[5]) * id;
+}
 
-// Vertex forces (this lane's vertices, summed over the wave) and the integration.
+// Whether the world point y is below the body's ground plane (contact_force is zero
+// elsewhere).
 template <typename T>
-__device__ __forceinline__ void rigid_forward(const RigidBodyDev<T>& B, const V3<T> p[RIGID_VPL], int lane,
-                                              const T s[13], T m, const T I[6], const T c[4], RigidFwd<T>& f) {
-    const V3<T> x = mk3(s[0], s[1], s[2]);
-    const V3<T> v = mk3(s[7], s[8], s[9]);
-    const V3<T> w = mk3(s[10], s[11], s[12]);
-    quat_rot(&s[3], f.R);
+__device__ __forceinline__ bool vertex_touches(const RigidBodyDev<T>& B, V3<T> y) {
+    return dot(mk3(B.plane[0], B.plane[1], B.plane[2]), y) - B.plane[3] < T(0);
+}
+
+// One step from s to out.
+template <typename T>
+__device__ __forceinline__ void rigid_step(const RigidBodyDev<T>& B, const V3<T> p[RIGID_VPL], int lane, const T s[13],
+                                           T im, const T I[6], const T c[4], T out[13]) {
+    const V3<T> x = mk3(s[0], s[1], s[2]), u = mk3(s[4], s[5], s[6]);
+    const V3<T> v = mk3(s[7], s[8], s[9]), w = mk3(s[10], s[11], s[12]);
+    T R[9];
+    quat_rot(&s[3], R);
     T acc[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
     if (B.contact_on) {
+        bool any = false;
 #pragma unroll
         for (int j = 0; j < RIGID_VPL; ++j) {
             if (lane + 64 * j >= B.nv) break;
-            const V3<T> a = mv(f.R, p[j]);
-            const V3<T> fk = contact_force(x + a, v + cross(w, a), B.plane, c);
-            const V3<T> tk = cross(a, fk);
-            acc[0] += fk.x; acc[1] += fk.y; acc[2] += fk.z;
-            acc[3] += tk.x; acc[4] += tk.y; acc[5] += tk.z;
+            const V3<T> a = mv(R, p[j]);
+            if (vertex_touches(B, x + a)) {
+                any = true;
+                const V3<T> fk = contact_force(x + a, v + cross(w, a), B.plane, c);
+                const V3<T> tk = cross(a, fk);
+                acc[0] += fk.x; acc[1] += fk.y; acc[2] += fk.z;
+                acc[3] += tk.x; acc[4] += tk.y; acc[5] += tk.z;
+            }
         }
-        wave_sum<T, 6>(acc);
+        if (__ballot(any)) wave_sum<T, 6>(acc);
     }
-    f.F = mk3(acc[0], acc[1], acc[2]);
-    f.tau = mk3(acc[3], acc[4], acc[5]);
     const T Ib[9] = {I[0], I[3], I[4], I[3], I[1], I[5], I[4], I[5], I[2]};
+    T T1[9], M[9], inv[9];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            f.T1[3 * i + j] = f.R[3 * i] * Ib[j] + f.R[3 * i + 1] * Ib[3 + j] + f.R[3 * i + 2] * Ib[6 + j];
+            T1[3 * i + j] = R[3 * i] * Ib[j] + R[3 * i + 1] * Ib[3 + j] + R[3 * i + 2] * Ib[6 + j];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            f.Iw[3 * i + j] = f.T1[3 * i] * f.R[3 * j] + f.T1[3 * i + 1] * f.R[3 * j + 1] + f.T1[3 * i + 2] * f.R[3 * j + 2];
-    const T* M = f.Iw;
+            M[3 * i + j] = T1[3 * i] * R[3 * j] + T1[3 * i + 1] * R[3 * j + 1] + T1[3 * i + 2] * R[3 * j + 2];
     const T det = M[0] * (M[4] * M[8] - M[5] * M[7]) - M[1] * (M[3] * M[8] - M[5] * M[6]) +
                   M[2] * (M[3] * M[7] - M[4] * M[6]);
     const T id = T(1) / det;
@@ -155,27 +254,19 @@ __device__ __forceinline__ void rigid_forward(const RigidBodyDev<T>& B, const V3
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const int r1 = (j + 1) % 3, r2 = (j + 2) % 3, c1 = (i + 1) % 3, c2 = (i + 2) % 3;
-            f.inv[3 * i + j] = (M[3 * r1 + c1] * M[3 * r2 + c2] - M[3 * r1 + c2] * M[3 * r2 + c1]) * id;
+            inv[3 * i + j] = (M[3 * r1 + c1] * M[3 * r2 + c2] - M[3 * r1 + c2] * M[3 * r2 + c1]) * id;
         }
-    f.L = mv(f.Iw, w);
-    f.alpha = mv(f.inv, f.tau - cross(w, f.L));
-    f.vn = v + (f.F * (T(1) / m) + mk3(B.g[0], B.g[1], B.g[2])) * B.dt;
-    f.wn = w + f.alpha * B.dt;
-    const V3<T> u = mk3(s[4], s[5], s[6]);
+    const V3<T> wn = w + mv(inv, mk3(acc[3], acc[4], acc[5]) - cross(w, mv(M, w))) * B.dt;
+    const V3<T> vn = v + (mk3(acc[0], acc[1], acc[2]) * im + mk3(B.g[0], B.g[1], B.g[2])) * B.dt;
+    const V3<T> xn = x + vn * B.dt;
     const T hd = T(0.5) * B.dt;
-    f.q0 = s[3] - hd * dot(f.wn, u);
-    f.qv = u + (f.wn * s[3] + cross(f.wn, u)) * hd;
-    f.qn = gsqrt(f.q0 * f.q0 + dot(f.qv, f.qv));
-}
-
-template <typename T>
-__device__ __forceinline__ void rigid_next(const T s[13], const RigidFwd<T>& f, T dt, T out[13]) {
-    const V3<T> xn = mk3(s[0], s[1], s[2]) + f.vn * dt;
-    const T iq = T(1) / f.qn;
+    const T q0 = s[3] - hd * dot(wn, u);
+    const V3<T> qv = u + (wn * s[3] + cross(wn, u)) * hd;
+    const T iq = T(1) / gsqrt(q0 * q0 + dot(qv, qv));
     out[0] = xn.x; out[1] = xn.y; out[2] = xn.z;
-    out[3] = f.q0 * iq; out[4] = f.qv.x * iq; out[5] = f.qv.y * iq; out[6] = f.qv.z * iq;
-    out[7] = f.vn.x; out[8] = f.vn.y; out[9] = f.vn.z;
-    out[10] = f.wn.x; out[11] = f.wn.y; out[12] = f.wn.z;
+    out[3] = q0 * iq; out[4] = qv.x * iq; out[5] = qv.y * iq; out[6] = qv.z * iq;
+    out[7] = vn.x; out[8] = vn.y; out[9] = vn.z;
+    out[10] = wn.x; out[11] = wn.y; out[12] = wn.z;
 }
 
 template <typename T>
@@ -204,135 +295,146 @@ __global__ __launch_bounds__(64 * RIGID_WAVES) void k_rigid_fwd(RigidArgs<T> A) 
     V3<T> p[RIGID_VPL];
     T m, I[6], c[4], s[13];
     load_body(A, B, b, lane, p, m, I, c);
+    const T im = T(1) / m;
 #pragma unroll
     for (int i = 0; i < 13; ++i) s[i] = A.s0[13 * b + i];
-    if (lane < 13) A.traj[13 * b + lane] = s[lane];
+    T* row = A.traj + 13 * b;
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < 13; ++i) gst(row, i, s[i]);
     for (int t = 0; t < A.n_steps; ++t) {
-        RigidFwd<T> f;
-        rigid_forward(B, p, lane, s, m, I, c, f);
         T out[13];
-        rigid_next(s, f, B.dt, out);
+        rigid_step(B, p, lane, s, im, I, c, out);
+        row += 13 * (int64_t)A.nb;
+        if (lane == 0)
+#pragma unroll
+            for (int i = 0; i < 13; ++i) gst(row, i, out[i]);
 #pragma unroll
         for (int i = 0; i < 13; ++i) s[i] = out[i];
-        if (lane < 13) A.traj[(int64_t)(t + 1) * 13 * A.nb + 13 * b + lane] = s[lane];
     }
 }
 
-// Reverse of one step at state s for the adjoint sb of the step's output: sb becomes
-// the adjoint of s; the parameter adjoints are added to gm, gI, gc.
-template <typename T>
+// Reverse of one step at state s, whose output state is n, for the adjoint sb of that
+// output: sb becomes the adjoint of s; the parameter adjoints are added to gm, gI, gc.
+// START: s is the caller's start state.
+template <bool START, typename T>
 __device__ __forceinline__ void rigid_step_adjoint(const RigidBodyDev<T>& B, const V3<T> p[RIGID_VPL], int lane,
-                                                   const T s[13], T m, const T I[6], const T c[4], T sb[13], T& gm,
-                                                   T gI[6], T gc[4]) {
-    RigidFwd<T> f;
-    rigid_forward(B, p, lane, s, m, I, c, f);
+                                                   const T s[13], const T n[13], T im, const T I[6], const T J[6],
+                                                   const T c[4], T sb[13], T& gm, T gI[6], T gc[4]) {
     const T dt = B.dt, hd = T(0.5) * dt;
-    const V3<T> x = mk3(s[0], s[1], s[2]);
-    const V3<T> v = mk3(s[7], s[8], s[9]);
-    const V3<T> w = mk3(s[10], s[11], s[12]);
-    const V3<T> u = mk3(s[4], s[5], s[6]);
-    // r+ = q / |q|
-    const T iq = T(1) / f.qn;
-    const T rn[4] = {f.q0 * iq, f.qv.x * iq, f.qv.y * iq, f.qv.z * iq};
+    const V3<T> x = mk3(s[0], s[1], s[2]), u = mk3(s[4], s[5], s[6]);
+    const V3<T> v = mk3(s[7], s[8], s[9]), w = mk3(s[10], s[11], s[12]);
+    const V3<T> wn = mk3(n[10], n[11], n[12]);
+    T R[9];
+    quat_rot(&s[3], R);
+    // r+ = q / |q|,  q0 = r0 - dt/2 wn.u,  qv = u + dt/2 (r0 wn + wn x u)
+    const T q0 = s[3] - hd * dot(wn, u);
+    const V3<T> qv = u + (wn * s[3] + cross(wn, u)) * hd;
+    const T iq = T(1) / gsqrt(q0 * q0 + dot(qv, qv));
+    const T rn[4] = {q0 * iq, qv.x * iq, qv.y * iq, qv.z * iq};
     const T rdot = rn[0] * sb[3] + rn[1] * sb[4] + rn[2] * sb[5] + rn[3] * sb[6];
     const T q0b = (sb[3] - rn[0] * rdot) * iq;
     const V3<T> qvb = mk3(sb[4] - rn[1] * rdot, sb[5] - rn[2] * rdot, sb[6] - rn[3] * rdot) * iq;
-    // q0 = r0 - dt/2 wn.u,  qv = u + dt/2 (r0 wn + wn x u)
     T rb[4];
-    rb[0] = q0b + hd * dot(f.wn, qvb);
-    const V3<T> ub = qvb - f.wn * (hd * q0b) + cross(qvb, f.wn) * hd;
+    rb[0] = q0b + hd * dot(wn, qvb);
+    const V3<T> ub = qvb - wn * (hd * q0b) + cross(qvb, wn) * hd;
     rb[1] = ub.x; rb[2] = ub.y; rb[3] = ub.z;
-    V3<T> wnb = mk3(sb[10], sb[11], sb[12]) + (u * (-q0b) + qvb * s[3] + cross(u, qvb)) * hd;
-    // x+ = x + dt v+
+    const V3<T> wnb = mk3(sb[10], sb[11], sb[12]) + (u * (-q0b) + qvb * s[3] + cross(u, qvb)) * hd;
+    // x+ = x + dt v+,  v+ = v + dt (F / m + g)
     const V3<T> xb0 = mk3(sb[0], sb[1], sb[2]);
     const V3<T> vnb = mk3(sb[7], sb[8], sb[9]) + xb0 * dt;
-    // v+ = v + dt (F / m + g)
-    const T im = T(1) / m;
     const V3<T> Fb = vnb * (dt * im);
-    gm += -dt * im * im * dot(f.F, vnb);
-    // omega+ = omega + dt alpha,  alpha = inv h,  h = tau - omega x L,  L = Iw omega
-    V3<T> wb = wnb;
+    // omega+ = omega + dt alpha, alpha = Iw^-1 h, h = tau - omega x L, L = Iw omega, Iw = R I R^T.
+    // With Q = R^-T: Iw^-1 = Q I^-1 Q^T.  Normalised states have Q = R; the caller's start
+    // state is a unit quaternion only to the rounding of its source.
+    T Q[9];
+    if constexpr (START) {
+        const V3<T> r0 = mk3(R[0], R[1], R[2]), r1 = mk3(R[3], R[4], R[5]), r2 = mk3(R[6], R[7], R[8]);
+        const V3<T> c0 = cross(r1, r2), c1 = cross(r2, r0), c2 = cross(r0, r1);
+        const T id = T(1) / dot(r0, c0);
+        Q[0] = c0.x * id; Q[1] = c0.y * id; Q[2] = c0.z * id;
+        Q[3] = c1.x * id; Q[4] = c1.y * id; Q[5] = c1.z * id;
+        Q[6] = c2.x * id; Q[7] = c2.y * id; Q[8] = c2.z * id;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Q[i] = R[i];
+    }
     const V3<T> alphab = wnb * dt;
-    const V3<T> hb = mtv(f.inv, alphab);
-    const V3<T> taub = hb;
-    wb -= cross(f.L, hb);
-    const V3<T> Lb = cross(w, hb);
-    wb += mtv(f.Iw, Lb);
-    // Iw-bar = -hb alpha^T + Lb omega^T
-    T Iwb[9];
-    const T al[3] = {f.alpha.x, f.alpha.y, f.alpha.z}, om[3] = {w.x, w.y, w.z};
-    const T hbv[3] = {hb.x, hb.y, hb.z}, Lbv[3] = {Lb.x, Lb.y, Lb.z};
+    const V3<T> wb = mtv(R, w), Lb = sym(I, wb), L = mv(R, Lb);
+    const V3<T> abb = mtv(Q, alphab);
+    const V3<T> hbb = sym(J, abb);
+    const V3<T> taub = mv(Q, hbb);
+    const V3<T> Lw = cross(w, taub);
+    const V3<T> Lbb = mtv(R, Lw);
+    const V3<T> ILb = sym(I, Lbb);
+    // vertices: F = sum f_k, tau = sum a_k x f_k, f_k = contact(y_k, w_k); their force sums
+    // come with the adjoints
+    constexpr int NA = 26;  // y (3), w_k (3), a x w_k (3), a p^T (9), contact (4), tau (3), f.vnb
+    T acc[NA];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) Iwb[3 * i + j] = -hbv[i] * al[j] + Lbv[i] * om[j];
-    // Iw = T1 R^T, T1 = R Ib
-    T Rb[9], T1b[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            T1b[3 * i + k] = Iwb[3 * i] * f.R[k] + Iwb[3 * i + 1] * f.R[3 + k] + Iwb[3 * i + 2] * f.R[6 + k];
-            Rb[3 * i + k] = Iwb[i] * f.T1[k] + Iwb[3 + i] * f.T1[3 + k] + Iwb[6 + i] * f.T1[6 + k];
-        }
-    const T Ib[9] = {I[0], I[3], I[4], I[3], I[1], I[5], I[4], I[5], I[2]};
-    T Ibb[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            Rb[3 * i + k] += T1b[3 * i] * Ib[3 * k] + T1b[3 * i + 1] * Ib[3 * k + 1] + T1b[3 * i + 2] * Ib[3 * k + 2];
-            Ibb[3 * i + k] = f.R[i] * T1b[k] + f.R[3 + i] * T1b[3 + k] + f.R[6 + i] * T1b[6 + k];
-        }
-    gI[0] += Ibb[0];
-    gI[1] += Ibb[4];
-    gI[2] += Ibb[8];
-    gI[3] += Ibb[1] + Ibb[3];
-    gI[4] += Ibb[2] + Ibb[6];
-    gI[5] += Ibb[5] + Ibb[7];
-    // vertices: F = sum f_k, tau = sum a_k x f_k, f_k = contact(y_k, w_k)
-    T acc[22];
-#pragma unroll
-    for (int i = 0; i < 22; ++i) acc[i] = T(0);
+    for (int i = 0; i < NA; ++i) acc[i] = T(0);
     if (B.contact_on) {
+        bool any = false;
 #pragma unroll
         for (int j = 0; j < RIGID_VPL; ++j) {
             if (lane + 64 * j >= B.nv) break;
-            const V3<T> a = mv(f.R, p[j]);
-            const V3<T> y = x + a, wk = v + cross(w, a);
-            // the force itself first (a_k-bar needs it), then its adjoint
-            const V3<T> fk = contact_force(y, wk, B.plane, c);
-            const V3<T> fkb = Fb + cross(taub, a);
-            V3<T> yb = zero3<T>(), wkb = zero3<T>();
-            T gck[4] = {T(0), T(0), T(0), T(0)};
-            contact_adjoint(y, wk, B.plane, c, fkb, yb, wkb, gck);
-            const V3<T> ab = cross(fk, taub) + yb + cross(wkb, w);
-            const V3<T> wa = cross(a, wkb);
-            acc[0] += yb.x; acc[1] += yb.y; acc[2] += yb.z;
-            acc[3] += wkb.x; acc[4] += wkb.y; acc[5] += wkb.z;
-            acc[6] += wa.x; acc[7] += wa.y; acc[8] += wa.z;
-            const T pk[3] = {p[j].x, p[j].y, p[j].z}, abv[3] = {ab.x, ab.y, ab.z};
+            const V3<T> a = mv(R, p[j]);
+            if (vertex_touches(B, x + a)) {
+                any = true;
+                const V3<T> fkb = Fb + cross(taub, a);
+                V3<T> yb = zero3<T>(), wkb = zero3<T>();
+                T gck[4] = {T(0), T(0), T(0), T(0)};
+                const V3<T> fk = contact_adjoint(x + a, v + cross(w, a), B.plane, c, fkb, yb, wkb, gck);
+                const V3<T> ab = cross(fk, taub) + yb + cross(wkb, w);
+                const V3<T> wa = cross(a, wkb), tk = cross(a, fk);
+                acc[0] += yb.x; acc[1] += yb.y; acc[2] += yb.z;
+                acc[3] += wkb.x; acc[4] += wkb.y; acc[5] += wkb.z;
+                acc[6] += wa.x; acc[7] += wa.y; acc[8] += wa.z;
+                const T pk[3] = {p[j].x, p[j].y, p[j].z}, abv[3] = {ab.x, ab.y, ab.z};
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
+                for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int k = 0; k < 3; ++k) acc[9 + 3 * i + k] += abv[i] * pk[k];
+                    for (int k = 0; k < 3; ++k) acc[9 + 3 * i + k] += abv[i] * pk[k];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc[18 + k] += gck[k];
+                for (int k = 0; k < 4; ++k) acc[18 + k] += gck[k];
+                acc[22] += tk.x; acc[23] += tk.y; acc[24] += tk.z;
+                acc[25] += dot(fk, vnb);
+            }
         }
-        wave_sum<T, 22>(acc);
+        if (__ballot(any)) wave_sum<T, NA>(acc);
     }
-#pragma unroll
-    for (int i = 0; i < 9; ++i) Rb[i] += acc[9 + i];
+    gm += -dt * im * im * acc[25];
 #pragma unroll
     for (int k = 0; k < 4; ++k) gc[k] += acc[18 + k];
+    const V3<T> tau = mk3(acc[22], acc[23], acc[24]);
+    const V3<T> hb = mtv(Q, tau - cross(w, L));
+    const V3<T> ab = sym(J, hb);
+    // Iw-bar = L-bar omega^T - tau-bar alpha^T;  I-bar = R^T Iw-bar R;  R-bar = (Iw-bar +
+    // Iw-bar^T) R I, each outer product with its right factor in the body frame
+    gI[0] += Lbb.x * wb.x - hbb.x * ab.x;
+    gI[1] += Lbb.y * wb.y - hbb.y * ab.y;
+    gI[2] += Lbb.z * wb.z - hbb.z * ab.z;
+    gI[3] += (Lbb.x * wb.y - hbb.x * ab.y) + (Lbb.y * wb.x - hbb.y * ab.x);
+    gI[4] += (Lbb.x * wb.z - hbb.x * ab.z) + (Lbb.z * wb.x - hbb.z * ab.x);
+    gI[5] += (Lbb.y * wb.z - hbb.y * ab.z) + (Lbb.z * wb.y - hbb.z * ab.y);
+    T Rb[9];
+    const V3<T> alpha = mv(Q, ab);
+    const T tv[3] = {taub.x, taub.y, taub.z}, Lv[3] = {Lw.x, Lw.y, Lw.z}, al[3] = {alpha.x, alpha.y, alpha.z};
+    const T om[3] = {w.x, w.y, w.z}, hv[3] = {hb.x, hb.y, hb.z}, bv[3] = {Lb.x, Lb.y, Lb.z};
+    const T av[3] = {abb.x, abb.y, abb.z}, iv[3] = {ILb.x, ILb.y, ILb.z};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            Rb[3 * i + k] = Lv[i] * bv[k] - tv[i] * hv[k] + om[i] * iv[k] - al[i] * av[k] + acc[9 + 3 * i + k];
     quat_rot_adjoint(&s[3], Rb, rb);
     const V3<T> xb = xb0 + mk3(acc[0], acc[1], acc[2]);
     const V3<T> vb = vnb + mk3(acc[3], acc[4], acc[5]);
-    wb += mk3(acc[6], acc[7], acc[8]);
+    const V3<T> wsb = wnb - cross(L, taub) + mv(R, ILb) + mk3(acc[6], acc[7], acc[8]);
     sb[0] = xb.x; sb[1] = xb.y; sb[2] = xb.z;
     sb[3] = rb[0]; sb[4] = rb[1]; sb[5] = rb[2]; sb[6] = rb[3];
     sb[7] = vb.x; sb[8] = vb.y; sb[9] = vb.z;
-    sb[10] = wb.x; sb[11] = wb.y; sb[12] = wb.z;
+    sb[10] = wsb.x; sb[11] = wsb.y; sb[12] = wsb.z;
 }
 
 template <typename T>
@@ -344,29 +446,50 @@ __global__ __launch_bounds__(64 * RIGID_WAVES) void k_rigid_adj(RigidArgs<T> A) 
     if (b >= A.nb) return;
     const RigidBodyDev<T> B = A.bodies[b];
     V3<T> p[RIGID_VPL];
-    T m, I[6], c[4], sb[13];
+    T m, I[6], J[6], c[4], sb[13];
     load_body(A, B, b, lane, p, m, I, c);
+    sym_inverse(I, J);
+    const T im = T(1) / m;
 #pragma unroll
     for (int i = 0; i < 13; ++i) sb[i] = A.sbar[13 * b + i];
-    for (int t = A.n_steps - 1; t >= 0; --t) {
-        T s[13];
+    // parameter sums, starting from what the caller's buffers hold
+    T gm = A.g_mass ? A.g_mass[b] : T(0), gI[6], gc[4];
 #pragma unroll
-        for (int i = 0; i < 13; ++i) s[i] = A.traj[(int64_t)t * 13 * A.nb + 13 * b + i];
-        // this step's parameter adjoints, added to the outputs at once (no
-        // accumulator lives across steps)
-        T gm = T(0), gI[6] = {T(0), T(0), T(0), T(0), T(0), T(0)}, gc[4] = {T(0), T(0), T(0), T(0)};
-        rigid_step_adjoint(B, p, lane, s, m, I, c, sb, gm, gI, gc);
-        if (lane == 0) {
-            if (A.g_mass) A.g_mass[b] += gm;
-            if (A.g_inertia)
+    for (int i = 0; i < 6; ++i) gI[i] = A.g_inertia ? A.g_inertia[6 * b + i] : T(0);
 #pragma unroll
-                for (int i = 0; i < 6; ++i) A.g_inertia[6 * b + i] += gI[i];
-            if (A.g_contact && B.contact_on)
+    for (int i = 0; i < 4; ++i) gc[i] = A.g_contact ? A.g_contact[4 * b + i] : T(0);
+    if (A.n_steps > 0) {
+        const int64_t stride = 13 * (int64_t)A.nb;
+        const T* row = A.traj + (A.n_steps - 1) * stride + 13 * b;
+        T s[13], n[13];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) A.g_contact[4 * b + i] += gc[i];
+        for (int i = 0; i < 13; ++i) s[i] = gld(row, i);
+        rigid_step(B, p, lane, s, im, I, c, n);  // the last output, from its own input
+        for (int t = A.n_steps - 1; t > 0; --t) {
+            T before[13];  // state t - 1, in flight during this step
+            row -= stride;
+#pragma unroll
+            for (int i = 0; i < 13; ++i) before[i] = gld(row, i);
+            rigid_step_adjoint<false>(B, p, lane, s, n, im, I, J, c, sb, gm, gI, gc);
+#pragma unroll
+            for (int i = 0; i < 13; ++i) {
+                n[i] = s[i];
+                s[i] = before[i];
+            }
         }
+        rigid_step_adjoint<true>(B, p, lane, s, n, im, I, J, c, sb, gm, gI, gc);
     }
-    if (lane < 13) A.sbar0[13 * b + lane] = sb[lane];
+    if (lane == 0) {
+        if (A.g_mass) A.g_mass[b] = gm;
+        if (A.g_inertia)
+#pragma unroll
+            for (int i = 0; i < 6; ++i) A.g_inertia[6 * b + i] = gI[i];
+        if (A.g_contact && B.contact_on)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) A.g_contact[4 * b + i] = gc[i];
+#pragma unroll
+        for (int i = 0; i < 13; ++i) A.sbar0[13 * b + i] = sb[i];
+    }
 }
 
 // Mean squared distance of each body's world vertices to target points, and (if
