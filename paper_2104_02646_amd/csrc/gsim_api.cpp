@@ -20,6 +20,7 @@
 #include <map>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "gsim_host.h"
@@ -303,6 +304,48 @@ int build_tiles(gsim_plan* P) {
     return GSIM_OK;
 }
 
+// Resident execution: FP32 models of tets whose bodies each fit one workgroup.  A body's
+// corner runs are laid out tile after tile, in the tiles' own order and each padded to a
+// multiple of RES_PAD, so the sums are those of the element tiles and their partials.
+void build_resident(gsim_plan* P) {
+    if (P->dtype != GSIM_F32 || P->any_air || P->nt || P->nh || !P->ne) return;
+    if (P->np > (int64_t)1 << 28 || P->ne > (int64_t)1 << 28) return;  // 32-bit byte offsets in every array
+    int64_t me = 0, mp = 0;
+    for (int b = 0; b < P->nb; ++b) {
+        me = std::max(me, P->eoff[b + 1] - P->eoff[b]);
+        mp = std::max(mp, P->poff[b + 1] - P->poff[b]);
+    }
+    if (me > RES_EPT * RES_BLOCK || mp > RES_BLOCK) return;
+    const int64_t ne = P->ne;
+    std::vector<uint32_t> code(4 * ne), run(std::max<int64_t>(P->nslot, 1), 0), at;
+    std::vector<int32_t> slots(P->nb, 0);
+    for (const Tile& t : P->etiles) {
+        // sorted corner position -> padded slot of the body
+        at.resize(4 * (size_t)t.count);
+        for (int j = t.id; j < t.id + t.pad; ++j) {
+            const uint32_t first = P->tp_run[j] & 0xffff, n = (uint32_t)P->tp_run[j] >> 16;
+            const uint32_t padded = (n + RES_PAD - 1) / RES_PAD * RES_PAD, base = (uint32_t)slots[t.body];
+            for (uint32_t q = 0; q < n; ++q) at[first + q] = base + q;
+            run[P->tp_slot[j]] = base | padded << 16;
+            slots[t.body] += (int32_t)padded;
+        }
+        for (int64_t e = t.begin; e < t.begin + t.count; ++e)
+            for (int c = 0; c < 4; ++c)
+                code[c * ne + e] = (uint32_t)(P->tet_idx[c * ne + e] - P->poff[t.body]) |
+                                   at[P->tet_code[c * ne + e] >> 16] << 16;
+    }
+    size_t lds = 0;
+    for (int b = 0; b < P->nb; ++b)
+        lds = std::max(lds, 16 * (size_t)(2 * (P->poff[b + 1] - P->poff[b]) + slots[b]));
+    if (lds > RES_LDS) return;  // (also keeps slot numbers and run lengths within 16 bits)
+    P->res_block = me <= 256 && mp <= 256 ? 256 : RES_BLOCK;
+    P->res_ept = (int)((me + P->res_block - 1) / P->res_block);
+    P->res_lds = lds;
+    P->r_code.swap(code);
+    P->r_run.swap(run);
+    P->r_slots.swap(slots);
+}
+
 // The corners of an element are distinct particles (the fused kernels update an
 // element's corners in LDS with all reads before all writes).
 bool distinct(const int32_t* id, int n) {
@@ -479,6 +522,7 @@ int build_plan(const gsim_model_desc* d, gsim_plan* P, bool fused) {
     if (int rc = build_tiles(P)) return rc;
     if (fused) {
         colour_elements(P);
+        build_resident(P);
     } else {
         P->fused_ok = P->coloured = false;
         P->cbase.assign(3 * nb, 0);
@@ -559,6 +603,8 @@ Layout make_layout(const gsim_plan* P, int max_steps) {
     L.f_gh = take(nh * sizeof(T));
     L.ntiles = take(sizeof(Tile) * (cap_e + cap_p));  // natural-order tiles (persistent execution)
     L.toff = take(2 * (P->nb + 1) * 4);
+    L.r_code = take(P->r_code.size() * 4 + 4);
+    L.r_run = take(P->r_run.size() * 4 + 4);
     L.table_cap = 4 * (int64_t)max_steps + 8;
     L.table = take(sizeof(StepDev<T>) * L.table_cap);
     L.total = align_up(o, 256);
@@ -730,6 +776,7 @@ enum Op : int {
     OP_FUSED_PARAMS = 7, // parameters into colour order (and colour-ordered gradient clear)
     OP_FUSED_GRADS = 8,  // colour-ordered gradients back to element order
     OP_FUSED_ADJ_ACT = 9, // OP_FUSED_ADJ that also accumulates actuation gradients
+    OP_RES = 11,          // row2 consecutive rows from `row` through the resident kernel
     OP_DUAL = 10          // adjoint pass of `row` and forward pass of `row2` in the same launches
 };
 
@@ -740,7 +787,7 @@ size_t fused_lds(const gsim_model* m, bool adjoint) {
 struct Launch {
     int op;
     int64_t row;
-    int64_t row2 = 0;  // OP_DUAL: the forward pass's row
+    int64_t row2 = 0;  // OP_DUAL: the forward pass's row; OP_RES: the number of rows
 };
 
 hipError_t take_event(gsim_model* m, hipEvent_t* e) {
@@ -863,6 +910,13 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
             }
             for (int k = 0; k < nl; ++k)
                 if (int rc = dual(k, sd, c.table + l.row2)) return rc;
+            continue;
+        }
+        if (l.op == OP_RES) {
+            if constexpr (std::is_same<T, float>::value)
+                LAUNCH_TRY(launch_resident(md, sd, (int)l.row2, m->nb, m->res_block, m->res_ept, m->pblock, m->res_lds,
+                                           stream),
+                           "resident steps");
             continue;
         }
         if (m->exec == GSIM_EXEC_PERSIST && (l.op == OP_FWD || l.op == OP_ADJ)) {
@@ -1034,6 +1088,61 @@ int check_params(const gsim_model* m, const gsim_params* p, const gsim_grads* g 
     return GSIM_OK;
 }
 
+// A call's steps go through the resident kernel: the model's bodies qualify, the particle
+// passes sum one particle per thread (a tile's contact sums are then whole wavefronts of
+// the resident workgroup), no kernel is being timed (the timed launches are the two-pass
+// ones), and per-step actuation gradients do not overlap (a tet's thread adds to its own
+// entries only, in its own time).
+bool runs_resident(const gsim_model* m, const gsim_grads* g = nullptr) {
+    return m->res_ept > 0 && m->exec != GSIM_EXEC_FUSED && m->timing_mask == 0 && m->pitems == 1 &&
+           (m->res_block % m->pblock == 0 || m->max_body_np <= m->pblock) &&
+           (!g || !g->act || g->act_stride == 0 || g->act_stride >= m->ne);
+}
+// Graph key of a call whose steps do.
+const long long RES_KEY = 1LL << 36;
+// Replaces each run of forward and adjoint steps on consecutive rows (rows[0] is table row
+// row0) by one launch, and sets what each row of it asks of memory: a state or adjoint
+// state that is the previous row's output stays in registers, an output that only the
+// next row reads (the internal buffers of [lo, hi)) is not stored.
+template <typename T>
+void make_resident(std::vector<Launch>& seq, std::vector<StepDev<T>>& rows, int64_t row0, const char* lo, const char* hi) {
+    std::vector<Launch> out;
+    for (const Launch& l : seq) {
+        const bool step = l.op == OP_FWD || l.op == OP_ADJ;
+        if (step && !out.empty() && out.back().op == OP_RES && out.back().row + out.back().row2 == l.row) ++out.back().row2;
+        else if (step) out.push_back({OP_RES, l.row, 1});
+        else out.push_back(l);
+    }
+    seq.swap(out);
+    auto internal = [&](const T* p) { return (const char*)p >= lo && (const char*)p < hi; };
+    for (const Launch& l : seq) {
+        if (l.op != OP_RES) continue;
+        const T *have = nullptr, *have_adj = nullptr;  // memory copies of the registers' state and adjoint state
+        for (int64_t i = l.row - row0, n = i + l.row2; i < n; ++i) {
+            StepDev<T>& r = rows[i];
+            const StepDev<T>* next = i + 1 < n ? &rows[i + 1] : nullptr;
+            r.res = 0;
+            if (r.x != have) r.res |= RES_LOAD | (r.x_abs ? RES_LOAD_ABS : 0);
+            if (r.act) r.res |= RES_ACT;
+            if (!r.adj) {
+                if (r.ckx) r.res |= RES_CKPT;
+                if (!internal(r.xo) || !next || next->x != r.xo) r.res |= RES_STORE | (r.xo_abs ? RES_STORE_ABS : 0);
+                have = r.xo_abs ? nullptr : r.xo;
+            } else {
+                r.res |= RES_ADJ;
+                if (r.xb != have_adj) r.res |= RES_LOAD_ADJ;
+                if (!internal(r.xbo) || !next || !next->adj || next->xb != r.xbo) r.res |= RES_STORE_ADJ;
+                if (r.g_act) {
+                    r.res |= RES_GACT;
+                    if (i > l.row - row0 && rows[i - 1].adj && rows[i - 1].g_act == r.g_act) r.res |= RES_GACT_ON;
+                }
+                have = r.x_abs ? nullptr : r.x;
+                have_adj = r.xbo;
+            }
+        }
+    }
+}
+
 // The second segment buffer is in use (kept last segment; overlapped recompute under
 // plain and graph execution): models without lift/drag, two-pass or persistent execution.
 bool uses_seg2(const gsim_model* m) {
@@ -1168,8 +1277,10 @@ int do_step(gsim_model* m, const gsim_params* p, gsim_state in, gsim_state out, 
         }
         seq.push_back({OP_FWD, r0 + t});
     }
+    const bool res = runs_resident(m);
+    if (res) make_resident(seq, rows, r0, m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, r0, rows, stream))) return rc;
-    return execute<T>(m, (1LL << 40) | n, seq, stream);
+    return execute<T>(m, (1LL << 40) | (res ? RES_KEY : 0) | n, seq, stream);
 }
 
 template <typename T>
@@ -1194,17 +1305,19 @@ int do_step_backward(gsim_model* m, const gsim_params* p, gsim_state s, gsim_sta
     r.ckpt_every = m->K;
     r.adj = 1;
     const int64_t r0 = region_misc(m);
+    std::vector<Launch> seq;
+    if (g && g->contact) seq.push_back({OP_FILL_CPART, r0});
+    seq.push_back({OP_ADJ, r0});
+    if (g && g->contact) seq.push_back({OP_CONTACT_REDUCE, r0});
+    const bool res = runs_resident(m, g);
+    if (res) make_resident(seq, rows, r0, m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, r0, rows, stream))) return rc;
     if (m->exec == GSIM_EXEC_FUSED) {
         const bool act = g && (g->act || g->hact);
         std::vector<Launch> fseq{{OP_FUSED_PARAMS, r0}, {act ? OP_FUSED_ADJ_ACT : OP_FUSED_ADJ, r0}, {OP_FUSED_GRADS, r0}};
         return execute<T>(m, (9LL << 40) | (act ? 1 : 0), fseq, stream);
     }
-    std::vector<Launch> seq;
-    if (g && g->contact) seq.push_back({OP_FILL_CPART, r0});
-    seq.push_back({OP_ADJ, r0});
-    if (g && g->contact) seq.push_back({OP_CONTACT_REDUCE, r0});
-    return execute<T>(m, (2LL << 40) | (g && g->contact ? 1 : 0), seq, stream);
+    return execute<T>(m, (2LL << 40) | (res ? RES_KEY : 0) | (g && g->contact ? 1 : 0), seq, stream);
 }
 
 template <typename T>
@@ -1256,8 +1369,11 @@ int do_rollout(gsim_model* m, const gsim_params* p, gsim_state s0, int n, void* 
         }
         seq.push_back({OP_FWD, region_rollout(m) + t});
     }
+    const bool res = runs_resident(m);
+    if (res) make_resident(seq, rows, region_rollout(m), m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, region_rollout(m), rows, stream))) return rc;
-    if ((rc = execute<T>(m, (3LL << 40) | ((long long)n << 1) | (ckpt ? 1 : 0), seq, stream))) return rc;
+    if ((rc = execute<T>(m, (3LL << 40) | (res ? RES_KEY : 0) | ((long long)n << 1) | (ckpt ? 1 : 0), seq, stream)))
+        return rc;
     if (tail) {
         m->tail_ckpt = ckpt;
         m->tail_seg2 = m->seg2;
@@ -1298,7 +1414,8 @@ int do_rollout_backward(gsim_model* m, const gsim_params* p, const void* ckpt, i
     // buffer and it, and the recompute of segment s - 1 runs in the same launches as
     // segment s's adjoint steps.  When the rollout of these checkpoints left the last
     // segment's states in that buffer, that segment is not recomputed.
-    const bool two = uses_seg2(m), overlap = two && nseg > 1 && m->exec != GSIM_EXEC_PERSIST;
+    const bool res = runs_resident(m, g);
+    const bool two = uses_seg2(m), overlap = two && nseg > 1 && m->exec != GSIM_EXEC_PERSIST && !res;
     const bool kept = two && m->tail_ckpt == ckpt && m->tail_seg2 == m->seg2 && m->tail_n == n;
     m->tail_ckpt = nullptr;  // this call overwrites the second buffer
     auto segbuf = [&](int s) -> T* { return two && ((nseg - 1 - s) & 1) == 0 ? (T*)m->seg2 : (T*)seg; };
@@ -1365,8 +1482,9 @@ int do_rollout_backward(gsim_model* m, const gsim_params* p, const void* ckpt, i
         }
     }
     if (want_contact) seq.push_back({OP_CONTACT_REDUCE, r0});
+    if (res) make_resident(seq, rows, r0, m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, r0, rows, stream))) return rc;
-    return execute<T>(m, (4LL << 40) | (overlap ? 1LL << 39 : 0) | (kept ? 1LL << 38 : 0) | (two ? 1LL << 37 : 0) |
+    return execute<T>(m, (4LL << 40) | (res ? RES_KEY : 0) | (overlap ? 1LL << 39 : 0) | (kept ? 1LL << 38 : 0) | (two ? 1LL << 37 : 0) |
                              ((long long)n << 1) | (want_contact ? 1 : 0),
                       seq, stream);
 }
@@ -1453,6 +1571,8 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
         tp3[3 * i + 2] = P->tp_slot[i];
     }
     chk(up(L.tp, tp3.data(), tp3.size() * 4));
+    chk(up(L.r_code, P->r_code.data(), P->r_code.size() * 4));
+    chk(up(L.r_run, P->r_run.data(), P->r_run.size() * 4));
     chk(up(L.gbase, P->gbase.data(), P->gbase.size() * 4));
     chk(up(L.pdeg, P->pdeg.data(), P->pdeg.size() * 4));
     chk(up(L.pinned, P->pinned.data(), P->pinned.size()));
@@ -1515,6 +1635,9 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
         return wa > wc;
     });
     chk(up(L.border, border.data(), border.size() * 4));
+    m->res_ept = P->res_ept;
+    m->res_block = P->res_block;
+    m->res_lds = P->res_lds;
     m->fused_ok = P->fused_ok;
     m->any_air = P->any_air;
     m->air_on = P->air_on;
@@ -1539,6 +1662,10 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
         B.np = P->poff[b + 1] - P->poff[b];
         B.contact_on = P->contact_on[b];
         B.air_on = P->air_on[b];
+        B.g0 = P->body_g0[b];
+        B.e0 = P->eoff[b];
+        B.ne = (int32_t)(P->eoff[b + 1] - P->eoff[b]);
+        B.nr = P->res_ept ? P->r_slots[b] : 0;
         for (int k = 0; k < 3; ++k) {
             B.cbase[k] = P->cbase[3 * b + k];
             B.ncol[k] = P->ncol[3 * b + k];
@@ -1579,6 +1706,8 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     M.vslots = P->any_air ? (T*)(ws + L.vslots) : nullptr;
     M.cpart = (T*)(ws + L.cpart);
     M.lpart = (T*)(ws + L.lpart);
+    M.r_code = P->res_ept ? (const uint32_t*)(ws + L.r_code) : nullptr;
+    M.r_run = P->res_ept ? (const uint32_t*)(ws + L.r_run) : nullptr;
     M.f_tet_idx = (const int32_t*)(ws + L.f_tet_idx);
     M.f_tet_dinv = (const T*)(ws + L.f_tet_dinv);
     M.f_tet_vol = (const T*)(ws + L.f_tet_vol);

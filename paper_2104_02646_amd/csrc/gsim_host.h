@@ -34,6 +34,12 @@ struct gsim_plan {
     std::vector<int32_t> body_g0;                  // [nb] first slice of each body
     // colour-ordered element copies for the fused path: within each body and kind,
     // elements sorted by (colour, index); no two elements of a colour share a particle
+    // resident execution (see gsim_internal.h): tables, tets per thread (0: the model does
+    // not qualify), threads, LDS bytes of the largest body
+    std::vector<uint32_t> r_code, r_run;
+    std::vector<int32_t> r_slots;                  // [nb] padded corner slots
+    int res_ept = 0, res_block = 0;
+    size_t res_lds = 0;
     bool fused_ok = false;                         // every kind of every body coloured with <= 128 colours
     bool coloured = false;                         // the fused path's colouring was made (not for serving queries)
     std::vector<int32_t> ftet, ftri, fhin;         // fused position -> element index
@@ -68,6 +74,7 @@ struct Layout {
     size_t f_tet_idx, f_tet_dinv, f_tet_vol, f_tet_orig, f_tri_idx, f_tri_dinv, f_tri_area, f_tri_orig;
     size_t f_hin_idx, f_hin_phi0, f_hin_orig, coff, border, f_par, f_ktri, f_g, f_gk, f_hpar, f_gh;
     size_t ntiles, toff;  // persistent execution: natural-order tiles, per-body ranges [2][nb + 1]
+    size_t r_code, r_run;  // resident execution
     size_t table;
     int64_t table_cap;
     size_t total;
@@ -161,6 +168,9 @@ struct gsim_model {
     std::vector<Pending> pending;
     double timing_ms[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t timing_n[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // resident execution: 0 tets per thread = not available
+    int res_ept = 0, res_block = 0;
+    size_t res_lds = 0;
     // fused path
     bool fused_ok = false;   // colouring succeeded for every body and kind
     bool any_air = false;    // some body has lift/drag (not modelled by the fused path)

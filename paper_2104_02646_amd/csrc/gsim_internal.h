@@ -66,6 +66,10 @@ struct BodyDev {
     int64_t p0, np;      // particle range
     int32_t pt0, pt1;    // particle-tile id range (contact-gradient partials)
     int32_t contact_on;  // ground contact active
+    int32_t g0;          // first gather slice of the body
+    int64_t e0;          // first tet of the body
+    int32_t ne;          // its tets
+    int32_t nr;          // resident execution: its corner slots in LDS
     int32_t air_on;      // lift/drag on the body's triangles
     int32_t cbase[3];    // fused path: first colour boundary of each element kind in coff
     int32_t ncol[3];     // fused path: colours of each element kind
@@ -105,6 +109,11 @@ struct ModelDev {
     T* vslots;  // [nslot][4] velocity-adjoint partials of air tiles (null when no body has air)
     T* cpart;   // [n_ptiles][4] contact-gradient partial sums
     T* lpart;   // [n_ptiles] loss partial sums
+    // resident execution (null when the model's bodies do not qualify): corner codes of
+    // the tets (body-local particle | body-level position of the corner << 16), and at a
+    // particle's partial slot the corner run behind it (first position | count << 16)
+    const uint32_t* r_code;
+    const uint32_t* r_run;
     // fused path: element records in colour order (same SoA layouts, corner indices
     // local to the element's body), the original element index of each position
     // (for parameters and gradients), colour bounds
@@ -169,6 +178,8 @@ struct StepDev {
     int32_t x_abs;     // x holds absolute positions (the caller's state), not displacements
     int32_t xo_abs;    // forward: write absolute positions to xo (the caller's state)
     int32_t adj;       // the row is an adjoint step (read by persistent execution)
+    int32_t res;       // resident execution: what the row asks of memory (RES_* bits)
+    int32_t unused;
 };
 
 // Kernel timing: when a pair of events is armed, the next launch of the element and
@@ -205,6 +216,31 @@ int launch_fill(T* p, int64_t n, T value, void* stream);
 template <typename T>
 int launch_persist(const ModelDev<T>* md, const StepDev<T>* rows, int n_rows, const Tile* etiles, const Tile* ptiles,
                    const int32_t* toff, int n_bodies, int block, size_t lds, void* stream);
+// Resident execution of steps rows[0 .. n_rows): workgroup b keeps body b on its compute
+// unit for the whole run (states and corner contributions in LDS, element records,
+// parameters and their gradients in registers: `ept` tets per thread, one particle per
+// thread).  pblock: the particle passes' block size (the contact sums' tree).
+int launch_resident(const ModelDev<float>* md, const StepDev<float>* rows, int n_rows, int n_bodies, int block, int ept,
+                    int pblock, size_t lds, void* stream);
+// Bits of StepDev::res (set for the rows of one launch by the host).
+enum : int32_t {
+    RES_ADJ = 1,         // an adjoint step
+    RES_LOAD = 2,        // its state comes from x, v (otherwise the registers hold it)
+    RES_LOAD_ABS = 4,    // ... absolute positions
+    RES_LOAD_ADJ = 8,    // its adjoint state comes from xb, vb
+    RES_STORE = 16,      // forward: someone reads xo, vo
+    RES_STORE_ABS = 32,  // ... absolute positions
+    RES_CKPT = 64,       // forward: ckx, ckv take the input state
+    RES_STORE_ADJ = 128, // adjoint: someone reads xbo, vbo
+    RES_ACT = 256,       // act is given
+    RES_GACT = 512,      // g_act is wanted
+    RES_GACT_ON = 1024   // g_act is the previous row's array: its sum is in the registers
+};
+// bodies that qualify: tets only, at most RES_EPT tets and one particle per thread
+// (corner runs are padded to a multiple of RES_PAD with slots that stay zero: adding zero
+// to a sum that started from zero changes no bit of it)
+const int RES_BLOCK = 512, RES_EPT = 3, RES_PAD = 4;
+const size_t RES_LDS = 150 * 1024;
 // Overlapped recompute: one element launch (particles = false) or one particle launch
 // (true) running the adjoint pass of row sd_adj and the forward pass of row sd_fwd
 // over the same tile list (models without lift/drag).  Split layout: the forward tiles

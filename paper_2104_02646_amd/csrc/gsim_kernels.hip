@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 #include "gsim_device.h"
@@ -32,9 +33,6 @@
 
 namespace gsim {
 namespace {
-
-__device__ __forceinline__ float gfma(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double gfma(double a, double b, double c) { return fma(a, b, c); }
 
 // Slots are 4-vectors accessed as one 16-byte (FP32) or two 16-byte (FP64)
 // global accesses (clang vector types: they can live in address space 1).
@@ -112,7 +110,8 @@ __device__ __forceinline__ V3<T> load_pos(const ModelDev<T>& M, const T* x, int3
 // Ground gap of particle i at displacement u: its rest gap n.X - d plus n.u.
 template <typename T>
 __device__ __forceinline__ T gap_of(T rgap, const T pl[4], V3<T> u) {
-    return rgap + dot(mk3(pl[0], pl[1], pl[2]), u);
+#pragma clang fp contract(off)
+    return rgap + fdot(mk3(pl[0], pl[1], pl[2]), u);
 }
 
 // Body status words (ModelDev::bflag): a plain store of 1, so any number of threads
@@ -187,44 +186,6 @@ struct TetKin {
     V3<T> Pmu[3];  // columns of dP/dmu
     T s, J1;       // Ic - 3, J - 1
 };
-
-// Every rounding of the tet's arithmetic is written out (contraction off, fused
-// multiply-adds explicit), so that each kernel that evaluates an element, however its
-// loads and branches are arranged, gets the same bits.
-template <typename T>
-__device__ __forceinline__ V3<T> fma3(V3<T> a, T s, V3<T> c) {
-    return mk3(gfma(a.x, s, c.x), gfma(a.y, s, c.y), gfma(a.z, s, c.z));
-}
-template <typename T>
-__device__ __forceinline__ V3<T> mul3(V3<T> a, T s) {
-#pragma clang fp contract(off)
-    return mk3(a.x * s, a.y * s, a.z * s);
-}
-template <typename T>
-__device__ __forceinline__ V3<T> add3(V3<T> a, V3<T> b) {
-#pragma clang fp contract(off)
-    return mk3(a.x + b.x, a.y + b.y, a.z + b.z);
-}
-template <typename T>
-__device__ __forceinline__ V3<T> sub3(V3<T> a, V3<T> b) {
-#pragma clang fp contract(off)
-    return mk3(a.x - b.x, a.y - b.y, a.z - b.z);
-}
-// a s + b t + c r, the first product fused into the rounded second, then the third
-template <typename T>
-__device__ __forceinline__ V3<T> lin3(V3<T> a, T s, V3<T> b, T t, V3<T> c, T r) {
-    return fma3(c, r, fma3(a, s, mul3(b, t)));
-}
-template <typename T>
-__device__ __forceinline__ T fdot(V3<T> a, V3<T> b) {
-#pragma clang fp contract(off)
-    return gfma(a.z, b.z, gfma(a.x, b.x, a.y * b.y));
-}
-template <typename T>
-__device__ __forceinline__ V3<T> fcross(V3<T> a, V3<T> b) {
-#pragma clang fp contract(off)
-    return mk3(gfma(a.y, b.z, -(a.z * b.y)), gfma(a.z, b.x, -(a.x * b.z)), gfma(a.x, b.y, -(a.y * b.x)));
-}
 
 template <typename T>
 __device__ __forceinline__ void tet_kin(const V3<T> u[4], const T D[9], TetKin<T>& k) {
@@ -801,6 +762,15 @@ __global__ void __launch_bounds__(512) k_elem_fwd(const ModelDev<T>* __restrict_
     elem_fwd_tile<T, AIR, ONE>(md[0], sd[0], tiles[blockIdx.x], smem);
 }
 
+// One particle's semi-implicit Euler update under the force f: (u, v) to the end of the
+// step.  Pinned particles (w = 0) feel no gravity.
+template <typename T>
+__device__ __forceinline__ void particle_step(V3<T>& u, V3<T>& v, V3<T> f, T w, V3<T> g, T dt) {
+    const T gate = w > T(0) ? T(1) : T(0);
+    v = fma3(fma3(g, gate, mul3(f, w)), dt, v);
+    u = fma3(v, dt, u);
+}
+
 template <typename T>
 __device__ __forceinline__ void part_fwd_tile(const ModelDev<T>& M, const StepDev<T>& S, const Tile tl) {
     const BodyDev<T>& B = M.bodies[tl.body];
@@ -834,9 +804,8 @@ __device__ __forceinline__ void part_fwd_tile(const ModelDev<T>& M, const StepDe
             st3o(S.ckv + tl.begin, np, o, v);
         }
         if (contact) f += contact_force_gap(gap_of(rg, pl, u), v, pl, cp);
-        const T gate = w > T(0) ? T(1) : T(0);
-        const V3<T> vn = v + (f * w + g * gate) * dt;
-        const V3<T> un = u + vn * dt;
+        V3<T> un = u, vn = v;
+        particle_step(un, vn, f, w, g, dt);
         if (!finite_pair(un, vn)) raise_flag(M, tl.body, 0);
         st3o(S.vo + tl.begin, np, o, vn);
         st3o(S.xo + tl.begin, np, o, S.xo_abs ? ld3o(rest, np, o) + un : un);
@@ -1051,7 +1020,7 @@ __device__ __forceinline__ void part_adj_tile(const ModelDev<T>& M, const StepDe
         V3<T> xs = zero3<T>();
         T ds = T(0);
         sum_slots(M.slots, base, deg, xs, ds);
-        const V3<T> vt = vbp + xbp * dt;
+        const V3<T> vt = fma3(xbp, dt, vbp);
         const V3<T> fb = fbar_of(xbp, vbp, dt, w);
         V3<T> xcb = zero3<T>(), vcb = zero3<T>();
         if (AIR && B.air_on) {  // velocity adjoint of the lift/drag force, same partial slots
@@ -1060,7 +1029,7 @@ __device__ __forceinline__ void part_adj_tile(const ModelDev<T>& M, const StepDe
         }
         if (contact) {
             const V3<T> fc = contact_adjoint_gap(gap_of(rg, pl, u), v, pl, cp, fb, xcb, vcb, gc);
-            ds += dot(fc, fb);
+            ds += fdot(fc, fb);
         }
         const V3<T> xbm = xbp + xs + xcb, vbm = vt + vcb;
         if (!finite_pair(xbm, vbm)) raise_flag(M, tl.body, 0);
@@ -1068,7 +1037,7 @@ __device__ __forceinline__ void part_adj_tile(const ModelDev<T>& M, const StepDe
         st3o(S.vbo + p0, np, o, vbm);
         // the adjoint force of the previous step, for the next adjoint element pass
         if (S.fbo) st3o(S.fbo + p0, np, o, fbar_of(xbm, vbm, dt, w));
-        if (S.g_mass && w > T(0)) gsto(S.g_mass + p0, o, gm0 + -w * ds);  // dm = -w^2 dw, dw = dt f.vt = f.fbar / w
+        if (S.g_mass && w > T(0)) gsto(S.g_mass + p0, o, gfma(-w, ds, gm0));  // dm = -w^2 dw, dw = dt f.vt = f.fbar / w
     }
     if (contact && S.g_contact) {
         T tot[4];
@@ -1114,6 +1083,338 @@ __global__ void __launch_bounds__(512) k_persist(const ModelDev<T>* __restrict__
             __syncthreads();  // the contact reduction's LDS
         }
         __syncthreads();  // (workgroup-scope release and acquire of global memory)
+    }
+}
+
+// A barrier over the workgroup's LDS traffic alone: global loads and stores stay in
+// flight across it (the resident kernel's threads read back only what they wrote
+// themselves), where __syncthreads would wait for every store of the step.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// A row of the launch table in a wavefront: lane i holds word row_word(i) of it, loaded by
+// one vector load several steps ahead; a field is read out of its lanes where its bit of
+// `res` asks for it.  (Scalar loads of the row would share their wait counter with the
+// LDS traffic, and a body of few wavefronts pays for every instruction it issues.)
+template <typename T>
+__device__ __forceinline__ uint32_t row_word(int lane) {  // byte offset in StepDev
+    static_assert(offsetof(StepDev<T>, x) == 0 && offsetof(StepDev<T>, vbo) == 72, "the first ten pointers in order");
+    if (lane < 20) return 4u * lane;  // x, v, xo, vo, ckx, ckv, xb, vb, xbo, vbo
+    if (lane < 22) return (uint32_t)offsetof(StepDev<T>, act) + 4u * (lane - 20);
+    if (lane < 24) return (uint32_t)offsetof(StepDev<T>, g_act) + 4u * (lane - 22);
+    return (uint32_t)offsetof(StepDev<T>, res);
+}
+enum { ROW_X = 0, ROW_V = 2, ROW_XO = 4, ROW_VO = 6, ROW_CKX = 8, ROW_CKV = 10, ROW_XB = 12, ROW_VB = 14, ROW_XBO = 16,
+       ROW_VBO = 18, ROW_ACT = 20, ROW_GACT = 22, ROW_RES = 24 };
+template <typename T>
+__device__ __forceinline__ T* row_ptr(uint32_t words, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)words, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)words, lane + 1);
+    return (T*)(((uint64_t)hi << 32) | lo);
+}
+
+// Resident execution: workgroup b runs body b through a run of steps without leaving its
+// compute unit.  The two-pass layouts pay, per step and pass, a launch (about 1.5 us) and
+// a chain of dependent memory accesses (tile, tile particle, position, partial, state),
+// which is nearly all the time of a body of a few tiles.  Here the state, the adjoint
+// forces and the corner contributions are in LDS, each thread keeps the records,
+// parameters and parameter gradients of its (at most EPT) tets and the state, adjoint
+// state and mass gradient of its one particle in registers, and a step is two barriers:
+//   positions (and adjoint forces) to LDS | barrier | corner contributions of every tet
+//   to LDS | barrier | each particle sums its runs of corners, contact, integration.
+// Memory is touched only where a row asks for it: states the call keeps, the adjoint's
+// stored states (loaded one step ahead), actuation rows and, at the end, the gradients.
+// A row's input that is the previous row's output stays in registers.
+// The corner positions, the runs and the contact sums' tree are those of the element and
+// particle tiles, and the arithmetic is theirs, so every result is bitwise the two-pass
+// one.  The line (plan time): FP32 models of tets only, every body at most RES_EPT tets
+// and one particle per thread of RES_BLOCK, and its LDS.  One compute unit then has up to
+// six wavefronts of tets per SIMD and step to run, which takes as long as the two-pass
+// launches' overhead; beyond it a body's tets are better spread over compute units.
+// What bounds it now: instruction issue and LDS latency of the few wavefronts (a forward
+// step of the 162-tet cube is 1.7 us, of which 570 of 1034 issue slots of its busiest
+// wavefront are used).  Measured, two-pass launches -> resident: gradient of 100 steps of
+// the 162-tet cube 1604 -> 676 us; 50 steps of one body of 432 tets 791 -> 454 us, of
+// 1200 tets 883 -> 652 us; of 256 bodies of up to 1260 tets 1467 -> 690 us.
+template <typename T, int EPT>
+__global__ void __launch_bounds__(RES_BLOCK) k_resident(const ModelDev<T>* __restrict__ md,
+                                                        const StepDev<T>* __restrict__ rows, int n_rows, int pblock) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ T red[RES_BLOCK / 64][4];
+    const ModelDev<T>& M = md[0];
+    const BodyDev<T>& B = M.bodies[blockIdx.x];
+    const int tid = threadIdx.x, nth = blockDim.x, body = blockIdx.x;
+    const int npb = (int)B.np, neb = B.ne;
+    L4<T>* xs = reinterpret_cast<L4<T>*>(smem);  // [npb] displacements at the step's start
+    L4<T>* fbs = xs + npb;                       // [npb] adjoint forces
+    L4<T>* cs = fbs + npb;                       // [B.nr] corner contributions, runs padded with zeros
+    for (int i = tid; i < B.nr; i += nth) cs[i] = L4<T>{T(0), T(0), T(0), T(0)};  // (the padding stays zero)
+    const T dt = B.dt;
+    const V3<T> g = mk3(B.g[0], B.g[1], B.g[2]);
+    const bool contact = B.contact_on != 0;
+    T pl[4], cp[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        pl[k] = B.plane[k];
+        cp[k] = contact ? rows[0].contact[4 * body + k] : T(0);
+    }
+    // this thread's tets
+    uint32_t code[EPT][4];
+    const uint32_t eo0 = (uint32_t)sizeof(T) * (uint32_t)(B.e0 + tid), eos = (uint32_t)(sizeof(T) * nth);
+    auto eo = [&](int k) { return eo0 + k * eos; };  // byte offset of tet k in every per-tet array
+    T D[EPT][9], V[EPT], mu[EPT], lam[EPT], gmu[EPT], glam[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        const int l = tid + k * nth;
+        if (l < neb) {
+            const uint32_t o = eo(k);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) code[k][c] = gldo(M.r_code + c * M.ne, 4u * (uint32_t)(B.e0 + l));
+#pragma unroll
+            for (int q = 0; q < 9; ++q) D[k][q] = gldo(M.tet_dinv + q * M.ne, o);
+            V[k] = gldo(M.tet_vol, o);
+            mu[k] = gldo(rows[0].mu, o);
+            lam[k] = gldo(rows[0].lam, o);
+        }
+        gmu[k] = glam[k] = T(0);
+    }
+    // this thread's particle; the byte offsets of its x, y and z in a state
+    const bool own = tid < npb;
+    const uint32_t px = (uint32_t)sizeof(T) * (uint32_t)(B.p0 + tid), py = px + (uint32_t)(sizeof(T) * M.np),
+                   pz = py + (uint32_t)(sizeof(T) * M.np);
+    auto ld = [&](const T* s) { return mk3(gldo(s, px), gldo(s, py), gldo(s, pz)); };
+    auto st = [&](T* s, V3<T> a) {
+        gsto(s, px, a.x);
+        gsto(s, py, a.y);
+        gsto(s, pz, a.z);
+    };
+    T w = T(0), rg = T(0), gm = T(0);
+    int deg = 0;
+    int64_t slot = 0;
+    uint32_t run[SLOT_BATCH];
+    if (own) {
+        w = inv_mass(M, rows[0], B.p0, (uint32_t)tid);
+        if (contact) rg = gldo(M.rgap, px);
+        deg = gld(M.pdeg, B.p0 + tid);
+        slot = (int64_t)gld(M.gbase, B.g0 + (tid >> 6)) + (tid & 63);
+    }
+#pragma unroll
+    for (int k = 0; k < SLOT_BATCH; ++k) run[k] = k < deg ? gld(M.r_run, slot + 64 * k) : 0u;
+    V3<T> u = zero3<T>(), v = zero3<T>(), xb = zero3<T>(), vb = zero3<T>();
+    // gradient outputs (the same in every adjoint row)
+    T *og_mu = nullptr, *og_lam = nullptr, *og_mass = nullptr, *og_contact = nullptr;
+    T ct[4] = {T(0), T(0), T(0), T(0)};  // contact sums of the tile this thread leads
+    const int lead = tid / pblock;       // (particle tiles of pblock particles)
+    const bool leads = contact && tid % pblock == 0 && tid < npb;
+    bool adjoint_seen = false;
+    const uint32_t word = row_word<T>(tid & 63);
+    auto row_at = [&](int r) { return gldo(reinterpret_cast<const uint32_t*>(rows + min(r, n_rows - 1)), word); };
+    auto bits_of = [](uint32_t row) { return __builtin_amdgcn_readlane((int)row, ROW_RES); };
+    auto load_state = [&](uint32_t row, int bits, V3<T>& a, V3<T>& b) {
+        if (own) {
+            a = ld(row_ptr<T>(row, ROW_X));
+            b = ld(row_ptr<T>(row, ROW_V));
+            if (bits & RES_LOAD_ABS) a = sub3(a, ld(M.rest));
+        }
+    };
+    T act[EPT], gact[EPT];  // this row's actuation and its gradient
+    auto load_tets = [&](uint32_t row, int field, T a[EPT]) {
+        const T* p = row_ptr<T>(row, field);
+#pragma unroll
+        for (int k = 0; k < EPT; ++k)
+            if (tid + k * nth < neb) a[k] = gldo(p, eo(k));
+    };
+    uint32_t row = row_at(0), row1 = row_at(1), row2 = row_at(2);
+    int bits = bits_of(row);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) act[k] = gact[k] = T(0);
+    if (bits & RES_ACT) load_tets(row, ROW_ACT, act);
+    load_state(row, bits, u, v);
+    // everything loaded so far has landed: no wait for it is left inside the loop
+    __builtin_amdgcn_s_waitcnt(0);
+    for (int r = 0; r < n_rows; ++r) {
+        const bool adj = bits & RES_ADJ;
+        const int bits1 = r + 1 < n_rows ? bits_of(row1) : 0;
+        if (adj) {
+            if (!adjoint_seen) {  // gradients so far
+                adjoint_seen = true;
+                og_mu = rows[r].g_mu;
+                og_lam = rows[r].g_lam;
+                og_mass = rows[r].g_mass;
+                og_contact = rows[r].g_contact;
+#pragma unroll
+                for (int k = 0; k < EPT; ++k) {
+                    const bool live = tid + k * nth < neb;
+                    if (live && og_mu) gmu[k] = gldo(og_mu, eo(k));
+                    if (live && og_lam) glam[k] = gldo(og_lam, eo(k));
+                }
+                if (own && og_mass) gm = gldo(og_mass, px);
+                if (leads && og_contact)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) ct[k] = gld(M.cpart, 4 * (int64_t)(B.pt0 + lead) + k);
+                __builtin_amdgcn_s_waitcnt(0);
+            }
+            // (one gradient array for every step: its sum so far is the one last stored)
+            if ((bits & RES_GACT) && !(bits & RES_GACT_ON)) load_tets(row, ROW_GACT, gact);
+            if ((bits & RES_LOAD_ADJ) && own) {
+                xb = ld(row_ptr<T>(row, ROW_XB));
+                vb = ld(row_ptr<T>(row, ROW_VB));
+            }
+        }
+        V3<T> fb = zero3<T>();
+        if (own) {
+            xs[tid] = l4(u, T(0));
+            if (adj) {
+                fb = fbar_of(xb, vb, dt, w);
+                fbs[tid] = l4(fb, T(0));
+            }
+        }
+        lds_barrier();
+        // what the next row reads from memory, in flight during this one
+        V3<T> un = zero3<T>(), vn = zero3<T>();
+        T act1[EPT];
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) act1[k] = T(0);
+        if (bits1 & RES_LOAD) load_state(row1, bits1, un, vn);
+        if (bits1 & RES_ACT) load_tets(row1, ROW_ACT, act1);
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) {
+            if (tid + k * nth >= neb) break;
+            V3<T> x[4], f[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = v3(xs[code[k][c] & 0xffffu]);
+            if (!adj) {
+                T J1;
+                tet_force(x, D[k], V[k], mu[k], lam[k], act[k], f, J1);
+                if (J1 <= T(-1)) raise_flag(M, body, 1);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) cs[code[k][c] >> 16] = l4(f[c], T(0));
+            } else {
+                V3<T> fc[4], xc[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) fc[c] = v3(fbs[code[k][c] & 0xffffu]);
+                tet_adjoint(x, D[k], V[k], mu[k], lam[k], act[k], fc, f, xc, gmu[k], glam[k], gact[k]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) cs[code[k][c] >> 16] = l4(xc[c], fdot(f[c], fc[c]));
+                if (bits & RES_GACT) gsto(row_ptr<T>(row, ROW_GACT), eo(k), gact[k]);
+            }
+        }
+        lds_barrier();
+        // each particle: its runs of corners, one partial after another
+        V3<T> fs = zero3<T>();
+        T ds = T(0);
+        auto add_run = [&](uint32_t rr) {  // RES_PAD corners at a time, the next ones on their way
+            const L4<T>* c = cs + (rr & 0xffffu);
+            const L4<T>* end = c + (rr >> 16);
+            V3<T> f = zero3<T>();
+            T d = T(0);
+            L4<T> q[RES_PAD];
+#pragma unroll
+            for (int j = 0; j < RES_PAD; ++j) q[j] = c[j];
+            for (c += RES_PAD; c < end; c += RES_PAD) {
+                L4<T> n[RES_PAD];
+#pragma unroll
+                for (int j = 0; j < RES_PAD; ++j) n[j] = c[j];
+#pragma unroll
+                for (int j = 0; j < RES_PAD; ++j) {
+                    f += v3(q[j]);
+                    d += q[j].w;
+                    q[j] = n[j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < RES_PAD; ++j) {
+                f += v3(q[j]);
+                d += q[j].w;
+            }
+            fs += f;
+            ds += d;
+        };
+        if (own) {
+#pragma unroll
+            for (int k = 0; k < SLOT_BATCH; ++k)
+                if (k < deg) add_run(run[k]);
+            for (int k = SLOT_BATCH; k < deg; ++k) add_run(gld(M.r_run, slot + 64 * k));
+        }
+        // the loads for the rows ahead are taken up here, before this row's stores: memory
+        // operations complete in order, and a wait below would be one for the stores
+        asm volatile("" : "+v"(un.x), "+v"(un.y), "+v"(un.z), "+v"(vn.x), "+v"(vn.y), "+v"(vn.z), "+v"(row2));
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) asm volatile("" : "+v"(act1[k]));
+        if (!adj) {
+            if (own) {
+                if (bits & RES_CKPT) {
+                    st(row_ptr<T>(row, ROW_CKX), u);
+                    st(row_ptr<T>(row, ROW_CKV), v);
+                }
+                if (contact) fs += contact_force_gap(gap_of(rg, pl, u), v, pl, cp);
+                particle_step(u, v, fs, w, g, dt);
+                if (!finite_pair(u, v)) raise_flag(M, body, 0);
+                if (bits & RES_STORE) {
+                    st(row_ptr<T>(row, ROW_VO), v);
+                    st(row_ptr<T>(row, ROW_XO), bits & RES_STORE_ABS ? add3(ld(M.rest), u) : u);
+                }
+            }
+        } else {
+            T gc[4] = {T(0), T(0), T(0), T(0)};
+            if (own) {
+                const V3<T> vt = fma3(xb, dt, vb);
+                V3<T> xcb = zero3<T>(), vcb = zero3<T>();
+                if (contact) {
+                    const V3<T> fc = contact_adjoint_gap(gap_of(rg, pl, u), v, pl, cp, fb, xcb, vcb, gc);
+                    ds += fdot(fc, fb);
+                }
+                xb = xb + fs + xcb;
+                vb = vt + vcb;
+                if (!finite_pair(xb, vb)) raise_flag(M, body, 0);
+                if (w > T(0)) gm = gfma(-w, ds, gm);
+                if (bits & RES_STORE_ADJ) {
+                    st(row_ptr<T>(row, ROW_XBO), xb);
+                    st(row_ptr<T>(row, ROW_VBO), vb);
+                }
+            }
+            if (contact && og_contact) {  // per particle tile, the tree of block_sum
+                wave_sum<T, 4>(gc);
+                if ((tid & 63) == 0)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) red[tid >> 6][k] = gc[k];
+                lds_barrier();
+                if (leads) {
+                    const int w0 = tid >> 6, w1 = min((nth + 63) >> 6, w0 + (pblock >> 6));
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        T s = T(0);
+                        for (int q = w0; q < w1; ++q) s += red[q][k];
+                        ct[k] += s;
+                    }
+                }
+            }
+        }
+        // on to the next row
+        if (bits1 & RES_LOAD) {
+            u = un;
+            v = vn;
+        }
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) act[k] = act1[k];
+        bits = bits1;
+        row = row1;
+        row1 = row2;
+        row2 = row_at(r + 3);
+    }
+    if (adjoint_seen) {
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) {
+            const bool live = tid + k * nth < neb;
+            if (live && og_mu) gsto(og_mu, eo(k), gmu[k]);
+            if (live && og_lam) gsto(og_lam, eo(k), glam[k]);
+        }
+        if (own && og_mass && w > T(0)) gsto(og_mass, px, gm);
+        if (leads && og_contact)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) gst(M.cpart, 4 * (int64_t)(B.pt0 + lead) + k, ct[k]);
     }
 }
 
@@ -1960,6 +2261,23 @@ int launch_dual(const ModelDev<T>* md, const StepDev<T>* sd_adj, const StepDev<T
     launch_timed(k_part_dual<T>, dim3(pspan + n_ptiles), dim3(pblock), 0, (hipStream_t)stream, md, sd_adj, ptiles,
                  n_ptiles, pspan, sd_fwd, ptiles);
     return check_launch();
+}
+template <int EPT>
+int launch_resident_v(const ModelDev<float>* md, const StepDev<float>* rows, int n_rows, int n_bodies, int block,
+                      int pblock, size_t lds, void* stream) {
+    static size_t allowed = 48 * 1024;
+    allow_lds(reinterpret_cast<const void*>(&k_resident<float, EPT>), lds, allowed);
+    hipLaunchKernelGGL((k_resident<float, EPT>), dim3(n_bodies), dim3(block), lds, (hipStream_t)stream, md, rows, n_rows,
+                       pblock);
+    return check_launch();
+}
+int launch_resident(const ModelDev<float>* md, const StepDev<float>* rows, int n_rows, int n_bodies, int block, int ept,
+                    int pblock, size_t lds, void* stream) {
+    if (n_rows <= 0 || n_bodies <= 0) return 0;
+    if (ept == 1) return launch_resident_v<1>(md, rows, n_rows, n_bodies, block, pblock, lds, stream);
+    if (ept == 2) return launch_resident_v<2>(md, rows, n_rows, n_bodies, block, pblock, lds, stream);
+    static_assert(RES_EPT == 3, "one variant per tets-per-thread count");
+    return launch_resident_v<3>(md, rows, n_rows, n_bodies, block, pblock, lds, stream);
 }
 int launch_stage_copy(const StageSeg* segs, int n_segs, void* stream) {
     if (n_segs <= 0) return 0;

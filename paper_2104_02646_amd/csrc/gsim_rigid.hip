@@ -78,80 +78,6 @@ struct RigidArgs {
     T* g_contact;
 };
 
-// Lane exchanges in the vector units, by 32-bit halves for doubles.
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double x) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-// a + (a of the other half-wave) in lanes 0-31 and the same of b in lanes 32-63.
-template <bool HALF>
-__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
-    if constexpr (HALF) {
-        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-        a = r[0];
-        b = r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-        a = r[0];
-        b = r[1];
-    }
-}
-template <bool HALF>
-__device__ __forceinline__ float swap_add(float a, float b) {
-    uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
-    swap_rows<HALF>(x, y);
-    return __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
-}
-template <bool HALF>
-__device__ __forceinline__ double swap_add(double a, double b) {
-    const uint64_t p = __builtin_bit_cast(uint64_t, a), q = __builtin_bit_cast(uint64_t, b);
-    uint32_t xl = (uint32_t)p, xh = (uint32_t)(p >> 32), yl = (uint32_t)q, yh = (uint32_t)(q >> 32);
-    swap_rows<HALF>(xl, yl);
-    swap_rows<HALF>(xh, yh);
-    return __builtin_bit_cast(double, ((uint64_t)xh << 32) | xl) + __builtin_bit_cast(double, ((uint64_t)yh << 32) | yl);
-}
-__device__ __forceinline__ float lane_of(float x, int lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
-}
-__device__ __forceinline__ double lane_of(double x, int lane) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// Sums of N values over the wavefront's 64 lanes; every lane gets every total.  All
-// lanes must be active.  Four values share a register after the half-wave and the row
-// exchange (value 4k in row 0, 4k + 2 in row 1, 4k + 1 in row 2, 4k + 3 in row 3); the
-// sum over a row's 16 lanes is a fixed tree (lanes 8, 4, 2, 1 apart).
-template <typename T, int N>
-__device__ __forceinline__ void wave_sum(T v[N]) {
-    constexpr int H = (N + 1) / 2, Q = (N + 3) / 4;
-    T h[2 * Q];
-#pragma unroll
-    for (int i = 0; i < H; ++i) h[i] = swap_add<true>(v[2 * i], 2 * i + 1 < N ? v[2 * i + 1] : T(0));
-    if constexpr (H < 2 * Q) h[2 * Q - 1] = T(0);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        T r = swap_add<false>(h[2 * i], h[2 * i + 1]);
-        r += dpp<0x128>(r);  // row_ror:8
-        r += dpp<0x124>(r);  // row_ror:4 (lanes 8 apart are equal by now)
-        r += dpp<0x4e>(r);   // quad_perm [2, 3, 0, 1]
-        r += dpp<0xb1>(r);   // quad_perm [1, 0, 3, 2]
-        const int row[4] = {0, 32, 16, 48};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (4 * i + k < N) v[4 * i + k] = lane_of(r, row[k]);
-    }
-}
-
 template <typename T>
 __device__ __forceinline__ void quat_rot(const T q[4], T R[9]) {
     const T w = q[0], a = q[1], b = q[2], c = q[3];
