@@ -640,6 +640,16 @@ void natural_tiles(const gsim_model* m, bool particles, int tile, std::vector<Ti
         }
 }
 
+// Lanes nobody asked for are used only where they pay: a second stream hides one lane's
+// particle pass behind the other's element pass, which needs launches that fill the card,
+// and costs a second set of launches.  Measured over ragged tet batches (100 steps, one
+// lane / two, us): gradient at 61 tiles 1754 / 2767, 493 tiles 2046 / 2632, 917 tiles
+// 2485 / 2883, 1252 tiles 3015 / 2784, 3570 tiles 6412 / 5548; rollout at 489 tiles
+// 815 / 1518, 1641 tiles 1284 / 1331 (1280 / 1446 as a graph), 1980 tiles 1532 / 1391.
+// 16 cloths with lift/drag (105 tiles), gradient: 2412 / 2947.
+const int LANES_MIN_TILES = 1024;      // element tiles (4 per CU); below: one lane
+const int LANES_MIN_TILES_FWD = 1792;  // (7 per CU) sequences of forward passes alone
+
 template <typename T>
 int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     std::vector<Tile> et, pt;
@@ -648,8 +658,9 @@ int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     natural_tiles(m, true, m->pblock * m->pitems, m->ptiles_nat, m->n_ptile_rows);
     // launch lanes: bodies assigned largest first to the lane with the least work so
     // far; each lane's tiles are XCD-ordered on their own and the lists concatenated
+    m->run_lanes = !m->lanes_chosen && (int)m->etiles_nat.size() < LANES_MIN_TILES ? 1 : m->lanes;
     std::vector<int> lane(m->nb, 0);
-    if (m->lanes > 1) {
+    if (m->run_lanes > 1) {
         std::vector<int> order(m->nb);
         for (int b = 0; b < m->nb; ++b) order[b] = b;
         auto work = [&](int b) {
@@ -660,7 +671,7 @@ int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
         int64_t load[MAX_LANES] = {};
         for (int b : order) {
             int l = 0;
-            for (int k = 1; k < m->lanes; ++k)
+            for (int k = 1; k < m->run_lanes; ++k)
                 if (load[k] < load[l]) l = k;
             lane[b] = l;
             load[l] += work(b);
@@ -672,7 +683,7 @@ int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
         out.clear();
         for (int l = 0; l <= MAX_LANES; ++l) bounds[l] = 0;
         for (int l = 0; l < MAX_LANES; ++l) air_from[l] = 0;
-        for (int l = 0; l < m->lanes; ++l) {
+        for (int l = 0; l < m->run_lanes; ++l) {
             for (int air = 0; air < 2; ++air) {
                 std::vector<Tile> mine, ord;
                 for (const Tile& t : nat)
@@ -688,8 +699,8 @@ int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     };
     by_lane(m->etiles_nat, TILE_TET, 0, et, m->lane_e, m->lane_e_air);
     by_lane(m->ptiles_nat, TILE_PART, m->n_ptile_rows, pt, m->lane_p, m->lane_p_air);
-    m->n_etiles = m->lane_e[m->lanes];
-    m->n_ptiles = m->lane_p[m->lanes];
+    m->n_etiles = m->lane_e[m->run_lanes];
+    m->n_ptiles = m->lane_p[m->run_lanes];
     hipStream_t s = (hipStream_t)stream;
     auto up = [&](void* dst, const void* src, size_t n) -> hipError_t {
         if (n == 0) return hipSuccess;
@@ -828,7 +839,12 @@ template <typename T>
 int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
     Ctx<T> c = ctx<T>(m);
     const ModelDev<T>* md = c.md;
-    const int nl = m->timing_mask == 0 ? m->lanes : 1;
+    int nl = m->timing_mask == 0 ? m->run_lanes : 1;
+    if (!m->lanes_chosen && !m->any_air && m->n_etiles < LANES_MIN_TILES_FWD) {
+        bool forward = true;  // (a sequence of forward passes alone)
+        for (const Launch& l : seq) forward = forward && l.op == OP_FWD;
+        if (forward) nl = 1;
+    }
     const bool one = m->etile_max <= m->block;  // every tile's elements fit one per thread
     hipStream_t s0 = (hipStream_t)stream;
     bool forked = false;
@@ -868,7 +884,7 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
             return ranges(m->lane_e[l], m->lane_e_air[l], m->lane_e[l + 1], m->lane_p[l], m->lane_p_air[l],
                           m->lane_p[l + 1], l > 0 ? (void*)m->lane_stream[l] : stream, sd, adjoint);
         if (!m->any_air) return ranges(0, m->n_etiles, m->n_etiles, 0, m->n_ptiles, m->n_ptiles, stream, sd, adjoint);
-        for (int k = 0; k < m->lanes; ++k)
+        for (int k = 0; k < m->run_lanes; ++k)
             if (int rc = ranges(m->lane_e[k], m->lane_e_air[k], m->lane_e[k + 1], m->lane_p[k], m->lane_p_air[k],
                                 m->lane_p[k + 1], stream, sd, adjoint))
                 return rc;
@@ -1928,7 +1944,8 @@ int gsim_model_set_lanes(gsim_model* m, int lanes) {
     if (!m) return fail(GSIM_E_INVALID, "NULL model");
     if (lanes < 1 || lanes > MAX_LANES) return fail(GSIM_E_INVALID, "lanes must be 1..%d", MAX_LANES);
     if (lanes > m->nb) return fail(GSIM_E_UNSUPPORTED, "%d lanes need at least %d bodies", lanes, lanes);
-    if (m->lanes == lanes) return GSIM_OK;
+    m->lanes_chosen = true;
+    if (m->lanes == lanes && m->run_lanes == lanes) return GSIM_OK;
     HIP_TRY(hipDeviceSynchronize(), "synchronize before retiling");
     m->lanes = lanes;
     return guarded<double>([&]() { return m->dtype == GSIM_F64 ? upload_tiles<double>(m, nullptr) : upload_tiles<float>(m, nullptr); });

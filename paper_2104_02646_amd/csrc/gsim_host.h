@@ -136,7 +136,10 @@ struct gsim_model {
     // lane the tiles of bodies with air come last, from lane_e_air[l] / lane_p_air[l]:
     // they run the kernel variant with lift/drag, the others the plain one, so a
     // body's arithmetic never depends on the rest of its batch.
-    int lanes = 1;
+    // run_lanes: the lanes the tiles are laid out for (`lanes`, or 1 for a small model
+    // that nobody chose lanes for, see upload_tiles).
+    int lanes = 1, run_lanes = 1;
+    bool lanes_chosen = false;        // gsim_model_set_lanes was called
     int lane_e[gsim::MAX_LANES + 1] = {}, lane_p[gsim::MAX_LANES + 1] = {};
     int lane_e_air[gsim::MAX_LANES] = {}, lane_p_air[gsim::MAX_LANES] = {};
     hipStream_t lane_stream[gsim::MAX_LANES] = {};

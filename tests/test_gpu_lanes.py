@@ -1,0 +1,52 @@
+"""Launch lanes that nobody chose: a model runs on one lane, on two, or on one for its
+forward sequences alone, by its count of element tiles.  Results are bitwise those of
+lanes set explicitly, on each side of both thresholds and with lift/drag bodies mixed in."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_02646_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def run(gs, bodies, tile, exec_mode, lanes, T=6, K=3):
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        m = gs.Model(bodies, torch.float32, max_steps=T, ckpt_every=K, tile_elems=tile)
+        m.set_exec(exec_mode)
+        assert m.get_lanes() == 2
+        if lanes:
+            m.set_lanes(lanes)
+            assert m.get_lanes() == lanes
+        p = m.params_from_bodies()
+        x0, v0 = (gs.soa(np.concatenate([getattr(b, k) for b in bodies]), dtype=torch.float32) for k in ("x0", "v0"))
+        tg = gs.soa(np.concatenate([W.synthetic_target(b, 7 + i) for i, b in enumerate(bodies)]), dtype=torch.float32)
+        xT, vT = m.rollout(p, x0, v0, T, stream=stream)
+        loss, xb, vb = m.loss_mse(xT, tg, stream=stream)
+        g = m.zero_grads(("mu", "lam", "ktri", "mass", "contact"))
+        xb0, vb0 = m.rollout_backward(p, T, xb, vb, g, stream=stream)
+        stream.synchronize()
+    out = {"x": xT, "v": vT, "loss": loss, "xb": xb0, "vb": vb0, **g}
+    return {k: v.detach().cpu().numpy() for k, v in out.items()}
+
+
+@pytest.mark.parametrize("case,tile", [("small", 0), ("mixed air", 0), ("forward", 64), ("many", 64)])
+def test_default_lanes_bitwise(case, tile):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2104_02646_amd import gsim as gs
+    gs.load()
+    n = {"small": 3, "mixed air": 2, "forward": 24, "many": 40}[case]
+    bodies = [W.batch_body(5000 + i, lo=2800, hi=4000).round_to(np.float32) for i in range(n)]
+    if case == "mixed air":
+        bodies += [W.control_cloth(31).round_to(np.float32), W.control_cloth(32).round_to(np.float32)]
+    tiles = sum(-(-b.ne // 64) for b in bodies)
+    if tile:  # between the thresholds of gradients and of rollouts, and above both
+        assert (1024 < tiles < 1700) if case == "forward" else tiles > 1792
+    for exec_mode in (gs.EXEC_PLAIN, gs.EXEC_GRAPH):
+        ref = run(gs, bodies, tile, exec_mode, 0)
+        for lanes in (1, 2):
+            got = run(gs, bodies, tile, exec_mode, lanes)
+            for k in ref:
+                assert np.array_equal(ref[k], got[k]), (k, lanes, exec_mode)
