@@ -111,17 +111,21 @@ struct Query {
     double t_submit = 0;
 };
 
-struct Live {
-    std::unique_ptr<Query> q;
-    gsim_model* model = nullptr;
-    size_t off = 0;  // pool region
-    char* base = nullptr;
+// A query's place in its schedule.
+struct Cursor {
     int phase = PH_FWD;
     int t = 0;         // forward step
     int seg = 0;       // current backward segment
     int j = 0;         // recompute index inside the segment (j < L-1), then adjoint
     int ta = 0;        // next adjoint step
     int qa = 0;        // adjoint steps done
+};
+
+struct Live : Cursor {
+    std::unique_ptr<Query> q;
+    gsim_model* model = nullptr;
+    size_t off = 0;  // pool region
+    char* base = nullptr;
     double t_admit = 0;
     float* F(size_t o) const { return reinterpret_cast<float*>(base + o); }
 };
@@ -176,6 +180,15 @@ struct Pool {
 };
 
 const int RING = 4;  // tick tables in flight
+const int PLAN_ROUNDS = 8;  // rounds planned ahead at most
+
+// A planned round: each live query's operation, and where its tables lie in the ring slot.
+struct Round {
+    std::vector<int> ops;
+    int n_seg[2] = {0, 0}, total[2] = {0, 0}, grid[2] = {0, 0};  // element, particle pass
+    size_t o_sd = 0, o_seg[2] = {0, 0};
+};
+
 const size_t STAGE_CHUNK_BYTES = 8 << 20;  // per staging chunk (host and device), 4 chunks
 const size_t RESULT_RING_BYTES = 32 << 20;  // pinned ring of results on their way out
 
@@ -321,6 +334,9 @@ struct gsim_engine {
     Stager stage;         // the queries' set-up copies
     ResultRing results;   // finished queries' results on their way to the host
     bool round_finished = false;  // the current round issued result copies
+    std::vector<Round> rounds;    // planned rounds (plan_rounds), issued up to next_round
+    size_t next_round = 0;
+    int round_slot = 0;           // the ring slot that holds their tables
 };
 
 namespace {
@@ -397,14 +413,15 @@ void base_step(const Live& L, StepDev<float>& r) {
     r.contact = L.F(ly.contact);
 }
 
-// Decides the next micro-step of a live query and fills its launch record.
-int next_op(const Live& L, StepDev<float>& r) {
+// Decides the micro-step of a live query at place `c` of its schedule and fills its
+// launch record.
+int next_op(const Live& L, const Cursor& c, StepDev<float>& r) {
     const Query& q = *L.q;
     const QLayout& ly = q.lay;
     const int64_t S = 6 * q.np, np = q.np;
     base_step(L, r);
-    if (L.phase == PH_FWD) {
-        const int t = L.t;
+    if (c.phase == PH_FWD) {
+        const int t = c.t;
         r.x = t == 0 ? L.F(ly.s0) : L.F((t - 1) & 1 ? ly.sB : ly.sA);
         r.v = r.x + 3 * np;
         r.x_abs = t == 0;  // the uploaded start state is absolute; later states are displacements
@@ -416,7 +433,7 @@ int next_op(const Live& L, StepDev<float>& r) {
         }
         return OP_FWD;
     }
-    if (L.phase == PH_LOSS) {
+    if (c.phase == PH_LOSS) {
         const int t = q.T - 1;
         r.x = L.F(t & 1 ? ly.sB : ly.sA);
         r.target = L.F(ly.target);
@@ -425,29 +442,29 @@ int next_op(const Live& L, StepDev<float>& r) {
         r.vbo = r.xbo + 3 * np;
         return OP_LOSS;
     }
-    if (L.phase == PH_BWD) {
-        const int t0 = L.seg * q.K, t1 = std::min(q.T, t0 + q.K), Ls = t1 - t0;
-        const float* ck = L.F(ly.ckpt) + (int64_t)L.seg * S;
+    if (c.phase == PH_BWD) {
+        const int t0 = c.seg * q.K, t1 = std::min(q.T, t0 + q.K), Ls = t1 - t0;
+        const float* ck = L.F(ly.ckpt) + (int64_t)c.seg * S;
         float* sg = L.F(ly.seg);
-        if (L.j + 1 < Ls) {  // recompute state t0 + j + 1
-            r.x = L.j == 0 ? ck : sg + (int64_t)(L.j - 1) * S;
+        if (c.j + 1 < Ls) {  // recompute state t0 + j + 1
+            r.x = c.j == 0 ? ck : sg + (int64_t)(c.j - 1) * S;
             r.v = r.x + 3 * np;
-            r.xo = sg + (int64_t)L.j * S;
+            r.xo = sg + (int64_t)c.j * S;
             r.vo = r.xo + 3 * np;
             return OP_FWD;
         }
-        const int t = L.ta;
+        const int t = c.ta;
         r.x = t == t0 ? ck : sg + (int64_t)(t - t0 - 1) * S;
         r.v = r.x + 3 * np;
-        r.xb = L.qa == 0 ? L.F(ly.seed) : L.F((L.qa - 1) & 1 ? ly.aB : ly.aA);
+        r.xb = c.qa == 0 ? L.F(ly.seed) : L.F((c.qa - 1) & 1 ? ly.aB : ly.aA);
         r.vb = r.xb + 3 * np;
-        r.xbo = L.F(L.qa & 1 ? ly.aB : ly.aA);
+        r.xbo = L.F(c.qa & 1 ? ly.aB : ly.aA);
         r.vbo = r.xbo + 3 * np;
         // adjoint-force hand-off (as in the rollout backward): this step's particle pass
         // stores step t-1's adjoint force, the element pass of the next one reads it
         float* fbar = reinterpret_cast<float*>(L.model->ws + L.model->L.fbar);
-        if (t > 0) r.fbo = fbar + (int64_t)(L.qa & 1) * 3 * np;
-        if (L.qa > 0) r.fb = fbar + (int64_t)((L.qa - 1) & 1) * 3 * np;
+        if (t > 0) r.fbo = fbar + (int64_t)(c.qa & 1) * 3 * np;
+        if (c.qa > 0) r.fb = fbar + (int64_t)((c.qa - 1) & 1) * 3 * np;
         r.g_mu = q.ne ? L.F(ly.g_mu) : nullptr;
         r.g_lam = q.ne ? L.F(ly.g_lam) : nullptr;
         r.g_ktri = q.nt ? L.F(ly.g_ktri) : nullptr;
@@ -459,36 +476,35 @@ int next_op(const Live& L, StepDev<float>& r) {
     return OP_FIN;
 }
 
-void advance(Live& L, int op) {
-    const Query& q = *L.q;
-    if (op == OP_FWD && L.phase == PH_FWD) {
-        if (++L.t == q.T) L.phase = PH_LOSS;
+void advance(const Query& q, Cursor& c, int op) {
+    if (op == OP_FWD && c.phase == PH_FWD) {
+        if (++c.t == q.T) c.phase = PH_LOSS;
         return;
     }
     if (op == OP_LOSS) {
-        L.phase = PH_BWD;
-        L.seg = (q.T + q.K - 1) / q.K - 1;
-        L.j = 0;
-        L.ta = q.T - 1;
-        L.qa = 0;
+        c.phase = PH_BWD;
+        c.seg = (q.T + q.K - 1) / q.K - 1;
+        c.j = 0;
+        c.ta = q.T - 1;
+        c.qa = 0;
         return;
     }
     if (op == OP_FWD) {  // recompute
-        L.j++;
+        c.j++;
         return;
     }
     if (op == OP_ADJ) {
-        L.qa++;
-        const int t0 = L.seg * q.K;
-        if (L.ta == t0) {
-            if (L.seg == 0) {
-                L.phase = PH_FIN;
+        c.qa++;
+        const int t0 = c.seg * q.K;
+        if (c.ta == t0) {
+            if (c.seg == 0) {
+                c.phase = PH_FIN;
                 return;
             }
-            L.seg--;
-            L.j = 0;
+            c.seg--;
+            c.j = 0;
         }
-        L.ta--;
+        c.ta--;
     }
 }
 
@@ -593,59 +609,100 @@ int finish(gsim_engine* E, Live& L) {
     return GSIM_OK;
 }
 
-// One micro-step of every live query: plan each query's next operation, upload the
-// round's tables in one copy, run the singular launches (loss seeds, final
-// reductions), then one element launch and one particle launch over the forward and
-// the adjoint tiles of every query together; finally advance the queries and finish
-// the completed ones.
+// Plans the next rounds of the live queries and uploads their tables in one copy: as many
+// as the ring slot holds, up to PLAN_ROUNDS and to the first round in which a query
+// finishes, since the tables hold until the live set changes (after an admission what is
+// left of them is dropped).  A copy per round cost more host time than the round's two
+// launches: 12 queries of 64 to 120 steps (350 rounds) took 8.6 ms with one, 6.0 ms with
+// a copy for up to 8 rounds.
+int plan_rounds(gsim_engine* E) {
+    const int n = (int)E->live.size();
+    const size_t md_sz = sizeof(ModelDev<float>), sd_sz = sizeof(StepDev<float>);
+    const int r = E->ring;
+    HIP_TRY(hipEventSynchronize(E->blob_evt[r]), "wait for table ring");
+    char* h = E->blob_host[r];
+    E->rounds.clear();
+    E->next_round = 0;
+    for (int i = 0; i < n; ++i) std::memcpy(h + i * md_sz, E->live[i].model->md_host.data(), md_sz);
+    size_t o = aup(md_sz * n);
+    std::vector<Cursor> at(E->live.begin(), E->live.end());  // the queries' places in their schedules
+    std::vector<StepDev<float>> sd(n);
+    bool last = false;
+    while (!last && (int)E->rounds.size() < PLAN_ROUNDS) {
+        Round R;
+        R.ops.resize(n);
+        for (int i = 0; i < n; ++i) R.ops[i] = next_op(E->live[i], at[i], sd[i]);
+        // segment tables: each query with a forward or adjoint micro-step contributes its
+        // resident element tiles and particle tiles; each workgroup of the round's two
+        // launches finds its tile in them (XCD order over the concatenation)
+        std::vector<TileSeg> seg[2];  // element pass, particle pass
+        for (int i = 0; i < n; ++i) {
+            if (R.ops[i] != OP_FWD && R.ops[i] != OP_ADJ) continue;
+            const Live& L = E->live[i];
+            const Tile* t = reinterpret_cast<const Tile*>(L.base + L.q->lay.tiles);
+            const int32_t flags = R.ops[i] == OP_ADJ ? TILE_ADJ : 0;
+            const int cnt[2] = {L.q->n_etiles, L.q->n_ptiles};
+            for (int k = 0; k < 2; ++k) {
+                if (cnt[k] == 0) continue;
+                seg[k].push_back({k == 0 ? t : t + L.q->n_etiles, R.total[k], cnt[k], i, flags});
+                R.total[k] += cnt[k];
+            }
+        }
+        for (int k = 0; k < 2; ++k) {
+            R.n_seg[k] = (int)seg[k].size();
+            R.grid[k] = R.total[k] < N_XCD ? R.total[k] : (R.total[k] + N_XCD - 1) / N_XCD * N_XCD;
+        }
+        R.o_sd = o;
+        R.o_seg[0] = aup(R.o_sd + sd_sz * n);
+        R.o_seg[1] = aup(R.o_seg[0] + sizeof(TileSeg) * seg[0].size());
+        const size_t end = aup(R.o_seg[1] + sizeof(TileSeg) * seg[1].size());
+        const bool tiles = R.grid[0] > E->max_tiles || R.grid[1] > E->max_tiles, bytes = end > E->head_bytes;
+        if ((tiles || bytes) && !E->rounds.empty()) break;  // a later plan's first round
+        if (tiles)
+            return fail(GSIM_E_WORKSPACE, "a round needs %d / %d tiles, the engine holds %lld", R.grid[0], R.grid[1],
+                        (long long)E->max_tiles);
+        if (bytes) return fail(GSIM_E_WORKSPACE, "round tables exceed the engine's table capacity");
+        std::memcpy(h + R.o_sd, sd.data(), sd_sz * n);
+        for (int k = 0; k < 2; ++k)
+            if (!seg[k].empty()) std::memcpy(h + R.o_seg[k], seg[k].data(), sizeof(TileSeg) * seg[k].size());
+        o = end;
+        for (int i = 0; i < n; ++i) {
+            last = last || R.ops[i] == OP_FIN;
+            advance(*E->live[i].q, at[i], R.ops[i]);
+        }
+        E->rounds.push_back(std::move(R));
+    }
+    E->ring = (E->ring + 1) % RING;
+    E->round_slot = r;
+    if (hipError_t e = hipMemcpyAsync(E->blob_dev[r], h, o, hipMemcpyHostToDevice, E->stream)) {
+        E->rounds.clear();
+        return hip_fail(e, "upload round tables");
+    }
+    return GSIM_OK;
+}
+
+// One micro-step of every live query, from the planned tables: the singular launches
+// (loss seeds, final reductions), then one element launch and one particle launch over
+// the forward and the adjoint tiles of every query together; finally advance the queries
+// and finish the completed ones.
 int micro_round(gsim_engine* E) {
     const int n = (int)E->live.size();
     E->ticks++;
     E->live_sum += n;
-    std::vector<int> ops(n);
-    std::vector<StepDev<float>> sd(n);
-    for (int i = 0; i < n; ++i) ops[i] = next_op(E->live[i], sd[i]);
-    // segment tables: each query with a forward or adjoint micro-step contributes its
-    // resident element tiles and particle tiles; each workgroup of the round's two
-    // launches finds its tile in them (XCD order over the concatenation)
-    std::vector<TileSeg> seg[2];  // element pass, particle pass
-    int total[2] = {0, 0};
-    for (int i = 0; i < n; ++i) {
-        if (ops[i] != OP_FWD && ops[i] != OP_ADJ) continue;
-        const Live& L = E->live[i];
-        const Tile* t = reinterpret_cast<const Tile*>(L.base + L.q->lay.tiles);
-        const int32_t flags = ops[i] == OP_ADJ ? TILE_ADJ : 0;
-        const int cnt[2] = {L.q->n_etiles, L.q->n_ptiles};
-        for (int k = 0; k < 2; ++k) {
-            if (cnt[k] == 0) continue;
-            seg[k].push_back({k == 0 ? t : t + L.q->n_etiles, total[k], cnt[k], i, flags});
-            total[k] += cnt[k];
-        }
+    if (E->next_round < E->rounds.size() && (int)E->rounds[E->next_round].ops.size() != n) {
+        // queries were admitted: the rest of the plan is dropped, and its slot stays in use
+        // up to the launches so far
+        HIP_TRY(hipEventRecord(E->blob_evt[E->round_slot], E->stream), "record tick");
+        E->next_round = E->rounds.size();
     }
-    int grid[2];
-    for (int k = 0; k < 2; ++k)
-        grid[k] = total[k] < N_XCD ? total[k] : (total[k] + N_XCD - 1) / N_XCD * N_XCD;
-    if (grid[0] > E->max_tiles || grid[1] > E->max_tiles)
-        return fail(GSIM_E_WORKSPACE, "a round needs %d / %d tiles, the engine holds %lld", grid[0], grid[1],
-                    (long long)E->max_tiles);
-    // one upload: [ModelDev x n][StepDev x n][element segments][particle segments]
-    const size_t md_sz = sizeof(ModelDev<float>), sd_sz = sizeof(StepDev<float>);
-    const size_t o_md = 0, o_sd = aup(md_sz * n), o_s0 = aup(o_sd + sd_sz * n);
-    const size_t o_s1 = aup(o_s0 + sizeof(TileSeg) * seg[0].size());
-    const size_t o = aup(o_s1 + sizeof(TileSeg) * seg[1].size());
-    if (o > E->head_bytes) return fail(GSIM_E_WORKSPACE, "round tables exceed the engine's table capacity");
-    const int r = E->ring;
-    E->ring = (E->ring + 1) % RING;
-    HIP_TRY(hipEventSynchronize(E->blob_evt[r]), "wait for table ring");
-    char* h = E->blob_host[r];
-    for (int i = 0; i < n; ++i) std::memcpy(h + o_md + i * md_sz, E->live[i].model->md_host.data(), md_sz);
-    std::memcpy(h + o_sd, sd.data(), sd_sz * n);
-    std::memcpy(h + o_s0, seg[0].data(), sizeof(TileSeg) * seg[0].size());
-    std::memcpy(h + o_s1, seg[1].data(), sizeof(TileSeg) * seg[1].size());
+    if (E->next_round == E->rounds.size())
+        if (int rc = plan_rounds(E)) return rc;
+    const Round R = std::move(E->rounds[E->next_round++]);
+    const std::vector<int>& ops = R.ops;
+    const int r = E->round_slot;
     char* d = E->blob_dev[r];
-    HIP_TRY(hipMemcpyAsync(d, h, o, hipMemcpyHostToDevice, E->stream), "upload tick tables");
-    const ModelDev<float>* dmd = reinterpret_cast<const ModelDev<float>*>(d + o_md);
-    const StepDev<float>* dsd = reinterpret_cast<const StepDev<float>*>(d + o_sd);
+    const ModelDev<float>* dmd = reinterpret_cast<const ModelDev<float>*>(d);
+    const StepDev<float>* dsd = reinterpret_cast<const StepDev<float>*>(d + R.o_sd);
     const int dummy_row = E->live[0].model->n_ptile_rows;  // empty tiles reduce into model 0's spare row
     // per-query singular launches (loss seed, contact reduction)
     for (int i = 0; i < n; ++i) {
@@ -667,11 +724,11 @@ int micro_round(gsim_engine* E) {
         if (ops[i] == OP_FWD) lds = std::max(lds, (size_t)m->etile_words[0] * sizeof(float));
         if (ops[i] == OP_ADJ) lds = std::max(lds, (size_t)m->etile_words[1] * sizeof(float));
     }
-    LAUNCH_TRY(launch_mixed<float>(dmd, dsd, reinterpret_cast<const TileSeg*>(d + o_s0), (int)seg[0].size(), total[0],
-                                   grid[0], reinterpret_cast<const TileSeg*>(d + o_s1), (int)seg[1].size(), total[1],
-                                   grid[1], dummy_row, block, lds, one, E->stream),
+    LAUNCH_TRY(launch_mixed<float>(dmd, dsd, reinterpret_cast<const TileSeg*>(d + R.o_seg[0]), R.n_seg[0], R.total[0],
+                                   R.grid[0], reinterpret_cast<const TileSeg*>(d + R.o_seg[1]), R.n_seg[1], R.total[1],
+                                   R.grid[1], dummy_row, block, lds, one, E->stream),
                "element and particle passes");
-    HIP_TRY(hipEventRecord(E->blob_evt[r], E->stream), "record tick");
+    if (E->next_round == E->rounds.size()) HIP_TRY(hipEventRecord(E->blob_evt[r], E->stream), "record tick");
     // advance; finish completed queries
     std::vector<Live> keep;
     keep.reserve(n);
@@ -683,7 +740,7 @@ int micro_round(gsim_engine* E) {
             if (rc) return rc;
             continue;
         }
-        advance(L, ops[i]);
+        advance(*L.q, L, ops[i]);
         keep.push_back(std::move(L));
     }
     E->live.swap(keep);
