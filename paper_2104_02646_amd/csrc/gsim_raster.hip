@@ -14,15 +14,15 @@
 // which needs no division by 1 - D_j, and d(d^2) / d(endpoint) of the nearest edge
 // point q = s0 + t (s1 - s0) is -2 (1 - t) (p - q) and -2 t (p - q).
 //
-// Kernels: projection (one thread per vertex); triangle records (one thread per
-// triangle: widened box, corners, orientation, reciprocal edge lengths, and each
-// chunk's box); forward (an 8 x 8 pixel tile per workgroup; the records of the
-// triangles whose widened box reaches the tile are compacted through LDS in order,
-// RCHUNK at a time, and split over the workgroup's RSLICE wavefronts); triangle adjoint
-// (16 lanes per triangle over the pixels of its widened box, the transmittance
-// recomputed by the forward kernels first); vertex gather (one thread per vertex
-// summing its triangle corners in a fixed order, then through the projection).  No
-// atomics anywhere: results are bitwise repeatable.
+// Kernels: triangle records (one thread per triangle: its corners projected, widened
+// box, orientation, reciprocal edge lengths, and each chunk's box); forward (an 8 x 8
+// or 4 x 4 pixel tile per workgroup: the chunks whose box reaches the tile are listed,
+// the records of their triangles that reach it are compacted through LDS in order, and
+// the wavefronts share the tile's 4 x 4 quadrants); triangle adjoint (one wavefront, or
+// a workgroup, per triangle over the pixels of its widened box, the transmittance recomputed by the
+// forward kernels first); vertex gather (one thread per vertex summing its triangle
+// corners in a fixed order, then through the projection).  No atomics anywhere: results
+// are bitwise repeatable.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,36 +39,37 @@
 namespace gsim {
 namespace {
 
-constexpr int RT = 8;             // pixel tile edge: one wavefront's 8 x 8 pixels
-constexpr int RSLICE = 8;         // wavefronts per tile, each over every 8th kept triangle
-constexpr int RCHUNK = 512;       // triangles staged per LDS chunk (one per thread)
-constexpr int RREC = 16;          // values per triangle record
-constexpr int RLANES = 16;        // lanes per triangle in the adjoint
+constexpr int RSLICE = 8;         // wavefronts per pixel tile
+constexpr int RCHUNK = 64;        // triangles per chunk (one wavefront's)
+constexpr int RROUND = 64 * RSLICE;  // triangles a round stages, and chunks a lookup tests
+constexpr int RBOX = 4;           // values per triangle box
+constexpr int RREC = 10;          // values per triangle record
+constexpr int RTERM = 16;         // values per staged record
 const double RCUT = 13.815510557964274;  // -ln(1e-6)
 
-// Per-triangle record, written once per frame: [0..3] bounding box widened by the
-// cut-off distance (xmin, xmax, ymin, ymax); [4..9] screen corners a, b, c;
-// [10] orientation (+1, -1, 0 for a degenerate triangle); [11..13] reciprocal
-// squared lengths of the edges ab, bc, ca; [14, 15] unused.
+// Per-triangle box and record, written once per frame.  Box: the bounding box widened by
+// the cut-off distance (xmin, xmax, ymin, ymax).  Record: [0..5] screen corners a, b, c;
+// [6] orientation (+1, -1, 0 for a degenerate triangle); [7..9] reciprocal squared lengths
+// of the edges ab, bc, ca.  Boxes stand apart because most triangles are only tested.
 template <typename T>
 struct RasterArgs {
     const int32_t* tris;   // [nt][3]
     const int32_t* coff;   // [nv + 1] vertex -> corner list
     const int32_t* cent;   // [3 nt] corner = 3 tri + k
-    T* uvw;                // [nv][3]: u, v, P2.[X,1]
     T* trans;              // [H][W]
     T* cg;                 // [nt][6] screen-space gradient of each corner
+    T* tbox;               // [nt][RBOX] triangle boxes
     T* trec;               // [nt][RREC] triangle records
-    T* cbox;               // [ceil(nt / RCHUNK)][4] widened box of each chunk of triangles
+    T* cbox;               // [ceil(nt / RCHUNK)][RBOX] widened box of each chunk of triangles
     int64_t nv, nt;
     int32_t H, W;
     T P[12];
     T isigma, cut;         // 1 / sigma; cut = CUT sigma
 };
 
-template <typename T>
-struct alignas(16) Rec {
-    T v[RREC];
+template <typename T, int N>
+struct alignas(16) Vec {
+    T v[N];
 };
 
 template <typename T>
@@ -76,62 +77,75 @@ __device__ __forceinline__ T cr2(T ax, T ay, T bx, T by) {
     return ax * by - ay * bx;
 }
 
-// Squared distance from p to segment s0 -> s1 (inv: 1 / |s1 - s0|^2) and the
-// parameter t of the nearest point.
+// A record as tri_term takes it: corners [0..5], edge vectors ab, bc, ca [6..11],
+// orientation [12], reciprocal squared edge lengths [13..15].
 template <typename T>
-__device__ __forceinline__ T seg_d2(T px, T py, T ax, T ay, T bx, T by, T inv, T& t) {
-    const T ex = bx - ax, ey = by - ay, wx = px - ax, wy = py - ay;
+__device__ __forceinline__ void term_of(const T* q, T* r) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int n = k == 2 ? 0 : k + 1;
+        r[2 * k] = q[2 * k];
+        r[2 * k + 1] = q[2 * k + 1];
+        r[6 + 2 * k] = q[2 * n] - q[2 * k];
+        r[7 + 2 * k] = q[2 * n + 1] - q[2 * k + 1];
+        r[13 + k] = q[7 + k];
+    }
+    r[12] = q[6];
+}
+
+// Squared distance from a point at w from the segment's start to the segment e (inv: 1 /
+// |e|^2) and the parameter t of the nearest point.
+template <typename T>
+__device__ __forceinline__ T seg_d2(T wx, T wy, T ex, T ey, T inv, T& t) {
     t = fmin(fmax((wx * ex + wy * ey) * inv, T(0)), T(1));  // (a zero-length edge: t = 0)
     const T dx = wx - t * ex, dy = wy - t * ey;
     return dx * dx + dy * dy;
 }
 
-// Signed scaled distance x = +-d^2 / sigma of pixel p to the triangle of record q;
-// returns false when the term is dropped.  edge / t: the nearest edge (0: ab,
-// 1: bc, 2: ca; the first minimum) and its parameter.
+// Signed scaled distance x = +-d^2 / sigma of pixel p to the triangle of q (see term_of);
+// returns false when the term is dropped.  edge / t: the nearest edge (0: ab, 1: bc,
+// 2: ca; the first minimum) and its parameter.
 template <typename T>
 __device__ __forceinline__ bool tri_term(T px, T py, const T* q, T isigma, T cut, T& x, int& edge, T& t) {
-    const T ax = q[4], ay = q[5], bx = q[6], by = q[7], cx = q[8], cy = q[9], s = q[10];
-    const T e0 = s * cr2(bx - ax, by - ay, px - ax, py - ay);
-    const T e1 = s * cr2(cx - bx, cy - by, px - bx, py - by);
-    const T e2 = s * cr2(ax - cx, ay - cy, px - cx, py - cy);
-    const bool inside = s != T(0) && e0 >= T(0) && e1 >= T(0) && e2 >= T(0);
-    T t0, t1, t2;
-    const T d0 = seg_d2(px, py, ax, ay, bx, by, q[11], t0);
-    const T d1 = seg_d2(px, py, bx, by, cx, cy, q[12], t1);
-    const T d2 = seg_d2(px, py, cx, cy, ax, ay, q[13], t2);
-    T d = d0;
+    T wx[3], wy[3], d[3], tk[3];
+    bool inside = q[12] != T(0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        wx[k] = px - q[2 * k];
+        wy[k] = py - q[2 * k + 1];
+        inside = inside & (q[12] * cr2(q[6 + 2 * k], q[7 + 2 * k], wx[k], wy[k]) >= T(0));
+        d[k] = seg_d2(wx[k], wy[k], q[6 + 2 * k], q[7 + 2 * k], q[13 + k], tk[k]);
+    }
+    T m = d[0];
     edge = 0;
-    t = t0;
-    if (d1 < d) { d = d1; edge = 1; t = t1; }
-    if (d2 < d) { d = d2; edge = 2; t = t2; }
-    if (!inside && d > cut) return false;
-    x = (inside ? d : -d) * isigma;
+    t = tk[0];
+    if (d[1] < m) { m = d[1]; edge = 1; t = tk[1]; }
+    if (d[2] < m) { m = d[2]; edge = 2; t = tk[2]; }
+    if (!inside && m > cut) return false;
+    x = (inside ? m : -m) * isigma;
     return true;
 }
 
 __device__ __forceinline__ float sigm(float x) { return 1.f / (1.f + expf(-x)); }
 __device__ __forceinline__ double sigm(double x) { return 1.0 / (1.0 + exp(-x)); }
 
+// Screen position of vertex i and its depth P2.[X, 1].
 template <typename T>
-__global__ __launch_bounds__(256) void k_raster_project(RasterArgs<T> A, const T* __restrict__ x) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= A.nv) return;
+__device__ __forceinline__ V3<T> project(const RasterArgs<T>& A, const T* __restrict__ x, int64_t i) {
     const V3<T> X = ld3(x, A.nv, i);
     const T n0 = A.P[0] * X.x + A.P[1] * X.y + A.P[2] * X.z + A.P[3];
     const T n1 = A.P[4] * X.x + A.P[5] * X.y + A.P[6] * X.z + A.P[7];
     const T dn = A.P[8] * X.x + A.P[9] * X.y + A.P[10] * X.z + A.P[11];
-    A.uvw[3 * i] = n0 / dn;
-    A.uvw[3 * i + 1] = n1 / dn;
-    A.uvw[3 * i + 2] = dn;
+    return {n0 / dn, n1 / dn, dn};
 }
 
-// One thread per triangle: its record, and the union of the widened boxes of each
-// chunk of RCHUNK triangles (so a tile can skip whole chunks).
+// One thread per triangle: its corners projected (a chain of three loads bounds the
+// kernel, so projecting a vertex once per triangle costs less than a launch that does it
+// once), its box and record, and the union of the boxes of each chunk of RCHUNK
+// triangles, one wavefront's (so a tile can skip whole chunks).
 template <typename T>
-__global__ __launch_bounds__(RCHUNK) void k_raster_tri_prep(RasterArgs<T> A) {
-    __shared__ T red[4][RCHUNK];
-    const int64_t j = (int64_t)blockIdx.x * RCHUNK + threadIdx.x;
+__global__ __launch_bounds__(256) void k_raster_tri_prep(RasterArgs<T> A, const T* __restrict__ x) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const T r = sqrt(A.cut);
     T b[4] = {T(INFINITY), T(-INFINITY), T(INFINITY), T(-INFINITY)};
     // a triangle with a corner index outside [0, nv) (possible only with a caller's
@@ -144,160 +158,218 @@ __global__ __launch_bounds__(RCHUNK) void k_raster_tri_prep(RasterArgs<T> A) {
             ci[k] = A.tris[3 * j + k];
             valid = valid && ci[k] >= 0 && ci[k] < A.nv;
         }
-    if (j < A.nt && !valid) {
-#pragma unroll
-        for (int k = 0; k < RREC; ++k) A.trec[RREC * j + k] = k < 4 ? b[k] : T(0);
-    }
-    if (valid) {
+    bool nan = false;
+    if (j < A.nt) {
         T q[RREC];
-        for (int k = 0; k < 3; ++k) {
-            const int32_t i = ci[k];
-            q[4 + 2 * k] = A.uvw[3 * i];
-            q[5 + 2 * k] = A.uvw[3 * i + 1];
+#pragma unroll
+        for (int k = 0; k < RREC; ++k) q[k] = T(0);
+        if (valid) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const V3<T> u = project(A, x, ci[k]);
+                q[2 * k] = u.x;
+                q[2 * k + 1] = u.y;
+            }
+            const T ax = q[0], ay = q[1], bx = q[2], by = q[3], cx = q[4], cy = q[5];
+            b[0] = fmin(fmin(ax, bx), cx) - r;
+            b[1] = fmax(fmax(ax, bx), cx) + r;
+            b[2] = fmin(fmin(ay, by), cy) - r;
+            b[3] = fmax(fmax(ay, by), cy) + r;
+            nan = b[0] != b[0] || b[2] != b[2];
+            const T area = cr2(bx - ax, by - ay, cx - ax, cy - ay);
+            q[6] = area > T(0) ? T(1) : (area < T(0) ? T(-1) : T(0));
+            q[7] = T(1) / ((bx - ax) * (bx - ax) + (by - ay) * (by - ay));
+            q[8] = T(1) / ((cx - bx) * (cx - bx) + (cy - by) * (cy - by));
+            q[9] = T(1) / ((ax - cx) * (ax - cx) + (ay - cy) * (ay - cy));
         }
-        const T ax = q[4], ay = q[5], bx = q[6], by = q[7], cx = q[8], cy = q[9];
-        b[0] = fmin(fmin(ax, bx), cx) - r;
-        b[1] = fmax(fmax(ax, bx), cx) + r;
-        b[2] = fmin(fmin(ay, by), cy) - r;
-        b[3] = fmax(fmax(ay, by), cy) + r;
-        const T area = cr2(bx - ax, by - ay, cx - ax, cy - ay);
-        q[0] = b[0];
-        q[1] = b[1];
-        q[2] = b[2];
-        q[3] = b[3];
-        q[10] = area > T(0) ? T(1) : (area < T(0) ? T(-1) : T(0));
-        q[11] = T(1) / ((bx - ax) * (bx - ax) + (by - ay) * (by - ay));
-        q[12] = T(1) / ((cx - bx) * (cx - bx) + (cy - by) * (cy - by));
-        q[13] = T(1) / ((ax - cx) * (ax - cx) + (ay - cy) * (ay - cy));
-        q[14] = T(0);
-        q[15] = T(0);
+#pragma unroll
+        for (int k = 0; k < RBOX; ++k) A.tbox[RBOX * j + k] = b[k];
 #pragma unroll
         for (int k = 0; k < RREC; ++k) A.trec[RREC * j + k] = q[k];
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) red[k][threadIdx.x] = b[k];
-    __syncthreads();
-    for (int h = RCHUNK / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            red[0][threadIdx.x] = fmin(red[0][threadIdx.x], red[0][threadIdx.x + h]);
-            red[1][threadIdx.x] = fmax(red[1][threadIdx.x], red[1][threadIdx.x + h]);
-            red[2][threadIdx.x] = fmin(red[2][threadIdx.x], red[2][threadIdx.x + h]);
-            red[3][threadIdx.x] = fmax(red[3][threadIdx.x], red[3][threadIdx.x + h]);
-        }
-        __syncthreads();
+    // (a box that is not a number is tested as reached everywhere, and so is its chunk's)
+    if (nan) {
+        b[0] = b[2] = T(-INFINITY);
+        b[1] = b[3] = T(INFINITY);
     }
-    if (threadIdx.x < 4) A.cbox[4 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) {
+        b[0] = fmin(b[0], __shfl_xor(b[0], h));
+        b[1] = fmax(b[1], __shfl_xor(b[1], h));
+        b[2] = fmin(b[2], __shfl_xor(b[2], h));
+        b[3] = fmax(b[3], __shfl_xor(b[3], h));
+    }
+    const int lane = threadIdx.x & 63;
+    if (lane < RBOX && j - lane < A.nt)
+        A.cbox[RBOX * (j / RCHUNK) + lane] = lane == 0 ? b[0] : lane == 1 ? b[1] : lane == 2 ? b[2] : b[3];
 }
 
-// One 8 x 8 pixel tile per workgroup of RSLICE wavefronts; writes the
-// transmittance and (if not null) the image.  Each chunk of RCHUNK triangle
-// records is tested against the tile (its box widened by the cut-off distance) and
-// the kept ones are compacted into LDS in triangle order; wavefront w then takes
-// kept triangles w, w + RSLICE, ... for all 64 pixels, with the product
-// Q_w = prod (1 + exp(x_j)) per pixel (T = 1 / prod_w Q_w, multiplied in wavefront
-// order: a fixed order, so results are bitwise repeatable).
-template <typename T>
-__global__ __launch_bounds__(64 * RSLICE) void k_raster_fwd(RasterArgs<T> A, T* __restrict__ image) {
-    __shared__ __align__(16) T rec[RCHUNK][RREC];
-    __shared__ T qw[RSLICE][64];
-    __shared__ int wcount[RSLICE];
-    static_assert(RCHUNK == 64 * RSLICE, "one record per thread per chunk");
+// Entries before this thread's among the workgroup's kept ones (in thread order), and
+// their count: the wavefronts' counts through LDS.  Two barriers; `count` must not be in
+// use by an earlier call's readers.
+__device__ __forceinline__ int rank_of(bool keep, int* count, int& total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * RT + (lane & 7), row = blockIdx.y * RT + (lane >> 3);
-    const T px = (T)col + T(0.5), py = (T)row + T(0.5);
+    const unsigned long long m = __ballot(keep);
+    __syncthreads();
+    if (lane == 0) count[wave] = __popcll(m);
+    __syncthreads();
+    int base = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < RSLICE; ++w) {
+        base += w < wave ? count[w] : 0;
+        total += count[w];
+    }
+    return base + __popcll(m & ((1ull << lane) - 1ull));
+}
+
+// One pixel tile of QUADS (4 or 1) quadrants of 4 x 4 pixels per workgroup of RSLICE
+// wavefronts; writes the transmittance and (if not null) the image.  RROUND chunk boxes at
+// a time are tested and the chunks that reach the tile listed in order; RSLICE listed
+// chunks at a time, the triangles whose box (widened by the cut-off distance) reaches a
+// quadrant are compacted into LDS in triangle order.  Each quadrant has RSLICE / QUADS
+// wavefronts: each lists every (RSLICE / QUADS)-th of its quadrant's triangles, and each of
+// its four groups of 16 lanes takes every fourth of those for the quadrant's 16 pixels,
+// with the product prod (1 + exp(x_j)) per pixel; T = 1 / the product of a pixel's partial
+// products, in a fixed order.
+//
+// Bound by the vector units: a triangle's box is mostly margin (its extent plus twice the
+// cut-off distance, 3.7 sqrt(sigma) pixels), so of the (tile, triangle) pairs that survive
+// most pixels of a large tile are out of reach.  4 x 4 pixels per step instead of 8 x 8
+// do 0.6 of the work at 3-pixel triangles.  Boxes of 64 triangles, and boxes apart from
+// records, cut what a tile reads.  Measured with a 64 x 64 cloth (7938 triangles) at
+// 256 x 256: 18.7 us with 8 x 8 steps and chunks of 512 records, 12.7 us so.
+template <typename T, int QUADS>
+__global__ __launch_bounds__(64 * RSLICE) void k_raster_fwd(RasterArgs<T> A, T* __restrict__ image) {
+    constexpr int RT = QUADS == 4 ? 8 : 4;     // tile edge
+    constexpr int SHARE = RSLICE / QUADS;      // wavefronts per quadrant
+    constexpr int PARTS = 4 * SHARE;           // partial products per pixel
+    __shared__ Vec<T, RTERM> rec[RROUND];
+    __shared__ T part[PARTS][RT * RT];
+    __shared__ uint16_t hit[RROUND];
+    __shared__ uint16_t mine[RSLICE][RROUND / SHARE];
+    __shared__ uint8_t reach[RROUND];
+    __shared__ int count[RSLICE];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int quad = wave & (QUADS - 1), turn = wave / QUADS, group = lane >> 4, pix = lane & 15;
+    const int tc = blockIdx.x * RT, tr = blockIdx.y * RT;
+    const T px = (T)(tc + 4 * (quad & 1) + (pix & 3)) + T(0.5), py = (T)(tr + 4 * (quad >> 1) + (pix >> 2)) + T(0.5);
     // the tile's pixel-centre extent
-    const T tx0 = (T)(blockIdx.x * RT) + T(0.5), tx1 = tx0 + T(RT - 1);
-    const T ty0 = (T)(blockIdx.y * RT) + T(0.5), ty1 = ty0 + T(RT - 1);
+    const T tx0 = (T)tc + T(0.5), tx1 = tx0 + T(RT - 1);
+    const T ty0 = (T)tr + T(0.5), ty1 = ty0 + T(RT - 1);
     T Q = T(1);
-    for (int64_t c0 = 0; c0 < A.nt; c0 += RCHUNK) {
-        // whole chunk out of reach: skip (uniform over the workgroup, before any barrier)
-        const T* cb = A.cbox + 4 * (c0 / RCHUNK);
-        if ((cb[1] < tx0) | (cb[0] > tx1) | (cb[3] < ty0) | (cb[2] > ty1)) continue;
-        const int64_t j = c0 + threadIdx.x;
-        T q[RREC];
-        bool keep = false;
-        if (j < A.nt) {
-#pragma unroll
-            for (int k = 0; k < RREC; ++k) q[k] = A.trec[RREC * j + k];
-            keep = !((q[1] < tx0) | (q[0] > tx1) | (q[3] < ty0) | (q[2] > ty1));
+    const int64_t nc = (A.nt + RCHUNK - 1) / RCHUNK;
+    for (int64_t c0 = 0; c0 < nc; c0 += RROUND) {
+        bool near = false;
+        if (c0 + threadIdx.x < nc) {
+            const Vec<T, RBOX> cb = *(const Vec<T, RBOX>*)(A.cbox + RBOX * (c0 + threadIdx.x));
+            near = !((cb.v[1] < tx0) | (cb.v[0] > tx1) | (cb.v[3] < ty0) | (cb.v[2] > ty1));
         }
-        const unsigned long long m = __ballot(keep);
-        const int before = __popcll(m & ((1ull << lane) - 1ull));
-        __syncthreads();  // the previous chunk's records and counts are no longer read
-        if (lane == 0) wcount[wave] = __popcll(m);
+        int hits;
+        const int at = rank_of(near, count, hits);
+        if (near) hit[at] = (uint16_t)threadIdx.x;
         __syncthreads();
-        int base = 0, total = 0;
+        for (int h0 = 0; h0 < hits; h0 += RSLICE) {
+            const int64_t j = h0 + wave < hits ? RCHUNK * (c0 + hit[h0 + wave]) + lane : A.nt;
+            int to = 0;  // quadrants in reach
+            if (j < A.nt) {
+                const Vec<T, RBOX> q = *(const Vec<T, RBOX>*)(A.tbox + RBOX * j);
 #pragma unroll
-        for (int w = 0; w < RSLICE; ++w) {
-            base += w < wave ? wcount[w] : 0;
-            total += wcount[w];
-        }
-        if (keep) {
+                for (int k = 0; k < QUADS; ++k) {
+                    const T x0 = tx0 + T(4 * (k & 1)), y0 = ty0 + T(4 * (k >> 1));
+                    const bool out = (q.v[1] < x0) | (q.v[0] > x0 + T(3)) | (q.v[3] < y0) | (q.v[2] > y0 + T(3));
+                    to |= out ? 0 : 1 << k;
+                }
+            }
+            int total;
+            const int k0 = rank_of(to != 0, count, total);  // (its barriers end the last round's reads)
+            if (to) {
+                T q[RREC];
 #pragma unroll
-            for (int k = 0; k < RREC; ++k) rec[base + before][k] = q[k];
-        }
-        __syncthreads();
-        // whole records through registers, the next one loaded while this one is used
-        Rec<T> cur = *(const Rec<T>*)rec[wave < total ? wave : 0];
-        for (int k = wave; k < total; k += RSLICE) {
-            const int kn = k + RSLICE < total ? k + RSLICE : k;
-            const Rec<T> nxt = *(const Rec<T>*)rec[kn];
-            const T* r = cur.v;
-            if (!((px < r[0]) | (px > r[1]) | (py < r[2]) | (py > r[3]))) {
+                for (int k = 0; k < RREC; ++k) q[k] = A.trec[RREC * j + k];
+                Vec<T, RTERM> r;
+                term_of(q, r.v);
+                rec[k0] = r;
+                reach[k0] = (uint8_t)to;
+            }
+            __syncthreads();
+            // this wavefront's triangles
+            int n = 0;
+            for (int k = 0; k < total; k += 64) {
+                const bool in = k + lane < total && (reach[k + lane] >> quad & 1);
+                const unsigned long long m = __ballot(in);
+                const int o = n + __popcll(m & ((1ull << lane) - 1ull));
+                if (in && o % SHARE == turn) mine[wave][o / SHARE] = (uint16_t)(k + lane);
+                n += __popcll(m);
+            }
+            n = (n + SHARE - 1 - turn) / SHARE;
+            __builtin_amdgcn_wave_barrier();
+            for (int k = group; k < n; k += 4) {
+                const Vec<T, RTERM> r = rec[mine[wave][k]];
                 T x, t;
                 int e;
-                if (tri_term(px, py, r, A.isigma, A.cut, x, e, t)) Q = fma(Q, exp(x), Q);  // Q (1 + e^x)
+                if (tri_term(px, py, r.v, A.isigma, A.cut, x, e, t)) Q = fma(Q, exp(x), Q);  // Q (1 + e^x)
             }
-            cur = nxt;
         }
+        __syncthreads();  // the list of chunks is no longer read
     }
-    qw[wave][lane] = Q;
+    part[4 * turn + group][16 * quad + pix] = Q;
     __syncthreads();
-    if (wave == 0 && col < A.W && row < A.H) {
-        T P = qw[0][lane];
+    const int col = tc + 4 * ((lane >> 4) & 1) + (lane & 3), row = tr + 4 * (lane >> 5) + ((lane >> 2) & 3);
+    if (wave == 0 && lane < RT * RT && col < A.W && row < A.H) {
+        T P = part[0][lane];
 #pragma unroll
-        for (int w = 1; w < RSLICE; ++w) P *= qw[w][lane];
+        for (int w = 1; w < PARTS; ++w) P *= part[w][lane];
         const T tr = T(1) / P;
         A.trans[(int64_t)row * A.W + col] = tr;
         if (image) image[(int64_t)row * A.W + col] = T(1) - tr;
     }
 }
 
-// RLANES lanes per triangle: d <Ibar, I> / d (screen corners) over the pixels of
-// its widened box, strided over the lanes, then a butterfly sum over the lanes
-// (fixed order).  Needs the transmittance of the same x (the forward runs first).
-template <typename T>
-__global__ __launch_bounds__(256) void k_raster_tri_adj(RasterArgs<T> A, const T* __restrict__ ibar) {
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t j = gid / RLANES;
-    const int sub = (int)(gid % RLANES);
-    const bool live = j < A.nt;  // the lanes of a triangle are all live or all not
-    T q[RREC];
+// WAVES wavefronts per triangle: d <Ibar, I> / d (screen corners) over the pixels of its
+// widened box, strided over the lanes, then summed over them (fixed order).  Needs the
+// transmittance of the same x (the forward runs first).  Bound by the chain of one pixel
+// after another in a lane (record, pixel, two image loads, exponential): one wavefront
+// takes the 110 pixels of a 3-pixel triangle in two steps, and the 8 of a workgroup share
+// the thousands of pixels of a triangle where there are few (see raster_backward).
+// Measured, 7938 triangles at 256 x 256: 11.7 us with 16 lanes per triangle, 7.6 us so.
+template <typename T, int WAVES>
+__global__ __launch_bounds__(WAVES == 1 ? 256 : 64 * WAVES) void k_raster_tri_adj(RasterArgs<T> A,
+                                                                                   const T* __restrict__ ibar) {
+    __shared__ T red[WAVES][6];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t j = WAVES == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x;
+    if (j >= A.nt) return;  // the whole wavefront (WAVES > 1: never)
+    T box[RBOX], rec[RREC], q[RTERM];
 #pragma unroll
-    for (int k = 0; k < RREC; ++k) q[k] = live ? A.trec[RREC * (live ? j : 0) + k] : T(0);
+    for (int k = 0; k < RBOX; ++k) box[k] = A.tbox[RBOX * j + k];
+#pragma unroll
+    for (int k = 0; k < RREC; ++k) rec[k] = A.trec[RREC * j + k];
+    term_of(rec, q);
     // pixel index range whose centres lie inside the widened box, clamped into the
     // image before any conversion to int (far or non-finite corners stay in range)
-    const int c0 = (int)fmin(T(A.W), fmax(T(0), ceil(q[0] - T(0.5))));
-    const int c1 = (int)fmax(T(-1), fmin(T(A.W - 1), floor(q[1] - T(0.5))));
-    const int r0 = (int)fmin(T(A.H), fmax(T(0), ceil(q[2] - T(0.5))));
-    const int r1 = (int)fmax(T(-1), fmin(T(A.H - 1), floor(q[3] - T(0.5))));
+    const int c0 = (int)fmin(T(A.W), fmax(T(0), ceil(box[0] - T(0.5))));
+    const int c1 = (int)fmax(T(-1), fmin(T(A.W - 1), floor(box[1] - T(0.5))));
+    const int r0 = (int)fmin(T(A.H), fmax(T(0), ceil(box[2] - T(0.5))));
+    const int r1 = (int)fmax(T(-1), fmin(T(A.H - 1), floor(box[3] - T(0.5))));
     const int bw = c1 >= c0 ? c1 - c0 + 1 : 0;
-    const int npx = live && r1 >= r0 ? bw * (r1 - r0 + 1) : 0;
+    const int npx = r1 >= r0 ? bw * (r1 - r0 + 1) : 0;
     T g[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-    for (int p = sub; p < npx; p += RLANES) {
+    for (int p = WAVES == 1 ? lane : (int)threadIdx.x; p < npx; p += 64 * WAVES) {
         const int row = r0 + p / bw, col = c0 + p % bw;
         const T px = (T)col + T(0.5), py = (T)row + T(0.5);
+        const int64_t pi = (int64_t)row * A.W + col;
+        const T ib = ibar[pi], tr = A.trans[pi];
         T x, t;
         int e;
         if (!tri_term(px, py, q, A.isigma, A.cut, x, e, t)) continue;
-        const int64_t pi = (int64_t)row * A.W + col;
-        const T gx = ibar[pi] * A.trans[pi] * sigm(x);
+        const T gx = ib * tr * sigm(x);
         if (gx == T(0)) continue;
         // x = +-d2 / sigma; d2 = |p - q|^2, q on edge e = (s0, s1)
         const T sgn = x >= T(0) ? T(1) : T(-1);
-        const int i0 = e, i1 = e == 2 ? 0 : e + 1;
-        const T s0x = q[4 + 2 * i0], s0y = q[5 + 2 * i0], s1x = q[4 + 2 * i1], s1y = q[5 + 2 * i1];
-        const T qx = s0x + t * (s1x - s0x), qy = s0y + t * (s1y - s0y);
+        const T s0x = e == 0 ? q[0] : e == 1 ? q[2] : q[4], s0y = e == 0 ? q[1] : e == 1 ? q[3] : q[5];
+        const T ex = e == 0 ? q[6] : e == 1 ? q[8] : q[10], ey = e == 0 ? q[7] : e == 1 ? q[9] : q[11];
+        const T qx = s0x + t * ex, qy = s0y + t * ey;
         const T k = gx * sgn * A.isigma * T(-2);
         const T a = k * (T(1) - t), b = k * t;
         if (e == 0) {
@@ -308,11 +380,20 @@ __global__ __launch_bounds__(256) void k_raster_tri_adj(RasterArgs<T> A, const T
             g[4] += a * (px - qx); g[5] += a * (py - qy); g[0] += b * (px - qx); g[1] += b * (py - qy);
         }
     }
+    wave_sum<T, 6>(g);
+    if constexpr (WAVES > 1) {
+        if (lane == 0)
 #pragma unroll
-    for (int k = 0; k < 6; ++k)
+            for (int k = 0; k < 6; ++k) red[wave][k] = g[k];
+        __syncthreads();
 #pragma unroll
-        for (int h = RLANES / 2; h > 0; h >>= 1) g[k] += __shfl_xor(g[k], h);
-    if (live && sub == 0) {
+        for (int k = 0; k < 6; ++k) {
+            g[k] = red[0][k];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) g[k] += red[w][k];
+        }
+    }
+    if (lane == 0 && (WAVES == 1 || wave == 0)) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) A.cg[6 * j + k] = g[k];
     }
@@ -321,7 +402,8 @@ __global__ __launch_bounds__(256) void k_raster_tri_adj(RasterArgs<T> A, const T
 // One thread per vertex: sum its corners' screen gradients (fixed order), then
 // through the projection; adds to xbar (SoA [3][nv]).
 template <typename T>
-__global__ __launch_bounds__(256) void k_raster_vertex_adj(RasterArgs<T> A, T* __restrict__ xbar) {
+__global__ __launch_bounds__(256) void k_raster_vertex_adj(RasterArgs<T> A, const T* __restrict__ x,
+                                                               T* __restrict__ xbar) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= A.nv) return;
     T gu = T(0), gv = T(0);
@@ -330,8 +412,8 @@ __global__ __launch_bounds__(256) void k_raster_vertex_adj(RasterArgs<T> A, T* _
         gu += A.cg[6 * (c / 3) + 2 * (c % 3)];
         gv += A.cg[6 * (c / 3) + 2 * (c % 3) + 1];
     }
-    const T u = A.uvw[3 * i], v = A.uvw[3 * i + 1], dn = A.uvw[3 * i + 2];
-    const T id = T(1) / dn;
+    const V3<T> at = project(A, x, i);
+    const T u = at.x, v = at.y, id = T(1) / at.z;
 #pragma unroll
     for (int k = 0; k < 3; ++k) xbar[k * A.nv + i] += (gu * (A.P[k] - u * A.P[8 + k]) + gv * (A.P[4 + k] - v * A.P[8 + k])) * id;
 }
@@ -347,7 +429,7 @@ struct gsim_raster {
     int64_t nv = 0, nt = 0;
     int H = 0, W = 0;
     char* ws = nullptr;
-    size_t o_tris = 0, o_coff = 0, o_cent = 0, o_uvw = 0, o_trans = 0, o_cg = 0, o_trec = 0, o_cbox = 0;
+    size_t o_tris = 0, o_coff = 0, o_cent = 0, o_trans = 0, o_cg = 0, o_tbox = 0, o_trec = 0, o_cbox = 0;
 };
 
 namespace {
@@ -363,11 +445,11 @@ size_t raster_layout(gsim_raster* R, size_t tsize) {
     R->o_tris = take(12 * (size_t)R->nt);
     R->o_coff = take(4 * (size_t)(R->nv + 1));
     R->o_cent = take(12 * (size_t)R->nt);
-    R->o_uvw = take(3 * tsize * (size_t)R->nv);
     R->o_trans = take(tsize * (size_t)R->H * R->W);
     R->o_cg = take(6 * tsize * (size_t)R->nt);
+    R->o_tbox = take(RBOX * tsize * (size_t)R->nt);
     R->o_trec = take(RREC * tsize * (size_t)R->nt);
-    R->o_cbox = take(4 * tsize * (size_t)((R->nt + RCHUNK - 1) / RCHUNK));
+    R->o_cbox = take(RBOX * tsize * (size_t)((R->nt + RCHUNK - 1) / RCHUNK));
     return (o + 255) & ~size_t(255);
 }
 
@@ -386,9 +468,9 @@ RasterArgs<T> raster_args(const gsim_raster* R, const gsim_camera* cam) {
     A.tris = (const int32_t*)(R->ws + R->o_tris);
     A.coff = (const int32_t*)(R->ws + R->o_coff);
     A.cent = (const int32_t*)(R->ws + R->o_cent);
-    A.uvw = (T*)(R->ws + R->o_uvw);
     A.trans = (T*)(R->ws + R->o_trans);
     A.cg = (T*)(R->ws + R->o_cg);
+    A.tbox = (T*)(R->ws + R->o_tbox);
     A.trec = (T*)(R->ws + R->o_trec);
     A.cbox = (T*)(R->ws + R->o_cbox);
     A.nv = R->nv;
@@ -417,14 +499,28 @@ int raster_cam_check(const gsim_raster* R, const gsim_camera* cam) {
     return GSIM_OK;
 }
 
+// The forward launches.  4 x 4 tiles give four times the workgroups, each staging its
+// triangles for a quarter of the pixels: they pay where the 8 x 8 tiles would not cover
+// the compute units or hold many triangles each.  Measured (8 x 8 / 4 x 4 tiles, us):
+// 7938 triangles at 60 x 60 71 / 24, 160 x 160 20.3 / 10.6, 200 x 200 (12.7 triangles per
+// tile) 15.4 / 11.7, 256 x 256 (7.8) 12.3 / 14.7, 512 x 512 (1.9) 14.6 / 36; 32258
+// triangles at 256 x 256 (31.5) 33.6 / 26.9, 700 x 700 (4.2) 33.9 / 85; 450 triangles at
+// 124 x 124 (256 tiles) 5.3 / 4.7, 98 at 700 x 700 16 / 51.
+template <typename T>
+hipError_t raster_frame(const gsim_raster* R, const RasterArgs<T>& A, const T* x, T* image, hipStream_t s) {
+    hipLaunchKernelGGL(k_raster_tri_prep<T>, dim3((unsigned)((R->nt + 255) / 256)), dim3(256), 0, s, A, x);
+    const int64_t tiles = (int64_t)((R->W + 7) / 8) * ((R->H + 7) / 8);
+    if (tiles < 256 || R->nt >= 10 * tiles)
+        hipLaunchKernelGGL((k_raster_fwd<T, 1>), dim3((R->W + 3) / 4, (R->H + 3) / 4), dim3(64 * RSLICE), 0, s, A, image);
+    else
+        hipLaunchKernelGGL((k_raster_fwd<T, 4>), dim3((R->W + 7) / 8, (R->H + 7) / 8), dim3(64 * RSLICE), 0, s, A, image);
+    return hipGetLastError();
+}
+
 template <typename T>
 int raster_forward(gsim_raster* R, const gsim_camera* cam, const T* x, T* image, hipStream_t s) {
     RasterArgs<T> A = raster_args<T>(R, cam);
-    hipLaunchKernelGGL(k_raster_project<T>, dim3((unsigned)((R->nv + 255) / 256)), dim3(256), 0, s, A, x);
-    hipLaunchKernelGGL(k_raster_tri_prep<T>, dim3((unsigned)((R->nt + RCHUNK - 1) / RCHUNK)), dim3(RCHUNK), 0, s, A);
-    hipLaunchKernelGGL(k_raster_fwd<T>, dim3((R->W + RT - 1) / RT, (R->H + RT - 1) / RT), dim3(64 * RSLICE), 0, s,
-                       A, image);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = raster_frame<T>(R, A, x, image, s);
     return e == hipSuccess ? GSIM_OK : hip_fail(e, "raster forward");
 }
 
@@ -433,8 +529,14 @@ int raster_backward(gsim_raster* R, const gsim_camera* cam, const T* x, const T*
     int rc = raster_forward<T>(R, cam, x, nullptr, s);  // transmittance and projection of this x
     if (rc) return rc;
     RasterArgs<T> A = raster_args<T>(R, cam);
-    hipLaunchKernelGGL(k_raster_tri_adj<T>, dim3((unsigned)((R->nt * RLANES + 255) / 256)), dim3(256), 0, s, A, ibar);
-    hipLaunchKernelGGL(k_raster_vertex_adj<T>, dim3((unsigned)((R->nv + 255) / 256)), dim3(256), 0, s, A, xbar);
+    // few triangles: a workgroup each, so that large ones do not leave the card to a few
+    // wavefronts (one / eight per triangle: 98 triangles at 700 x 700 70 / 12 us, 450 at
+    // 124 x 124 4.8 / 4.0, 1922 at 400 x 300 5.1 / 6.5)
+    if (R->nt <= 1024)
+        hipLaunchKernelGGL((k_raster_tri_adj<T, 8>), dim3((unsigned)R->nt), dim3(512), 0, s, A, ibar);
+    else
+        hipLaunchKernelGGL((k_raster_tri_adj<T, 1>), dim3((unsigned)((R->nt + 3) / 4)), dim3(256), 0, s, A, ibar);
+    hipLaunchKernelGGL(k_raster_vertex_adj<T>, dim3((unsigned)((R->nv + 255) / 256)), dim3(256), 0, s, A, x, xbar);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? GSIM_OK : hip_fail(e, "raster backward");
 }
@@ -467,8 +569,8 @@ int scratch_ptr(char** out) {
     return GSIM_OK;
 }
 
-// Offsets of the forward's scratch (projected vertices, transmittance, triangle
-// records, chunk boxes) from one base; returns the bytes it needs.
+// Offsets of the forward's scratch (transmittance, triangle boxes and records, chunk
+// boxes) from one base; returns the bytes it needs.
 size_t raster_fwd_layout(gsim_raster* R, size_t tsize) {
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -477,10 +579,10 @@ size_t raster_fwd_layout(gsim_raster* R, size_t tsize) {
         o += std::max<size_t>(bytes, 1);
         return at;
     };
-    R->o_uvw = take(3 * tsize * (size_t)R->nv);
     R->o_trans = take(tsize * (size_t)R->H * R->W);
+    R->o_tbox = take(RBOX * tsize * (size_t)R->nt);
     R->o_trec = take(RREC * tsize * (size_t)R->nt);
-    R->o_cbox = take(4 * tsize * (size_t)((R->nt + RCHUNK - 1) / RCHUNK));
+    R->o_cbox = take(RBOX * tsize * (size_t)((R->nt + RCHUNK - 1) / RCHUNK));
     return (o + 255) & ~size_t(255);
 }
 
@@ -491,11 +593,7 @@ int raster_forward_noalloc(gsim_raster* R, const int32_t* d_tris, const gsim_cam
     A.tris = d_tris;  // the caller's device list (coff, cent, cg: only the adjoint uses them)
     A.coff = A.cent = nullptr;
     A.cg = nullptr;
-    hipLaunchKernelGGL(k_raster_project<T>, dim3((unsigned)((R->nv + 255) / 256)), dim3(256), 0, s, A, x);
-    hipLaunchKernelGGL(k_raster_tri_prep<T>, dim3((unsigned)((R->nt + RCHUNK - 1) / RCHUNK)), dim3(RCHUNK), 0, s, A);
-    hipLaunchKernelGGL(k_raster_fwd<T>, dim3((R->W + RT - 1) / RT, (R->H + RT - 1) / RT), dim3(64 * RSLICE), 0, s,
-                       A, image);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = raster_frame<T>(R, A, x, image, s);
     return e == hipSuccess ? GSIM_OK : hip_fail(e, "raster forward (no allocation)");
 }
 
