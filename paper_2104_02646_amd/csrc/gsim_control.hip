@@ -13,14 +13,19 @@
 // the two sums  sum_t zbar_t sin(omega tau_t)  and  sum_t zbar_t cos(omega tau_t)
 // and maps them back to the N weights with the same phase table.
 //
-// Both kernels stream: one thread per output element walks the steps, so every
-// row access of act / act_grad is one coalesced 1 KB (FP32) wavefront access; the
-// (sin, cos) table of a chunk of steps is computed once per workgroup (FP64,
-// rounded to the dtype) into LDS and read as broadcasts.  The backward issues the
-// loads of CTRL_BATCH steps before using any of them, so each wave keeps several
-// HBM reads in flight.  Forward: reads W once, writes n_steps rows.  Backward:
+// Both kernels stream: WAVES wavefronts share 64 output elements, each walking every
+// WAVES-th batch of steps, so every row access of act / act_grad is one coalesced 256 B
+// (FP32) wavefront access; the (sin, cos) table of a chunk of steps is computed once per
+// workgroup (FP64, rounded to the dtype) into LDS and read as broadcasts.  The backward
+// issues the loads of a batch of steps before using any of them, so each wave keeps
+// several HBM reads in flight.  Forward: reads W once, writes n_steps rows.  Backward:
 // recomputes the layer from W (cheaper than re-reading act), reads n_steps rows of
-// act_grad, and adds its N sums per element to W_grad.
+// act_grad, and adds its N sums per element to W_grad (the wavefronts' sums in order).
+//
+// WAVES = 1 with four element groups per workgroup for large layers, where one thread per
+// element fills the card and the weights are read once; 8 for small ones, which are
+// bound by one thread's chain: the FP64 sines (phases and steps side by side, the weights
+// on their way meanwhile), then a tanh per step.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -30,9 +35,9 @@
 
 namespace {
 
-constexpr int CTRL_BLOCK = 256;
 constexpr int CTRL_CHUNK = 128;  // steps per LDS table
-constexpr int CTRL_BATCH = 8;    // backward: act_grad loads issued together
+constexpr int CTRL_BATCH = 8;    // steps a wavefront takes at a time
+constexpr int CTRL_SPLIT = 8;    // wavefronts per 64 elements of a small layer
 constexpr int MAXN = GSIM_CTRL_MAX_SIGNALS;
 
 struct CtrlArgs {
@@ -46,79 +51,104 @@ struct SC {
     T s, c;
 };
 
+// Threads of a workgroup: one group of 64 elements with WAVES wavefronts, or four groups.
+template <int WAVES>
+constexpr int ctrl_block() {
+    return WAVES == 1 ? 256 : 64 * WAVES;
+}
+
 // (sin, cos) of omega tau for steps tc .. tc + CTRL_CHUNK - 1 of the call.
 template <typename T>
-__device__ void ctrl_table(const CtrlArgs& a, int64_t tc, SC<T>* tab) {
-    for (int t = threadIdx.x; t < CTRL_CHUNK; t += blockDim.x) {
+__device__ __forceinline__ void ctrl_table(const CtrlArgs& a, int64_t tc, SC<T>* tab, int from) {
+    for (int t = (int)threadIdx.x - from; t < CTRL_CHUNK && tc + t < a.n_steps; t += blockDim.x - from) {
+        if (t < 0) continue;
         const double x = a.omega * ((double)(a.t0 + tc + t) * a.dt);
         tab[t].s = (T)sin(x);
         tab[t].c = (T)cos(x);
     }
 }
 
-// Phase table cos / sin(2 pi k / N) (FP64 rounded to T) into LDS, then this
-// thread's A, B from its weights.  Contains a barrier: every thread calls it.
+// The phase table cos / sin(2 pi k / N) (FP64 rounded to T) and the first chunk's step
+// table into LDS, then this thread's A, B from its weights.  Contains a barrier: every
+// thread calls it.
 template <typename T>
-__device__ void ctrl_coeffs(const CtrlArgs& a, const T* __restrict__ W, int64_t e, bool live, T* cp, T* sp, T& A,
-                            T& B) {
+__device__ __forceinline__ void ctrl_coeffs(const CtrlArgs& a, const T* __restrict__ W, int64_t e, bool live,
+                                            SC<T>* tab, T* cp, T* sp, T& A, T& B) {
     const double two_pi = 6.283185307179586476925287;
-    if (threadIdx.x < a.n_signals) {
-        const double p = two_pi * (double)threadIdx.x / (double)a.n_signals;
-        cp[threadIdx.x] = (T)cos(p);
-        sp[threadIdx.x] = (T)sin(p);
+    T w[MAXN];
+#pragma unroll
+    for (int k = 0; k < MAXN; ++k) w[k] = live && k < a.n_signals ? W[(int64_t)k * a.n + e] : T(0);
+    if (threadIdx.x < 64) {
+        if ((int)threadIdx.x < a.n_signals) {
+            const double p = two_pi * (double)threadIdx.x / (double)a.n_signals;
+            cp[threadIdx.x] = (T)cos(p);
+            sp[threadIdx.x] = (T)sin(p);
+        }
+    } else {
+        ctrl_table<T>(a, 0, tab, 64);
     }
     __syncthreads();
     A = T(0);
     B = T(0);
 #pragma unroll
     for (int k = 0; k < MAXN; ++k)
-        if (live && k < a.n_signals) {
-            const T w = W[(int64_t)k * a.n + e];
-            A += w * cp[k];
-            B += w * sp[k];
+        if (k < a.n_signals) {
+            A = fma(w[k], cp[k], A);
+            B = fma(w[k], sp[k], B);
         }
 }
 
+// tanh of the layer at a step's (sin, cos).
 template <typename T>
-__global__ __launch_bounds__(CTRL_BLOCK) void k_ctrl_fwd(CtrlArgs a, const T* __restrict__ W, T* __restrict__ act) {
+__device__ __forceinline__ T ctrl_layer(T A, T B, SC<T> q) {
+    return tanh(fma(A, q.s, B * q.c));
+}
+
+template <typename T, int WAVES>
+__global__ __launch_bounds__(ctrl_block<WAVES>()) void k_ctrl_fwd(CtrlArgs a, const T* __restrict__ W,
+                                                                  T* __restrict__ act) {
     __shared__ SC<T> tab[CTRL_CHUNK];
     __shared__ T cp[MAXN], sp[MAXN];
-    const int64_t e = (int64_t)blockIdx.x * CTRL_BLOCK + threadIdx.x;
+    const int wave = WAVES == 1 ? 0 : (int)threadIdx.x >> 6;
+    const int64_t e = WAVES == 1 ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     const bool live = e < a.n;
     const T scale = (T)a.scale;
     T A, B;
-    ctrl_coeffs<T>(a, W, e, live, cp, sp, A, B);
+    ctrl_coeffs<T>(a, W, e, live, tab, cp, sp, A, B);
     for (int64_t tc = 0; tc < a.n_steps; tc += CTRL_CHUNK) {
-        __syncthreads();  // the previous chunk's table is no longer read
-        ctrl_table<T>(a, tc, tab);
-        __syncthreads();
+        if (tc > 0) {
+            __syncthreads();  // the previous chunk's table is no longer read
+            ctrl_table<T>(a, tc, tab, 0);
+            __syncthreads();
+        }
         const int nt = (int)(a.n_steps - tc < CTRL_CHUNK ? a.n_steps - tc : CTRL_CHUNK);
         if (live)
-            for (int t = 0; t < nt; ++t) {
-                const SC<T> q = tab[t];
-                act[(tc + t) * a.n + e] = scale * tanh(A * q.s + B * q.c);
-            }
+            for (int t = wave; t < nt; t += WAVES) act[(tc + t) * a.n + e] = scale * ctrl_layer(A, B, tab[t]);
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(CTRL_BLOCK) void k_ctrl_bwd(CtrlArgs a, const T* __restrict__ W,
-                                                         const T* __restrict__ g, T* __restrict__ gW) {
+template <typename T, int WAVES>
+__global__ __launch_bounds__(ctrl_block<WAVES>()) void k_ctrl_bwd(CtrlArgs a, const T* __restrict__ W,
+                                                                  const T* __restrict__ g, T* __restrict__ gW) {
     __shared__ SC<T> tab[CTRL_CHUNK];
     __shared__ T cp[MAXN], sp[MAXN];
-    const int64_t e = (int64_t)blockIdx.x * CTRL_BLOCK + threadIdx.x;
+    __shared__ T sum[2][WAVES == 1 ? 1 : 64 * WAVES];
+    const int wave = WAVES == 1 ? 0 : (int)threadIdx.x >> 6;
+    const int64_t e = WAVES == 1 ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     const bool live = e < a.n;
     const T scale = (T)a.scale;
     T A, B;
-    ctrl_coeffs<T>(a, W, e, live, cp, sp, A, B);
+    ctrl_coeffs<T>(a, W, e, live, tab, cp, sp, A, B);
     T gA = T(0), gB = T(0);
     for (int64_t tc = 0; tc < a.n_steps; tc += CTRL_CHUNK) {
-        __syncthreads();
-        ctrl_table<T>(a, tc, tab);
-        __syncthreads();
+        if (tc > 0) {
+            __syncthreads();
+            ctrl_table<T>(a, tc, tab, 0);
+            __syncthreads();
+        }
         const int nt = (int)(a.n_steps - tc < CTRL_CHUNK ? a.n_steps - tc : CTRL_CHUNK);
         if (live)
-            for (int t0 = 0; t0 < nt; t0 += CTRL_BATCH) {
+            for (int t0 = wave * CTRL_BATCH; t0 < nt; t0 += WAVES * CTRL_BATCH) {
                 T gv[CTRL_BATCH];
 #pragma unroll
                 for (int j = 0; j < CTRL_BATCH; ++j)
@@ -127,17 +157,30 @@ __global__ __launch_bounds__(CTRL_BLOCK) void k_ctrl_bwd(CtrlArgs a, const T* __
                 for (int j = 0; j < CTRL_BATCH; ++j)
                     if (t0 + j < nt) {
                         const SC<T> q = tab[t0 + j];
-                        const T y = tanh(A * q.s + B * q.c);
+                        const T y = ctrl_layer(A, B, q);
                         const T dz = gv[j] * scale * (T(1) - y * y);
                         gA += dz * q.s;
                         gB += dz * q.c;
                     }
             }
     }
-    if (live)
+    if constexpr (WAVES > 1) {  // the wavefronts' sums, in order
+        sum[0][threadIdx.x] = gA;
+        sum[1][threadIdx.x] = gB;
+        __syncthreads();
+        const int l = threadIdx.x & 63;
+        gA = sum[0][l];
+        gB = sum[1][l];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            gA += sum[0][64 * w + l];
+            gB += sum[1][64 * w + l];
+        }
+    }
+    if (live)  // the signals are shared over the wavefronts
 #pragma unroll
         for (int k = 0; k < MAXN; ++k)
-            if (k < a.n_signals) gW[(int64_t)k * a.n + e] += gA * cp[k] + gB * sp[k];
+            if (k % WAVES == wave && k < a.n_signals) gW[(int64_t)k * a.n + e] += gA * cp[k] + gB * sp[k];
 }
 
 int check_ctrl(int dtype, const gsim_controller* c, int64_t n, int64_t t0, int64_t n_steps, CtrlArgs& a) {
@@ -158,6 +201,21 @@ int check_ctrl(int dtype, const gsim_controller* c, int64_t n, int64_t t0, int64
     return GSIM_OK;
 }
 
+// Layers of fewer elements than this (256 per compute unit) take CTRL_SPLIT wavefronts per
+// 64 elements.  Measured at 60 steps, 8 signals, float32 (one / eight wavefronts, us):
+// forward at 600 elements 11.4 / 5.3, 32000 13.3 / 7.2, 64000 14.5 / 11.0, 200000 19.4 /
+// 23.3; backward 14.4 / 6.5, 14.2 / 7.9, 15.2 / 13.0, 22.5 / 35.7.
+constexpr int64_t CTRL_SMALL = 65536;
+#define CTRL_LAUNCH(K, T, ...)                                                                                    \
+    do {                                                                                                          \
+        if (n < CTRL_SMALL)                                                                                       \
+            hipLaunchKernelGGL((K<T, CTRL_SPLIT>), dim3((unsigned)((n + 63) / 64)), dim3(64 * CTRL_SPLIT), 0,      \
+                               (hipStream_t)stream, a, __VA_ARGS__);                                              \
+        else                                                                                                      \
+            hipLaunchKernelGGL((K<T, 1>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, a, \
+                               __VA_ARGS__);                                                                      \
+    } while (0)
+
 int launched(const char* what) {
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? GSIM_OK : gsim::hip_fail(e, what);
@@ -174,13 +232,8 @@ int gsim_controller_forward(int dtype, const gsim_controller* ctrl, const void* 
     if (rc) return rc;
     if (n == 0 || n_steps == 0) return GSIM_OK;
     if (!W || !act) return gsim::fail(GSIM_E_INVALID, "NULL W or act");
-    const dim3 grid((unsigned)((n + CTRL_BLOCK - 1) / CTRL_BLOCK));
-    if (dtype == GSIM_F32)
-        hipLaunchKernelGGL(k_ctrl_fwd<float>, grid, dim3(CTRL_BLOCK), 0, (hipStream_t)stream, a, (const float*)W,
-                           (float*)act);
-    else
-        hipLaunchKernelGGL(k_ctrl_fwd<double>, grid, dim3(CTRL_BLOCK), 0, (hipStream_t)stream, a, (const double*)W,
-                           (double*)act);
+    if (dtype == GSIM_F32) CTRL_LAUNCH(k_ctrl_fwd, float, (const float*)W, (float*)act);
+    else CTRL_LAUNCH(k_ctrl_fwd, double, (const double*)W, (double*)act);
     return launched("controller forward launch");
 }
 
@@ -191,13 +244,8 @@ int gsim_controller_backward(int dtype, const gsim_controller* ctrl, const void*
     if (rc) return rc;
     if (n == 0 || n_steps == 0) return GSIM_OK;
     if (!W || !act_grad || !W_grad) return gsim::fail(GSIM_E_INVALID, "NULL W, act_grad or W_grad");
-    const dim3 grid((unsigned)((n + CTRL_BLOCK - 1) / CTRL_BLOCK));
-    if (dtype == GSIM_F32)
-        hipLaunchKernelGGL(k_ctrl_bwd<float>, grid, dim3(CTRL_BLOCK), 0, (hipStream_t)stream, a, (const float*)W,
-                           (const float*)act_grad, (float*)W_grad);
-    else
-        hipLaunchKernelGGL(k_ctrl_bwd<double>, grid, dim3(CTRL_BLOCK), 0, (hipStream_t)stream, a, (const double*)W,
-                           (const double*)act_grad, (double*)W_grad);
+    if (dtype == GSIM_F32) CTRL_LAUNCH(k_ctrl_bwd, float, (const float*)W, (const float*)act_grad, (float*)W_grad);
+    else CTRL_LAUNCH(k_ctrl_bwd, double, (const double*)W, (const double*)act_grad, (double*)W_grad);
     return launched("controller backward launch");
 }
 
