@@ -1566,6 +1566,23 @@ __global__ void __launch_bounds__(256) k_stage_copy(const StageSeg* __restrict__
     for (int64_t i = done + threadIdx.x; i < n; i += blockDim.x) dst[i] = src ? src[i] : (char)0;
 }
 
+// Sum of p[stride r], r = r0 .. r1 - 1, in that order.  A thread's chain of loads would
+// bound it (100 ns a row), so 32 rows are on their way at a time: per-body contact rows of
+// a 200k-tet body (rows of 256 particles) 14.6 -> 5.2 us, its loss rows 11.0 -> 5.5.
+template <typename T>
+__device__ __forceinline__ T ordered_sum(const T* p, int stride, int r0, int r1) {
+    T s = T(0);
+    for (int r = r0; r < r1; r += 32) {
+        T v[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) v[j] = gld(p, (int64_t)stride * min(r + j, r1 - 1));
+#pragma unroll
+        for (int j = 0; j < 32; ++j)
+            if (r + j < r1) s += v[j];
+    }
+    return s;
+}
+
 template <typename T>
 __global__ void k_contact_reduce(const ModelDev<T>* __restrict__ md, const StepDev<T>* __restrict__ sd) {
     const ModelDev<T>& M = md[0];
@@ -1575,9 +1592,7 @@ __global__ void k_contact_reduce(const ModelDev<T>* __restrict__ md, const StepD
     const int b = t >> 2, k = t & 3;
     const BodyDev<T>& B = M.bodies[b];
     if (!B.contact_on) return;
-    T s = T(0);
-    for (int r = B.pt0; r < B.pt1; ++r) s += M.cpart[4 * r + k];
-    S.g_contact[t] += s;
+    S.g_contact[t] += ordered_sum(M.cpart + k, 4, B.pt0, B.pt1);
 }
 
 template <typename T>
@@ -1613,9 +1628,7 @@ __global__ void k_loss_reduce(const ModelDev<T>* __restrict__ md, const StepDev<
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= M.n_bodies) return;
     const BodyDev<T>& B = M.bodies[b];
-    T s = T(0);
-    for (int r = B.pt0; r < B.pt1; ++r) s += M.lpart[r];
-    S.loss[b] = s / T(B.np);
+    S.loss[b] = ordered_sum(M.lpart, 1, B.pt0, B.pt1) / T(B.np);
 }
 
 template <typename T>
