@@ -10,15 +10,8 @@ from paper_2104_02646_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def run(gs, bodies, tile, exec_mode, lanes, T=6, K=3):
-    stream = torch.cuda.Stream()
+def run(gs, m, bodies, stream, T=6):
     with torch.cuda.stream(stream):
-        m = gs.Model(bodies, torch.float32, max_steps=T, ckpt_every=K, tile_elems=tile)
-        m.set_exec(exec_mode)
-        assert m.get_lanes() == 2
-        if lanes:
-            m.set_lanes(lanes)
-            assert m.get_lanes() == lanes
         p = m.params_from_bodies()
         x0, v0 = (gs.soa(np.concatenate([getattr(b, k) for b in bodies]), dtype=torch.float32) for k in ("x0", "v0"))
         tg = gs.soa(np.concatenate([W.synthetic_target(b, 7 + i) for i, b in enumerate(bodies)]), dtype=torch.float32)
@@ -44,9 +37,14 @@ def test_default_lanes_bitwise(case, tile):
     tiles = sum(-(-b.ne // 64) for b in bodies)
     if tile:  # between the thresholds of gradients and of rollouts, and above both
         assert (1024 < tiles < 1700) if case == "forward" else tiles > 1792
-    for exec_mode in (gs.EXEC_PLAIN, gs.EXEC_GRAPH):
-        ref = run(gs, bodies, tile, exec_mode, 0)
-        for lanes in (1, 2):
-            got = run(gs, bodies, tile, exec_mode, lanes)
-            for k in ref:
-                assert np.array_equal(ref[k], got[k]), (k, lanes, exec_mode)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        m = gs.Model(bodies, torch.float32, max_steps=6, ckpt_every=3, tile_elems=tile)
+    assert m.get_lanes() == 2
+    ref = run(gs, m, bodies, stream)
+    for lanes in (1, 2):
+        m.set_lanes(lanes)
+        assert m.get_lanes() == lanes
+        got = run(gs, m, bodies, stream)
+        for k in ref:
+            assert np.array_equal(ref[k], got[k]), (k, lanes)
