@@ -181,7 +181,7 @@ void colour_elements(gsim_plan* P) {
 // Element tiles of the two-pass path.  Per body and element kind, consecutive
 // elements are cut into tiles of at most tile_elems elements, a tile ending early when
 // its adjoint LDS (8 words per tile particle, 4 per corner) would exceed
-// ETILE_WORDS.  Per tile: its particles in increasing index order (the tile
+// ETILE_WORDS, or what a corner code can hold (CODE_PARTICLES, CODE_CORNERS).  Per tile: its particles in increasing index order (the tile
 // particles); its corners ordered by (tile particle, element, corner), so each
 // tile particle's corners form one contiguous run; corner code = tile-local
 // particle | position in that order << 16.  The kernels sum each run into one
@@ -190,16 +190,20 @@ void colour_elements(gsim_plan* P) {
 // holds width_g = max partials per particle of its particles, and the k-th tile
 // (plan order) touching the particle at lane j writes slot gbase[g] + 64 k + j.
 // Everything here depends only on the body itself, never on the rest of a batch.
-int build_tiles(gsim_plan* P) {
+// wide: also the corner codes of gsim_plan_codes (the serving engine's plans need none).
+int build_tiles(gsim_plan* P, bool wide) {
     const int nb = P->nb;
     P->etiles.clear();
     P->tp_id.clear();
     P->tp_run.clear();
-    P->tet_code.assign(4 * P->ne, 0);
-    P->tri_code.assign(3 * P->nt, 0);
-    P->hin_code.assign(4 * P->nh, 0);
+    P->tet_code.resize(wide ? 4 * P->ne : 0);
+    P->tri_code.resize(wide ? 3 * P->nt : 0);
+    P->hin_code.resize(wide ? 4 * P->nh : 0);
+    P->corner[0].resize(P->ne);
+    P->corner[1].resize(P->nt);
+    P->corner[2].resize(P->nh);
     P->etile_words[0] = P->etile_words[1] = 0;
-    std::vector<int32_t> mark(P->np, -1), loc(P->np, 0), parts, cnt, fill;
+    std::vector<int32_t> mark(P->np, -1), loc(P->np, 0), cnt(P->np, 0), parts, fill;  // cnt: corners in the tile
     for (int b = 0; b < nb; ++b)
         for (int kind = 0; kind < 3; ++kind) {
             const std::vector<int64_t>& off = kind == 0 ? P->eoff : kind == 1 ? P->toff : P->hoff;
@@ -218,15 +222,23 @@ int build_tiles(gsim_plan* P) {
                 parts.clear();
                 while (e < off[b + 1] && e - s < P->tile_elems) {
                     int add = 0;
-                    for (int c = 0; c < nc; ++c) add += mark[idx[c * n + e]] != tile;
+                    bool full = false;  // a corner code could not hold the particle's next corner
+                    for (int c = 0; c < nc; ++c) {
+                        const int32_t p = idx[c * n + e];
+                        if (mark[p] != tile) ++add;
+                        else full |= cnt[p] >= CODE_CORNERS;
+                    }
                     const int64_t words = wp * (int64_t)(parts.size() + add) + wc * (int64_t)nc * (e - s + 1);
-                    if (e > s && words > ETILE_WORDS) break;
+                    full |= words > ETILE_WORDS || parts.size() + add > (size_t)CODE_PARTICLES;
+                    if (e > s && full) break;
                     for (int c = 0; c < nc; ++c) {
                         const int32_t p = idx[c * n + e];
                         if (mark[p] != tile) {
                             mark[p] = tile;
+                            cnt[p] = 0;
                             parts.push_back(p);
                         }
+                        cnt[p]++;
                     }
                     ++e;
                 }
@@ -247,18 +259,24 @@ int build_tiles(gsim_plan* P) {
                     }
                 }
                 const int m = (int)parts.size();
-                for (int j = 0; j < m; ++j) loc[parts[j]] = j;
-                cnt.assign(m, 0);
-                for (int64_t l = s; l < e; ++l)
-                    for (int c = 0; c < nc; ++c) cnt[loc[idx[c * n + l]]]++;
-                fill.assign(m, 0);
-                for (int j = 1; j < m; ++j) fill[j] = fill[j - 1] + cnt[j - 1];
-                for (int j = 0; j < m; ++j) P->tp_run.push_back(fill[j] | (cnt[j] << 16));
-                for (int64_t l = s; l < e; ++l)
+                fill.resize(m);
+                for (int j = 0, at = 0; j < m; ++j) {
+                    const int32_t k = cnt[parts[j]];
+                    loc[parts[j]] = j;
+                    fill[j] = at;
+                    P->tp_run.push_back(at | (k << 16));
+                    at += k;
+                }
+                const int32_t* runs = P->tp_run.data() + P->tp_id.size();
+                for (int64_t l = s; l < e; ++l) {
+                    uint64_t packed = 0;
                     for (int c = 0; c < nc; ++c) {
-                        const int j = loc[idx[c * n + l]];
-                        code[c * n + l] = (uint32_t)j | ((uint32_t)fill[j]++ << 16);
+                        const int j = loc[idx[c * n + l]], at = fill[j]++;
+                        if (wide) code[c * n + l] = (uint32_t)j | ((uint32_t)at << 16);
+                        packed |= (uint64_t)(j | (at - (runs[j] & 0xffff)) << CODE_BITS) << 16 * c;
                     }
+                    P->corner[kind][l] = packed;
+                }
                 Tile t{};
                 t.model = 0;
                 t.body = b;
@@ -519,7 +537,7 @@ int build_plan(const gsim_model_desc* d, gsim_plan* P, bool fused) {
             for (int c = 0; c < 4; ++c) P->hin_idx[c * nh + h] = id[c];
         }
 
-    if (int rc = build_tiles(P)) return rc;
+    if (int rc = build_tiles(P, fused)) return rc;
     if (fused) {
         colour_elements(P);
         build_resident(P);
@@ -559,14 +577,9 @@ Layout make_layout(const gsim_plan* P, int max_steps) {
     L.bodies = take(sizeof(BodyDev<T>) * P->nb);
     L.etiles = take(sizeof(Tile) * cap_e);
     L.ptiles = take(sizeof(Tile) * cap_p);
-    L.tet_code = take(4 * ne * 4);
-    L.tet_dinv = take(9 * ne * sizeof(T));
-    L.tet_vol = take(ne * sizeof(T));
-    L.tri_code = take(3 * nt * 4);
-    L.tri_dinv = take(4 * nt * sizeof(T));
-    L.tri_area = take(nt * sizeof(T));
-    L.hin_code = take(4 * nh * 4);
-    L.hin_phi0 = take(nh * sizeof(T));
+    L.tet_rec = take(12 * ne * sizeof(T));
+    L.tri_rec = take(8 * nt * sizeof(T));
+    L.hin_rec = take(4 * nh * sizeof(T));
     L.tp = take(P->tp_id.size() * 12 + 16);
     L.gbase = take(P->gbase.size() * 4 + 4);
     L.pdeg = take(np * 4);
@@ -605,6 +618,7 @@ Layout make_layout(const gsim_plan* P, int max_steps) {
     L.toff = take(2 * (P->nb + 1) * 4);
     L.r_code = take(P->r_code.size() * 4 + 4);
     L.r_run = take(P->r_run.size() * 4 + 4);
+    L.r_dinv = take(P->res_ept ? 10 * ne * sizeof(T) : 4);
     L.table_cap = 4 * (int64_t)max_steps + 8;
     L.table = take(sizeof(StepDev<T>) * L.table_cap);
     L.total = align_up(o, 256);
@@ -1581,18 +1595,55 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
         return sink ? sink->copy(ws + off, src, n) : hipMemcpyAsync(ws + off, src, n, hipMemcpyHostToDevice, s);
     };
     auto cvt = [](const std::vector<double>& v) { return std::vector<T>(v.begin(), v.end()); };
-    std::vector<T> tet_dinv = cvt(P->tet_dinv), tet_vol = cvt(P->tet_vol), tri_dinv = cvt(P->tri_dinv),
-                   tri_area = cvt(P->tri_area), hin_phi0 = cvt(P->hin_phi0);
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-    chk(up(L.tet_code, P->tet_code.data(), P->tet_code.size() * 4));
-    chk(up(L.tet_dinv, tet_dinv.data(), tet_dinv.size() * sizeof(T)));
-    chk(up(L.tet_vol, tet_vol.data(), tet_vol.size() * sizeof(T)));
-    chk(up(L.tri_code, P->tri_code.data(), P->tri_code.size() * 4));
-    chk(up(L.tri_dinv, tri_dinv.data(), tri_dinv.size() * sizeof(T)));
-    chk(up(L.tri_area, tri_area.data(), tri_area.size() * sizeof(T)));
-    chk(up(L.hin_code, P->hin_code.data(), P->hin_code.size() * 4));
-    chk(up(L.hin_phi0, hin_phi0.data(), hin_phi0.size() * sizeof(T)));
+    {  // element records (see ModelDev)
+        const int64_t ne = P->ne, nt = P->nt, nh = P->nh;
+        // written where the set-up copy reads them, or into a vector and copied
+        auto fill = [&](size_t off, size_t n, auto write) {
+            if (!n) return;
+            void* at = nullptr;
+            if (sink) chk(sink->place(ws + off, n * sizeof(T), &at));
+            if (e != hipSuccess) return;
+            if (at) return write(static_cast<T*>(at));
+            std::vector<T> rec(n);
+            write(rec.data());
+            chk(up(off, rec.data(), n * sizeof(T)));
+            if (!sink && e == hipSuccess) e = hipStreamSynchronize(s);  // (the vector ends here)
+        };
+        fill(L.tet_rec, 12 * (size_t)ne, [&](T* rec) {
+            const double* d = P->tet_dinv.data();
+            for (int64_t i = 0; i < ne; ++i) {
+                T *q0 = rec + 4 * i, *q1 = rec + 4 * (ne + i), *q2 = rec + 4 * (2 * ne + i);
+                for (int q = 0; q < 4; ++q) {
+                    q0[q] = (T)d[q * ne + i];
+                    q1[q] = (T)d[(4 + q) * ne + i];
+                }
+                q2[0] = (T)d[8 * ne + i];
+                q2[1] = (T)P->tet_vol[i];
+                q2[3] = T(0);
+                std::memcpy(q2 + 2, &P->corner[0][i], 8);
+            }
+        });
+        fill(L.tri_rec, 8 * (size_t)nt, [&](T* rec) {
+            const double* d = P->tri_dinv.data();
+            for (int64_t i = 0; i < nt; ++i) {
+                T *q0 = rec + 4 * i, *q1 = rec + 4 * (nt + i);
+                for (int q = 0; q < 4; ++q) q0[q] = (T)d[q * nt + i];
+                q1[0] = (T)P->tri_area[i];
+                q1[2] = q1[3] = T(0);
+                std::memcpy(q1 + 1, &P->corner[1][i], 8);
+            }
+        });
+        fill(L.hin_rec, 4 * (size_t)nh, [&](T* rec) {
+            for (int64_t i = 0; i < nh; ++i) {
+                T* q = rec + 4 * i;
+                q[0] = (T)P->hin_phi0[i];
+                q[2] = q[3] = T(0);
+                std::memcpy(q + 1, &P->corner[2][i], 8);
+            }
+        });
+    }
     std::vector<int32_t> tp3(3 * P->tp_id.size(), 0);
     for (size_t i = 0; i < P->tp_id.size(); ++i) {
         tp3[3 * i] = P->tp_id[i];
@@ -1602,6 +1653,12 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     chk(up(L.tp, tp3.data(), tp3.size() * 4));
     chk(up(L.r_code, P->r_code.data(), P->r_code.size() * 4));
     chk(up(L.r_run, P->r_run.data(), P->r_run.size() * 4));
+    std::vector<T> r_dinv;
+    if (P->res_ept) {
+        r_dinv = cvt(P->tet_dinv);
+        r_dinv.insert(r_dinv.end(), P->tet_vol.begin(), P->tet_vol.end());
+    }
+    chk(up(L.r_dinv, r_dinv.data(), r_dinv.size() * sizeof(T)));
     chk(up(L.gbase, P->gbase.data(), P->gbase.size() * 4));
     chk(up(L.pdeg, P->pdeg.data(), P->pdeg.size() * 4));
     chk(up(L.pinned, P->pinned.data(), P->pinned.size()));
@@ -1620,6 +1677,8 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     // (set-up, never inside a captured sequence)
     chk(sink ? sink->zero(ws + L.bflag, 2 * (size_t)P->nb * 4) : hipMemsetAsync(ws + L.bflag, 0, 2 * (size_t)P->nb * 4, s));
     if (P->coloured) {  // colour-ordered copies of the element records (fused path)
+        std::vector<T> tet_dinv = cvt(P->tet_dinv), tet_vol = cvt(P->tet_vol), tri_dinv = cvt(P->tri_dinv),
+                       tri_area = cvt(P->tri_area), hin_phi0 = cvt(P->hin_phi0);
         // corner indices become body-local (the fused kernels address the body's particles in LDS)
         auto perm_i = [P](const std::vector<int32_t>& a, const std::vector<int32_t>& ord, int rows, int64_t n,
                           const std::vector<int64_t>& off) {
@@ -1714,14 +1773,9 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     M.nh = P->nh;
     M.nslot = P->nslot;
     M.n_bodies = P->nb;
-    M.tet_code = (const uint32_t*)(ws + L.tet_code);
-    M.tet_dinv = (const T*)(ws + L.tet_dinv);
-    M.tet_vol = (const T*)(ws + L.tet_vol);
-    M.tri_code = (const uint32_t*)(ws + L.tri_code);
-    M.tri_dinv = (const T*)(ws + L.tri_dinv);
-    M.tri_area = (const T*)(ws + L.tri_area);
-    M.hin_code = (const uint32_t*)(ws + L.hin_code);
-    M.hin_phi0 = (const T*)(ws + L.hin_phi0);
+    M.tet_rec = (const T*)(ws + L.tet_rec);
+    M.tri_rec = (const T*)(ws + L.tri_rec);
+    M.hin_rec = (const T*)(ws + L.hin_rec);
     M.tp = (const int32_t*)(ws + L.tp);
     M.gbase = (const int32_t*)(ws + L.gbase);
     M.pdeg = (const int32_t*)(ws + L.pdeg);
@@ -1737,6 +1791,7 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     M.lpart = (T*)(ws + L.lpart);
     M.r_code = P->res_ept ? (const uint32_t*)(ws + L.r_code) : nullptr;
     M.r_run = P->res_ept ? (const uint32_t*)(ws + L.r_run) : nullptr;
+    M.r_dinv = P->res_ept ? (const T*)(ws + L.r_dinv) : nullptr;
     M.f_tet_idx = (const int32_t*)(ws + L.f_tet_idx);
     M.f_tet_dinv = (const T*)(ws + L.f_tet_dinv);
     M.f_tet_vol = (const T*)(ws + L.f_tet_vol);

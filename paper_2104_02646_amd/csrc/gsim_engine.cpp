@@ -218,19 +218,27 @@ struct Stager final : UploadSink {
         for (size_t o = 0; o < n; o += (size_t)STAGE_PIECE)
             segs.push_back({src ? src + o : nullptr, dst + o, (int64_t)std::min((size_t)STAGE_PIECE, n - o)});
     }
+    hipError_t place(void* dst, size_t n, void** bytes) override {
+        *bytes = nullptr;
+        const size_t need = (n + 15) / 16 * 16;
+        if (need + (pieces(n) + 1) * sizeof(StageSeg) > cap) return hipSuccess;
+        if (table_end(fill + need, pieces(n)) > cap)
+            if (hipError_t e = flush()) return e;
+        *bytes = host[cur] + fill;
+        add(dev[cur] + fill, (char*)dst, n);
+        fill += need;
+        return hipSuccess;
+    }
     hipError_t copy(void* dst, const void* src, size_t n) override {
         if (n == 0) return hipSuccess;
-        const size_t need = (n + 15) / 16 * 16;
-        if (need + (pieces(n) + 1) * sizeof(StageSeg) > cap) {
+        void* at = nullptr;
+        if (hipError_t e = place(dst, n, &at)) return e;
+        if (!at) {
             ++direct;
             hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, stream);
             return e == hipSuccess ? hipStreamSynchronize(stream) : e;
         }
-        if (table_end(fill + need, pieces(n)) > cap)
-            if (hipError_t e = flush()) return e;
-        std::memcpy(host[cur] + fill, src, n);
-        add(dev[cur] + fill, (char*)dst, n);
-        fill += need;
+        std::memcpy(at, src, n);
         return hipSuccess;
     }
     hipError_t zero(void* dst, size_t n) override {

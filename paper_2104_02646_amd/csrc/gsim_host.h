@@ -26,6 +26,7 @@ struct gsim_plan {
     // per kind, per-tile-particle index / corner run / partial slot
     std::vector<gsim::Tile> etiles;
     std::vector<uint32_t> tet_code, tri_code, hin_code;  // SoA [corners][n]
+    std::vector<uint64_t> corner[3];  // per kind [n]: the corner codes of the element records
     std::vector<int32_t> tp_id, tp_run, tp_slot;
     int tile_elems = gsim::ETILE;                  // elements per two-pass element tile
     int64_t etile_words[2] = {0, 0};               // largest tile's LDS words, forward / adjoint
@@ -61,9 +62,7 @@ const int DEFAULT_LANES = 2;  // lanes of a new model with that many bodies or m
 
 struct Layout {
     size_t model, bodies, etiles, ptiles;
-    size_t tet_code, tet_dinv, tet_vol;
-    size_t tri_code, tri_dinv, tri_area;
-    size_t hin_code, hin_phi0;
+    size_t tet_rec, tri_rec, hin_rec;
     size_t tp;
     size_t gbase, pdeg, pinned, slots, fslots, vslots, cpart, lpart;  // vslots: only when a body has air
     size_t rest, rgap;  // rest positions [3][np], rest ground gaps [np]
@@ -74,7 +73,7 @@ struct Layout {
     size_t f_tet_idx, f_tet_dinv, f_tet_vol, f_tet_orig, f_tri_idx, f_tri_dinv, f_tri_area, f_tri_orig;
     size_t f_hin_idx, f_hin_phi0, f_hin_orig, coff, border, f_par, f_ktri, f_g, f_gk, f_hpar, f_gh;
     size_t ntiles, toff;  // persistent execution: natural-order tiles, per-body ranges [2][nb + 1]
-    size_t r_code, r_run;  // resident execution
+    size_t r_code, r_run, r_dinv;  // resident execution
     size_t table;
     int64_t table_cap;
     size_t total;
@@ -97,11 +96,13 @@ void xcd_order(const std::vector<Tile>& nat, int empty_kind, int dummy_id, std::
 // hipMemcpyAsync on the set-up stream and the set-up ends with a synchronisation of
 // that stream (the host arrays are temporaries).  The serving engine passes its
 // staging area instead: copy() takes the bytes at once (the source may be freed on
-// return) and zero() records a zero fill; both land on the device, in stream order,
-// before any later launch on that stream reads them.
+// return), place() gives the caller room for the bytes instead (to be filled before the
+// next call; null: none that large) and zero() records a zero fill; all land on the device,
+// in stream order, before any later launch on that stream reads them.
 struct UploadSink {
     virtual ~UploadSink() = default;
     virtual hipError_t copy(void* dst, const void* src, size_t n) = 0;
+    virtual hipError_t place(void* dst, size_t n, void** bytes) = 0;
     virtual hipError_t zero(void* dst, size_t n) = 0;
 };
 

@@ -83,16 +83,13 @@ template <typename T>
 struct ModelDev {
     int64_t np, ne, nt, nh, nslot;
     int32_t n_bodies, n_ptiles;
-    // element records (SoA over elements); corner codes: tile-local particle |
-    // position in the tile's particle-sorted corner order << 16
-    const uint32_t* tet_code;
-    const T* tet_dinv;
-    const T* tet_vol;
-    const uint32_t* tri_code;
-    const T* tri_dinv;
-    const T* tri_area;
-    const uint32_t* hin_code;
-    const T* hin_phi0;
+    // element records, 4-vectors SoA over elements: tets {Dm^-1 0..3} {Dm^-1 4..7}
+    // {Dm^-1 8, volume, codes}; triangles {Dm^-1 0..3} {area, codes}; hinges {rest angle,
+    // codes}.  The codes are 16 bits per corner, 8 bytes in the vector's next element(s):
+    // tile-local particle | rank among the particle's corners in the tile << CODE_BITS
+    const T* tet_rec;  // [3][ne][4]
+    const T* tri_rec;  // [2][nt][4]
+    const T* hin_rec;  // [nh][4]
     // tile particles (Tile.id = first, Tile.pad = count), one 16-byte record each:
     // particle index, corner run (first sorted corner | count << 16), partial slot, 0
     const int32_t* tp;
@@ -114,6 +111,7 @@ struct ModelDev {
     // particle's partial slot the corner run behind it (first position | count << 16)
     const uint32_t* r_code;
     const uint32_t* r_run;
+    const T* r_dinv;  // [10][ne] Dm^-1 and volume, values apart (loaded once into registers)
     // fused path: element records in colour order (same SoA layouts, corner indices
     // local to the element's body), the original element index of each position
     // (for parameters and gradients), colour bounds
@@ -282,6 +280,8 @@ int launch_fused_adj(const ModelDev<T>* md, const StepDev<T>* sd, const int32_t*
 // body, and at most ETILE_WORDS words of adjoint LDS (8 per tile particle, 4 per
 // corner; triangle tiles of bodies with air: 12 and 8)
 const int ETILE = 256, ETILE_WORDS = 16384;
+// and what a corner code holds: particles of a tile, corners of a particle in a tile
+const int CODE_BITS = 10, CODE_PARTICLES = 1 << CODE_BITS, CODE_CORNERS = 1 << (16 - CODE_BITS);
 
 const int FUSED_FWD_BLOCK = 1024, FUSED_ADJ_BLOCK = 512;
 // dynamic LDS per particle of the largest body: x, v, f (forward); fbar, xbar-acc, f.fbar (adjoint)

@@ -611,12 +611,35 @@ __device__ __forceinline__ gi4 ld_tp(const int32_t* tp, uint32_t j) {
     return gi4{gldo(tp, 12 * j), gldo(tp + 1, 12 * j), gldo(tp + 2, 12 * j), 0};
 }
 
+// The 4-vectors of the element records (one 16-byte load in FP32), and a particle's
+// first corner slot in the w of its staged position.
+template <typename T> struct Vec4;
+template <> struct Vec4<float> { typedef float t __attribute__((ext_vector_type(4))); };
+template <> struct Vec4<double> { typedef double t __attribute__((ext_vector_type(4))); };
+template <typename T>
+__device__ __forceinline__ typename Vec4<T>::t ld_rec(const T* rec, uint32_t l) {
+    return gldo(reinterpret_cast<const typename Vec4<T>::t*>(rec), (uint32_t)(4 * sizeof(T)) * l);
+}
+__device__ __forceinline__ void codes_of(float a, float b, uint32_t& c0, uint32_t& c1) {
+    c0 = __builtin_bit_cast(uint32_t, a);
+    c1 = __builtin_bit_cast(uint32_t, b);
+}
+__device__ __forceinline__ void codes_of(double a, double, uint32_t& c0, uint32_t& c1) {
+    const uint64_t q = __builtin_bit_cast(uint64_t, a);
+    c0 = (uint32_t)q;
+    c1 = (uint32_t)(q >> 32);
+}
+__device__ __forceinline__ float slot_value(int s, float) { return __builtin_bit_cast(float, s); }
+__device__ __forceinline__ double slot_value(int s, double) { return __builtin_bit_cast(double, (int64_t)s); }
+__device__ __forceinline__ int slot_index(float w) { return __builtin_bit_cast(int, w); }
+__device__ __forceinline__ int slot_index(double w) { return (int)__builtin_bit_cast(int64_t, w); }
+
 // An element's record and parameters, held in registers between the loads and the
-// force: corner codes, Dm^-1 (tets 9 values, triangles 4), volume / area / rest angle,
-// (mu, lambda, actuation) / (k) / (hinge actuation).
+// force: corner codes (16 bits each), Dm^-1 (tets 9 values, triangles 4), volume / area /
+// rest angle, (mu, lambda, actuation) / (k) / (hinge actuation).
 template <typename T>
 struct ElemRec {
-    uint32_t c0, c1, c2, c3;
+    uint32_t c0, c1;
     T d0, d1, d2, d3, d4, d5, d6, d7, d8;
     T V, p0, p1, act;
 };
@@ -626,38 +649,43 @@ struct ElemRec {
 template <typename T>
 __device__ __forceinline__ ElemRec<T> load_elem(const ModelDev<T>& M, const StepDev<T>& S, int kind, int64_t begin,
                                                 uint32_t l) {
-    const uint32_t oc = 4 * l, o = (uint32_t)sizeof(T) * l;
-    uint32_t c[4] = {0, 0, 0, 0};
+    const uint32_t o = (uint32_t)sizeof(T) * l;
+    uint32_t c[2] = {0, 0};
     T d[9] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
     T V, p0 = T(0), p1 = T(0), act = T(0);
     if (kind == TILE_TET) {
-        const uint32_t* code = M.tet_code + begin;
-        const T* dinv = M.tet_dinv + begin;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c[k] = gldo(code + k * M.ne, oc);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) d[k] = gldo(dinv + k * M.ne, o);
-        V = gldo(M.tet_vol + begin, o);
+        const T* rec = M.tet_rec + 4 * begin;
+        const auto a = ld_rec(rec, l), b = ld_rec(rec + 4 * M.ne, l), q = ld_rec(rec + 8 * M.ne, l);
+        d[0] = a.x, d[1] = a.y, d[2] = a.z, d[3] = a.w;
+        d[4] = b.x, d[5] = b.y, d[6] = b.z, d[7] = b.w;
+        d[8] = q.x;
+        V = q.y;
+        codes_of(q.z, q.w, c[0], c[1]);
         p0 = gldo(S.mu + begin, o);
         p1 = gldo(S.lam + begin, o);
         if (S.act) act = gldo(S.act + begin, o);
     } else if (kind == TILE_TRI) {
-        const uint32_t* code = M.tri_code + begin;
-        const T* dinv = M.tri_dinv + begin;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) c[k] = gldo(code + k * M.nt, oc);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) d[k] = gldo(dinv + k * M.nt, o);
-        V = gldo(M.tri_area + begin, o);
+        const T* rec = M.tri_rec + 4 * begin;
+        const auto a = ld_rec(rec, l), q = ld_rec(rec + 4 * M.nt, l);
+        d[0] = a.x, d[1] = a.y, d[2] = a.z, d[3] = a.w;
+        V = q.x;
+        codes_of(q.y, q.z, c[0], c[1]);
         p0 = gldo(S.ktri + begin, o);
     } else {
-        const uint32_t* code = M.hin_code + begin;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c[k] = gldo(code + k * M.nh, oc);
-        V = gldo(M.hin_phi0 + begin, o);
+        const auto q = ld_rec(M.hin_rec + 4 * begin, l);
+        V = q.x;
+        codes_of(q.y, q.z, c[0], c[1]);
         if (S.hact) act = gldo(S.hact + begin, o);
     }
-    return ElemRec<T>{c[0], c[1], c[2], c[3], d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8], V, p0, p1, act};
+    return ElemRec<T>{c[0], c[1], d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8], V, p0, p1, act};
+}
+
+// A corner's staged position and its slot in the tile's particle-sorted corner order.
+template <typename T>
+__device__ __forceinline__ V3<T> staged(const L4<T>* xs, uint32_t code, int& at) {
+    const L4<T> q = xs[code & (CODE_PARTICLES - 1)];
+    at = slot_index(q.w) + (int)(code >> CODE_BITS);
+    return v3(q);
 }
 
 // Element pass: one workgroup per planned element tile.  The positions of the
@@ -677,6 +705,10 @@ __device__ __forceinline__ ElemRec<T> load_elem(const ModelDev<T>& M, const Step
 // scalar bases with one 32-bit offset per lane (64-bit lane addresses took 63 vector
 // instructions a tile in the forward pass, now 19); the models' own launches take their
 // model and step records at a fixed address, not through the tile's model index.
+// A batch also moves its element records twice a step, so a tet's is 48 bytes in three
+// 16-byte loads: corner codes of 16 bits, the particle's first slot riding in the w of its
+// staged position (with 32-bit codes and one array per value, 56 bytes in 14 loads: 256-body
+// batch gradient 7230 -> 6890 us, 64-body rollout 1274 -> 1219 us).
 // Measured together, before and after: one-cube gradient of 100 steps 1689 -> 1611 us,
 // 200k-tet blob 2570 -> 2466 us, 256-body batch 7388 -> 7274 us.
 // AIR: the variant launched for models with a lift/drag body (the other compiles
@@ -700,7 +732,7 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDe
     for (int j = tid; j < m; j += nth) {
         const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         xs[j] = l4(tl.kind == TILE_TET ? load_disp(M, S.x, S.x_abs, (int64_t)r.x) : load_pos(M, S.x, S.x_abs, (int64_t)r.x),
-                   T(0));
+                   slot_value(r.y & 0xffff, T(0)));
         if (air) vs[j] = l4(ld3(S.v, np, (int64_t)r.x), T(0));
     }
     __syncthreads();
@@ -708,40 +740,43 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDe
         V3<T> x[4], f[4];
         if (tl.kind == TILE_TET) {
             if constexpr (!ONE) rec = load_elem(M, S, TILE_TET, tl.begin, (uint32_t)l);
-            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const uint32_t cd[4] = {rec.c0 & 0xffffu, rec.c0 >> 16, rec.c1 & 0xffffu, rec.c1 >> 16};
+            int at[4];  // corner slots
             const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) x[c] = v3(xs[cd[c] & 0xffffu]);
+            for (int c = 0; c < 4; ++c) x[c] = staged(xs, cd[c], at[c]);
             T J1;
             tet_force(x, D, rec.V, rec.p0, rec.p1, rec.act, f, J1);
             if (J1 <= T(-1)) raise_flag(M, tl.body, 1);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) cs[cd[c] >> 16] = l4(f[c], T(0));
+            for (int c = 0; c < 4; ++c) cs[at[c]] = l4(f[c], T(0));
         } else if (tl.kind == TILE_TRI) {
             if constexpr (!ONE) rec = load_elem(M, S, TILE_TRI, tl.begin, (uint32_t)l);
-            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const uint32_t cd[4] = {rec.c0 & 0xffffu, rec.c0 >> 16, rec.c1 & 0xffffu, rec.c1 >> 16};
+            int at[4];  // corner slots
             const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
-            for (int c = 0; c < 3; ++c) x[c] = v3(xs[cd[c] & 0xffffu]);
+            for (int c = 0; c < 3; ++c) x[c] = staged(xs, cd[c], at[c]);
             tri_force(x, D, rec.V, rec.p0, f);
             if (air) {
                 V3<T> v[3];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) v[c] = v3(vs[cd[c] & 0xffffu]);
+                for (int c = 0; c < 3; ++c) v[c] = v3(vs[cd[c] & (CODE_PARTICLES - 1)]);
                 const V3<T> F = air_total(x, v, S.air[2 * tl.body], S.air[2 * tl.body + 1]) * (T(1) / T(3));
 #pragma unroll
                 for (int c = 0; c < 3; ++c) f[c] += F;
             }
 #pragma unroll
-            for (int c = 0; c < 3; ++c) cs[cd[c] >> 16] = l4(f[c], T(0));
+            for (int c = 0; c < 3; ++c) cs[at[c]] = l4(f[c], T(0));
         } else {
             if constexpr (!ONE) rec = load_elem(M, S, TILE_HINGE, tl.begin, (uint32_t)l);
-            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const uint32_t cd[4] = {rec.c0 & 0xffffu, rec.c0 >> 16, rec.c1 & 0xffffu, rec.c1 >> 16};
+            int at[4];  // corner slots
 #pragma unroll
-            for (int c = 0; c < 4; ++c) x[c] = v3(xs[cd[c] & 0xffffu]);
+            for (int c = 0; c < 4; ++c) x[c] = staged(xs, cd[c], at[c]);
             hinge_force(x, rec.V, M.bodies[tl.body].kb, rec.act, f);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) cs[cd[c] >> 16] = l4(f[c], T(0));
+            for (int c = 0; c < 4; ++c) cs[at[c]] = l4(f[c], T(0));
         }
         if constexpr (ONE) break;
     }
@@ -879,7 +914,8 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
     for (int j = tid; j < m; j += nth) {
         const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int64_t p = r.x;
-        xs[j] = l4(tl.kind == TILE_TET ? load_disp(M, S.x, S.x_abs, p) : load_pos(M, S.x, S.x_abs, p), T(0));
+        xs[j] = l4(tl.kind == TILE_TET ? load_disp(M, S.x, S.x_abs, p) : load_pos(M, S.x, S.x_abs, p),
+                   slot_value(r.y & 0xffff, T(0)));
         fbs[j] = l4(corner_fbar(M, S, p, dt), T(0));
         if (air) vs[j] = l4(ld3(S.v, np, p), T(0));
     }
@@ -894,63 +930,66 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
         V3<T> x[4], f[4], fb[4], xb[4];
         if (tl.kind == TILE_TET) {
             if constexpr (!ONE) rec = load_elem(M, S, TILE_TET, tl.begin, (uint32_t)l);
-            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const uint32_t cd[4] = {rec.c0 & 0xffffu, rec.c0 >> 16, rec.c1 & 0xffffu, rec.c1 >> 16};
+            int at[4];  // corner slots
             const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                x[c] = v3(xs[cd[c] & 0xffffu]);
-                fb[c] = v3(fbs[cd[c] & 0xffffu]);
+                x[c] = staged(xs, cd[c], at[c]);
+                fb[c] = v3(fbs[cd[c] & (CODE_PARTICLES - 1)]);
             }
             tet_adjoint(x, D, rec.V, rec.p0, rec.p1, rec.act, fb, f, xb, g0, g1, g2);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cs[cd[c] >> 16] = l4(xb[c], fdot(f[c], fb[c]));
+                cs[at[c]] = l4(xb[c], fdot(f[c], fb[c]));
             }
             if (w0) gsto(G0, o, g0);
             if (w1) gsto(G1, o, g1);
             if (w2) gsto(G2, o, g2);
         } else if (tl.kind == TILE_TRI) {
             if constexpr (!ONE) rec = load_elem(M, S, TILE_TRI, tl.begin, (uint32_t)l);
-            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const uint32_t cd[4] = {rec.c0 & 0xffffu, rec.c0 >> 16, rec.c1 & 0xffffu, rec.c1 >> 16};
+            int at[4];  // corner slots
             const T D[9] = {rec.d0, rec.d1, rec.d2, rec.d3, rec.d4, rec.d5, rec.d6, rec.d7, rec.d8};
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                x[c] = v3(xs[cd[c] & 0xffffu]);
-                fb[c] = v3(fbs[cd[c] & 0xffffu]);
+                x[c] = staged(xs, cd[c], at[c]);
+                fb[c] = v3(fbs[cd[c] & (CODE_PARTICLES - 1)]);
             }
             T gk;
             tri_adjoint(x, D, rec.V, rec.p0, fb, f, xb, gk);
             if (air) {
                 V3<T> v[3], vbc;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) v[c] = v3(vs[cd[c] & 0xffffu]);
+                for (int c = 0; c < 3; ++c) v[c] = v3(vs[cd[c] & (CODE_PARTICLES - 1)]);
                 const V3<T> G = (fb[0] + fb[1] + fb[2]) * (T(1) / T(3));
                 const V3<T> F =
                     air_adjoint(x, v, S.air[2 * tl.body], S.air[2 * tl.body + 1], G, xb, vbc) * (T(1) / T(3));
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     f[c] += F;
-                    cv[cd[c] >> 16] = l4(vbc, T(0));
+                    cv[at[c]] = l4(vbc, T(0));
                 }
             }
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                cs[cd[c] >> 16] = l4(xb[c], dot(f[c], fb[c]));
+                cs[at[c]] = l4(xb[c], dot(f[c], fb[c]));
             }
             if (w0) gsto(G0, o, g0 + gk);
         } else {
             if constexpr (!ONE) rec = load_elem(M, S, TILE_HINGE, tl.begin, (uint32_t)l);
-            const uint32_t cd[4] = {rec.c0, rec.c1, rec.c2, rec.c3};
+            const uint32_t cd[4] = {rec.c0 & 0xffffu, rec.c0 >> 16, rec.c1 & 0xffffu, rec.c1 >> 16};
+            int at[4];  // corner slots
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                x[c] = v3(xs[cd[c] & 0xffffu]);
-                fb[c] = v3(fbs[cd[c] & 0xffffu]);
+                x[c] = staged(xs, cd[c], at[c]);
+                fb[c] = v3(fbs[cd[c] & (CODE_PARTICLES - 1)]);
             }
             T gact;
             hinge_adjoint(x, rec.V, M.bodies[tl.body].kb, rec.act, fb, f, xb, gact);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cs[cd[c] >> 16] = l4(xb[c], dot(f[c], fb[c]));
+                cs[at[c]] = l4(xb[c], dot(f[c], fb[c]));
             }
             if (w0) gsto(G0, o, g0 + gact);
         }
@@ -1173,8 +1212,8 @@ __global__ void __launch_bounds__(RES_BLOCK) k_resident(const ModelDev<T>* __res
 #pragma unroll
             for (int c = 0; c < 4; ++c) code[k][c] = gldo(M.r_code + c * M.ne, 4u * (uint32_t)(B.e0 + l));
 #pragma unroll
-            for (int q = 0; q < 9; ++q) D[k][q] = gldo(M.tet_dinv + q * M.ne, o);
-            V[k] = gldo(M.tet_vol, o);
+            for (int q = 0; q < 9; ++q) D[k][q] = gldo(M.r_dinv + q * M.ne, o);
+            V[k] = gldo(M.r_dinv + 9 * M.ne, o);
             mu[k] = gldo(rows[0].mu, o);
             lam[k] = gldo(rows[0].lam, o);
         }
