@@ -107,13 +107,12 @@ int check_offsets(const int64_t* off, int nb, int64_t total, const char* name) {
     return GSIM_OK;
 }
 
-// Rest dihedral angle with the same orientation convention as the kernels.
-double rest_angle(const D3 x[4]) {
-    D3 E = sub(x[3], x[2]);
-    D3 N1 = crs(sub(x[0], x[2]), sub(x[0], x[3]));
-    D3 N2 = crs(sub(x[1], x[3]), sub(x[1], x[2]));
-    double el = nrm(E);
-    return std::atan2(-dt3(crs(N1, N2), E) / el, dt3(N1, N2));
+// Rest dihedral angle of the edge E (length el) between the normals N1 and N2, with the
+// same orientation convention as the kernels.  (A flat pair needs no arctangent: of a zero
+// over a positive number it is that zero.)
+double rest_angle(D3 E, double el, D3 N1, D3 N2) {
+    const double s = -dt3(crs(N1, N2), E) / el, c = dt3(N1, N2);
+    return s == 0 && c > 0 ? s : std::atan2(s, c);
 }
 
 // Greedy colouring for the fused path: per body and element kind, each element
@@ -203,7 +202,13 @@ int build_tiles(gsim_plan* P, bool wide) {
     P->corner[1].resize(P->nt);
     P->corner[2].resize(P->nh);
     P->etile_words[0] = P->etile_words[1] = 0;
-    std::vector<int32_t> mark(P->np, -1), loc(P->np, 0), cnt(P->np, 0), parts, fill;  // cnt: corners in the tile
+    // a particle in the tile being cut: the tile, its corners there (counted twice: when they
+    // are collected and when they are placed), its local index and first corner slot
+    struct InTile {
+        int32_t tile, corners, loc, first;
+    };
+    std::vector<InTile> in(P->np, InTile{-1, 0, 0, 0});
+    std::vector<int32_t> parts;
     for (int b = 0; b < nb; ++b)
         for (int kind = 0; kind < 3; ++kind) {
             const std::vector<int64_t>& off = kind == 0 ? P->eoff : kind == 1 ? P->toff : P->hoff;
@@ -225,20 +230,20 @@ int build_tiles(gsim_plan* P, bool wide) {
                     bool full = false;  // a corner code could not hold the particle's next corner
                     for (int c = 0; c < nc; ++c) {
                         const int32_t p = idx[c * n + e];
-                        if (mark[p] != tile) ++add;
-                        else full |= cnt[p] >= CODE_CORNERS;
+                        if (in[p].tile != tile) ++add;
+                        else full |= in[p].corners >= CODE_CORNERS;
                     }
                     const int64_t words = wp * (int64_t)(parts.size() + add) + wc * (int64_t)nc * (e - s + 1);
                     full |= words > ETILE_WORDS || parts.size() + add > (size_t)CODE_PARTICLES;
                     if (e > s && full) break;
                     for (int c = 0; c < nc; ++c) {
                         const int32_t p = idx[c * n + e];
-                        if (mark[p] != tile) {
-                            mark[p] = tile;
-                            cnt[p] = 0;
+                        if (in[p].tile != tile) {
+                            in[p].tile = tile;
+                            in[p].corners = 0;
                             parts.push_back(p);
                         }
-                        cnt[p]++;
+                        in[p].corners++;
                     }
                     ++e;
                 }
@@ -253,27 +258,27 @@ int build_tiles(gsim_plan* P, bool wide) {
                     if (!parts.empty() && (int64_t)hi - lo < 8 * (int64_t)parts.size()) {
                         size_t k = 0;
                         for (int32_t p = lo; p <= hi; ++p)
-                            if (mark[p] == tile) parts[k++] = p;
+                            if (in[p].tile == tile) parts[k++] = p;
                     } else {
                         std::sort(parts.begin(), parts.end());
                     }
                 }
                 const int m = (int)parts.size();
-                fill.resize(m);
                 for (int j = 0, at = 0; j < m; ++j) {
-                    const int32_t k = cnt[parts[j]];
-                    loc[parts[j]] = j;
-                    fill[j] = at;
-                    P->tp_run.push_back(at | (k << 16));
-                    at += k;
+                    InTile& q = in[parts[j]];
+                    q.loc = j;
+                    q.first = at;
+                    P->tp_run.push_back(at | (q.corners << 16));
+                    at += q.corners;
+                    q.corners = 0;
                 }
-                const int32_t* runs = P->tp_run.data() + P->tp_id.size();
                 for (int64_t l = s; l < e; ++l) {
                     uint64_t packed = 0;
                     for (int c = 0; c < nc; ++c) {
-                        const int j = loc[idx[c * n + l]], at = fill[j]++;
-                        if (wide) code[c * n + l] = (uint32_t)j | ((uint32_t)at << 16);
-                        packed |= (uint64_t)(j | (at - (runs[j] & 0xffff)) << CODE_BITS) << 16 * c;
+                        InTile& q = in[idx[c * n + l]];
+                        const int rank = q.corners++;
+                        if (wide) code[c * n + l] = (uint32_t)q.loc | ((uint32_t)(q.first + rank) << 16);
+                        packed |= (uint64_t)(q.loc | rank << CODE_BITS) << 16 * c;
                     }
                     P->corner[kind][l] = packed;
                 }
@@ -528,12 +533,12 @@ int build_plan(const gsim_model_desc* d, gsim_plan* P, bool fused) {
                 x[c] = X[id[c]];
             }
             if (!distinct(id, 4)) return fail(GSIM_E_TOPOLOGY, "hinge %lld repeats a particle", (long long)h);
-            D3 E = sub(x[3], x[2]);
-            double el = nrm(E);
-            double n1 = nrm(crs(sub(x[0], x[2]), sub(x[0], x[3]))), n2 = nrm(crs(sub(x[1], x[3]), sub(x[1], x[2])));
+            const D3 E = sub(x[3], x[2]), N1 = crs(sub(x[0], x[2]), sub(x[0], x[3])),
+                     N2 = crs(sub(x[1], x[3]), sub(x[1], x[2]));
+            const double el = nrm(E), n1 = nrm(N1), n2 = nrm(N2);
             if (!(el > 0) || !(n1 > 1e-12 * el * el) || !(n2 > 1e-12 * el * el))
                 return fail(GSIM_E_DEGENERATE, "hinge %lld is degenerate", (long long)h);
-            P->hin_phi0[h] = rest_angle(x);
+            P->hin_phi0[h] = rest_angle(E, el, N1, N2);
             for (int c = 0; c < 4; ++c) P->hin_idx[c * nh + h] = id[c];
         }
 

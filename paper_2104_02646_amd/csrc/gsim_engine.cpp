@@ -17,6 +17,7 @@
 // then for each checkpoint segment in reverse the recomputed forward steps and
 // the adjoint steps, then the contact-gradient reduction and the copy-out.
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <chrono>
 #include <cstring>
@@ -904,7 +905,11 @@ int gsim_engine_prepare(const gsim_query* in, gsim_prepared** out) {
     if (d->n_tris && !in->k_tri) return fail(GSIM_E_INVALID, "k_tri is required");
     // parameters are on the host here: a query that could only produce non-finite
     // results is refused before it takes a slot
+    // (one pass without exits first, which the compiler runs several values at a time)
     auto positive = [](const float* a, int64_t n, const char* what) -> int {
+        bool ok = true;
+        for (int64_t i = 0; i < n; ++i) ok &= (a[i] > 0.f) & (a[i] <= FLT_MAX);
+        if (ok) return GSIM_OK;
         for (int64_t i = 0; i < n; ++i) {
             if (!std::isfinite(a[i])) return fail(GSIM_E_NONFINITE, "%s[%lld] is not finite", what, (long long)i);
             if (!(a[i] > 0.f)) return fail(GSIM_E_INVALID, "%s[%lld] must be > 0", what, (long long)i);
@@ -912,6 +917,9 @@ int gsim_engine_prepare(const gsim_query* in, gsim_prepared** out) {
         return GSIM_OK;
     };
     auto finite = [](const float* a, int64_t n, const char* what) -> int {
+        bool ok = true;
+        for (int64_t i = 0; i < n; ++i) ok &= (a[i] >= -FLT_MAX) & (a[i] <= FLT_MAX);
+        if (ok) return GSIM_OK;
         for (int64_t i = 0; i < n; ++i)
             if (!std::isfinite(a[i])) return fail(GSIM_E_NONFINITE, "%s[%lld] is not finite", what, (long long)i);
         return GSIM_OK;
