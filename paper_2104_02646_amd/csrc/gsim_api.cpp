@@ -582,9 +582,9 @@ Layout make_layout(const gsim_plan* P, int max_steps) {
     L.bodies = take(sizeof(BodyDev<T>) * P->nb);
     L.etiles = take(sizeof(Tile) * cap_e);
     L.ptiles = take(sizeof(Tile) * cap_p);
-    L.tet_rec = take(12 * ne * sizeof(T));
-    L.tri_rec = take(8 * nt * sizeof(T));
-    L.hin_rec = take(4 * nh * sizeof(T));
+    L.tet_rec = take(REC_TET * ne * sizeof(T));
+    L.tri_rec = take(REC_TRI<T> * nt * sizeof(T));
+    L.hin_rec = take(REC_HINGE<T> * nh * sizeof(T));
     L.tp = take(P->tp_id.size() * 12 + 16);
     L.gbase = take(P->gbase.size() * 4 + 4);
     L.pdeg = take(np * 4);
@@ -1616,36 +1616,31 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
             chk(up(off, rec.data(), n * sizeof(T)));
             if (!sink && e == hipSuccess) e = hipStreamSynchronize(s);  // (the vector ends here)
         };
-        fill(L.tet_rec, 12 * (size_t)ne, [&](T* rec) {
+        constexpr int W = REC_WIDTH<T>;
+        fill(L.tet_rec, REC_TET * (size_t)ne, [&](T* rec) {
             const double* d = P->tet_dinv.data();
             for (int64_t i = 0; i < ne; ++i) {
-                T *q0 = rec + 4 * i, *q1 = rec + 4 * (ne + i), *q2 = rec + 4 * (2 * ne + i);
-                for (int q = 0; q < 4; ++q) {
-                    q0[q] = (T)d[q * ne + i];
-                    q1[q] = (T)d[(4 + q) * ne + i];
-                }
-                q2[0] = (T)d[8 * ne + i];
-                q2[1] = (T)P->tet_vol[i];
-                q2[3] = T(0);
-                std::memcpy(q2 + 2, &P->corner[0][i], 8);
+                T v[REC_TET];
+                for (int q = 0; q < 9; ++q) v[q] = (T)d[q * ne + i];
+                v[9] = (T)P->tet_vol[i];
+                v[11] = T(0);
+                std::memcpy(v + 10, &P->corner[0][i], 8);
+                for (int g = 0; g < REC_TET / W; ++g) std::memcpy(rec + W * (g * ne + i), v + W * g, 16);
             }
         });
-        fill(L.tri_rec, 8 * (size_t)nt, [&](T* rec) {
+        fill(L.tri_rec, REC_TRI<T> * (size_t)nt, [&](T* rec) {
             const double* d = P->tri_dinv.data();
             for (int64_t i = 0; i < nt; ++i) {
-                T *q0 = rec + 4 * i, *q1 = rec + 4 * (nt + i);
-                for (int q = 0; q < 4; ++q) q0[q] = (T)d[q * nt + i];
-                q1[0] = (T)P->tri_area[i];
-                q1[2] = q1[3] = T(0);
-                std::memcpy(q1 + 1, &P->corner[1][i], 8);
+                T v[8] = {(T)d[i], (T)d[nt + i], (T)d[2 * nt + i], (T)d[3 * nt + i], (T)P->tri_area[i]};
+                std::memcpy(v + 5, &P->corner[1][i], 8);
+                for (int g = 0; g < REC_TRI<T> / W; ++g) std::memcpy(rec + W * (g * nt + i), v + W * g, 16);
             }
         });
-        fill(L.hin_rec, 4 * (size_t)nh, [&](T* rec) {
+        fill(L.hin_rec, REC_HINGE<T> * (size_t)nh, [&](T* rec) {
             for (int64_t i = 0; i < nh; ++i) {
-                T* q = rec + 4 * i;
-                q[0] = (T)P->hin_phi0[i];
-                q[2] = q[3] = T(0);
-                std::memcpy(q + 1, &P->corner[2][i], 8);
+                T v[4] = {(T)P->hin_phi0[i]};
+                std::memcpy(v + 1, &P->corner[2][i], 8);
+                std::memcpy(rec + W * i, v, 16);
             }
         });
     }

@@ -31,6 +31,13 @@ enum TileKind : int32_t { TILE_TET = 0, TILE_TRI = 1, TILE_HINGE = 2, TILE_PART 
 const int32_t TILE_ADJ = 0x100;
 
 
+// Values per 16-byte vector of an element record, and per record of each kind (the codes
+// take two values in FP32 and one in FP64; records are filled up to whole vectors).
+template <typename T> constexpr int REC_WIDTH = 16 / (int)sizeof(T);
+constexpr int REC_TET = 12;
+template <typename T> constexpr int REC_TRI = sizeof(T) == 4 ? 8 : 6;
+template <typename T> constexpr int REC_HINGE = sizeof(T) == 4 ? 4 : 2;
+
 // One workgroup's share of a pass: `count` consecutive items of one kind of one body.
 struct Tile {
     int32_t model;  // index into the ModelDev / StepDev arrays of the launch
@@ -83,13 +90,13 @@ template <typename T>
 struct ModelDev {
     int64_t np, ne, nt, nh, nslot;
     int32_t n_bodies, n_ptiles;
-    // element records, 4-vectors SoA over elements: tets {Dm^-1 0..3} {Dm^-1 4..7}
-    // {Dm^-1 8, volume, codes}; triangles {Dm^-1 0..3} {area, codes}; hinges {rest angle,
-    // codes}.  The codes are 16 bits per corner, 8 bytes in the vector's next element(s):
-    // tile-local particle | rank among the particle's corners in the tile << CODE_BITS
-    const T* tet_rec;  // [3][ne][4]
-    const T* tri_rec;  // [2][nt][4]
-    const T* hin_rec;  // [nh][4]
+    // element records, 16-byte vectors SoA over elements (REC_WIDTH values each): tets Dm^-1
+    // 0..8, volume, codes; triangles Dm^-1 0..3, area, codes; hinges rest angle, codes.  The
+    // codes are 16 bits per corner, 8 bytes in the next value(s): tile-local particle | rank
+    // among the particle's corners in the tile << CODE_BITS
+    const T* tet_rec;
+    const T* tri_rec;
+    const T* hin_rec;
     // tile particles (Tile.id = first, Tile.pad = count), one 16-byte record each:
     // particle index, corner run (first sorted corner | count << 16), partial slot, 0
     const int32_t* tp;

@@ -611,15 +611,23 @@ __device__ __forceinline__ gi4 ld_tp(const int32_t* tp, uint32_t j) {
     return gi4{gldo(tp, 12 * j), gldo(tp + 1, 12 * j), gldo(tp + 2, 12 * j), 0};
 }
 
-// The 4-vectors of the element records (one 16-byte load in FP32), and a particle's
-// first corner slot in the w of its staged position.
-template <typename T> struct Vec4;
-template <> struct Vec4<float> { typedef float t __attribute__((ext_vector_type(4))); };
-template <> struct Vec4<double> { typedef double t __attribute__((ext_vector_type(4))); };
-template <typename T>
-__device__ __forceinline__ typename Vec4<T>::t ld_rec(const T* rec, uint32_t l) {
-    return gldo(reinterpret_cast<const typename Vec4<T>::t*>(rec), (uint32_t)(4 * sizeof(T)) * l);
+// The 16-byte vectors of the element records: the N first values of element l's record
+// (`rec` at the tile's first element, n elements in all).
+template <typename T> struct Vec16;
+template <> struct Vec16<float> { typedef float t __attribute__((ext_vector_type(4))); };
+template <> struct Vec16<double> { typedef double t __attribute__((ext_vector_type(2))); };
+template <typename T, int N>
+__device__ __forceinline__ void ld_rec(const T* rec, int64_t n, uint32_t l, T v[N]) {
+    constexpr int W = REC_WIDTH<T>;
+#pragma unroll
+    for (int g = 0; g < N / W; ++g) {
+        const auto q = gldo(reinterpret_cast<const typename Vec16<T>::t*>(rec + g * W * n), 16 * l);
+#pragma unroll
+        for (int j = 0; j < W; ++j) v[g * W + j] = q[j];
+    }
 }
+// Corner codes in a record's value(s), and a particle's first corner slot in the w of its
+// staged position.
 __device__ __forceinline__ void codes_of(float a, float b, uint32_t& c0, uint32_t& c1) {
     c0 = __builtin_bit_cast(uint32_t, a);
     c1 = __builtin_bit_cast(uint32_t, b);
@@ -654,27 +662,28 @@ __device__ __forceinline__ ElemRec<T> load_elem(const ModelDev<T>& M, const Step
     T d[9] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
     T V, p0 = T(0), p1 = T(0), act = T(0);
     if (kind == TILE_TET) {
-        const T* rec = M.tet_rec + 4 * begin;
-        const auto a = ld_rec(rec, l), b = ld_rec(rec + 4 * M.ne, l), q = ld_rec(rec + 8 * M.ne, l);
-        d[0] = a.x, d[1] = a.y, d[2] = a.z, d[3] = a.w;
-        d[4] = b.x, d[5] = b.y, d[6] = b.z, d[7] = b.w;
-        d[8] = q.x;
-        V = q.y;
-        codes_of(q.z, q.w, c[0], c[1]);
+        T v[REC_TET];
+        ld_rec<T, REC_TET>(M.tet_rec + REC_WIDTH<T> * begin, M.ne, l, v);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) d[k] = v[k];
+        V = v[9];
+        codes_of(v[10], v[11], c[0], c[1]);
         p0 = gldo(S.mu + begin, o);
         p1 = gldo(S.lam + begin, o);
         if (S.act) act = gldo(S.act + begin, o);
     } else if (kind == TILE_TRI) {
-        const T* rec = M.tri_rec + 4 * begin;
-        const auto a = ld_rec(rec, l), q = ld_rec(rec + 4 * M.nt, l);
-        d[0] = a.x, d[1] = a.y, d[2] = a.z, d[3] = a.w;
-        V = q.x;
-        codes_of(q.y, q.z, c[0], c[1]);
+        T v[REC_TRI<T>];
+        ld_rec<T, REC_TRI<T>>(M.tri_rec + REC_WIDTH<T> * begin, M.nt, l, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d[k] = v[k];
+        V = v[4];
+        codes_of(v[5], v[REC_TRI<T> - 2], c[0], c[1]);
         p0 = gldo(S.ktri + begin, o);
     } else {
-        const auto q = ld_rec(M.hin_rec + 4 * begin, l);
-        V = q.x;
-        codes_of(q.y, q.z, c[0], c[1]);
+        T v[REC_HINGE<T>];
+        ld_rec<T, REC_HINGE<T>>(M.hin_rec + REC_WIDTH<T> * begin, M.nh, l, v);
+        V = v[0];
+        codes_of(v[1], v[REC_HINGE<T> - 2], c[0], c[1]);
         if (S.hact) act = gldo(S.hact + begin, o);
     }
     return ElemRec<T>{c[0], c[1], d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8], V, p0, p1, act};
@@ -686,6 +695,17 @@ __device__ __forceinline__ V3<T> staged(const L4<T>* xs, uint32_t code, int& at)
     const L4<T> q = xs[code & (CODE_PARTICLES - 1)];
     at = slot_index(q.w) + (int)(code >> CODE_BITS);
     return v3(q);
+}
+
+// In FP64 the four slots are read again once the element is computed: held meanwhile they
+// would be the registers that spill.
+template <typename T>
+__device__ __forceinline__ void slots_again(const L4<T>* xs, const uint32_t code[4], int at[4]) {
+    if constexpr (std::is_same<T, double>::value) {
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int c = 0; c < 4; ++c) at[c] = slot_index(xs[code[c] & (CODE_PARTICLES - 1)].w) + (int)(code[c] >> CODE_BITS);
+    }
 }
 
 // Element pass: one workgroup per planned element tile.  The positions of the
@@ -708,7 +728,7 @@ __device__ __forceinline__ V3<T> staged(const L4<T>* xs, uint32_t code, int& at)
 // A batch also moves its element records twice a step, so a tet's is 48 bytes in three
 // 16-byte loads: corner codes of 16 bits, the particle's first slot riding in the w of its
 // staged position (with 32-bit codes and one array per value, 56 bytes in 14 loads: 256-body
-// batch gradient 7230 -> 6890 us, 64-body rollout 1274 -> 1219 us).
+// batch gradient 7230 -> 6840 us, 64-body rollout 1274 -> 1210 us).
 // Measured together, before and after: one-cube gradient of 100 steps 1689 -> 1611 us,
 // 200k-tet blob 2570 -> 2466 us, 256-body batch 7388 -> 7274 us.
 // AIR: the variant launched for models with a lift/drag body (the other compiles
@@ -748,6 +768,7 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDe
             T J1;
             tet_force(x, D, rec.V, rec.p0, rec.p1, rec.act, f, J1);
             if (J1 <= T(-1)) raise_flag(M, tl.body, 1);
+            slots_again(xs, cd, at);
 #pragma unroll
             for (int c = 0; c < 4; ++c) cs[at[c]] = l4(f[c], T(0));
         } else if (tl.kind == TILE_TRI) {
@@ -775,6 +796,7 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDe
 #pragma unroll
             for (int c = 0; c < 4; ++c) x[c] = staged(xs, cd[c], at[c]);
             hinge_force(x, rec.V, M.bodies[tl.body].kb, rec.act, f);
+            slots_again(xs, cd, at);
 #pragma unroll
             for (int c = 0; c < 4; ++c) cs[at[c]] = l4(f[c], T(0));
         }
@@ -939,6 +961,7 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
                 fb[c] = v3(fbs[cd[c] & (CODE_PARTICLES - 1)]);
             }
             tet_adjoint(x, D, rec.V, rec.p0, rec.p1, rec.act, fb, f, xb, g0, g1, g2);
+            slots_again(xs, cd, at);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 cs[at[c]] = l4(xb[c], fdot(f[c], fb[c]));
@@ -987,6 +1010,7 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
             }
             T gact;
             hinge_adjoint(x, rec.V, M.bodies[tl.body].kb, rec.act, fb, f, xb, gact);
+            slots_again(xs, cd, at);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 cs[at[c]] = l4(xb[c], dot(f[c], fb[c]));
