@@ -661,11 +661,19 @@ void natural_tiles(const gsim_model* m, bool particles, int tile, std::vector<Ti
 
 // Lanes nobody asked for are used only where they pay: a second stream hides one lane's
 // particle pass behind the other's element pass, which needs launches that fill the card,
-// and costs a second set of launches.  Measured over ragged tet batches (100 steps, one
-// lane / two, us): gradient at 61 tiles 1754 / 2767, 493 tiles 2046 / 2632, 917 tiles
-// 2485 / 2883, 1252 tiles 3015 / 2784, 3570 tiles 6412 / 5548; rollout at 489 tiles
-// 815 / 1518, 1641 tiles 1284 / 1331 (1280 / 1446 as a graph), 1980 tiles 1532 / 1391.
-// 16 cloths with lift/drag (105 tiles), gradient: 2412 / 2947.
+// and costs a second set of launches.  Measured over ragged tet batches (one lane / two, us;
+// FP32, 100 steps): gradient at 16k elements 1754 / 2767, 126k 2046 / 2632, 235k 2485 / 2883,
+// 321k 3015 / 2784, 914k 6412 / 5548; rollout at 125k 815 / 1518, 420k 1284 / 1331 (1280 /
+// 1446 as a graph), 507k 1532 / 1391.  FP64, 20 steps: gradient at 118k 560 / 796, 235k 848 /
+// 855 (912 / 844 in tiles of 512), 357k 1146 / 1023; rollout at 235k 279 / 335, 357k 401 /
+// 363.  16 cloths with lift/drag (27k elements), gradient: 2412 / 2947.
+const int64_t LANES_MIN = 1 << 18;           // elements, an FP64 one counting one and a half
+const int64_t LANES_MIN_FWD = 7 << 16;       // sequences of forward passes alone
+template <typename T>
+int64_t lane_work(const gsim_model* m) {
+    const int64_t n = m->ne + m->nt + m->nh;
+    return std::is_same<T, double>::value ? n + n / 2 : n;
+}
 // Four lanes run as three: with the caller's stream they would take all four hardware
 // queues, and each costs its set of launches.  Measured on the 256-body gradient at 512
 // elements a tile, three / four lanes, ms: plain 7.08 / 8.90, graphs 7.38 / 7.68 (one model
@@ -673,8 +681,6 @@ void natural_tiles(const gsim_model* m, bool particles, int tile, std::vector<Ti
 // fault inside hipGraph calls came with (a process with many graphs before, cause not
 // known); none are made now.
 const int RUN_LANES = 3;
-const int LANES_MIN_TILES = 1024;      // element tiles (4 per CU); below: one lane
-const int LANES_MIN_TILES_FWD = 1792;  // (7 per CU) sequences of forward passes alone
 
 template <typename T>
 int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
@@ -684,7 +690,7 @@ int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     natural_tiles(m, true, m->pblock * m->pitems, m->ptiles_nat, m->n_ptile_rows);
     // launch lanes: bodies assigned largest first to the lane with the least work so
     // far; each lane's tiles are XCD-ordered on their own and the lists concatenated
-    m->run_lanes = !m->lanes_chosen && (int)m->etiles_nat.size() < LANES_MIN_TILES ? 1 : std::min(m->lanes, RUN_LANES);
+    m->run_lanes = !m->lanes_chosen && lane_work<T>(m) < LANES_MIN ? 1 : std::min(m->lanes, RUN_LANES);
     if (m->run_lanes > 1 && !m->ev_fork) HIP_TRY(hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming), "lane event");
     for (int l = 1; l < m->run_lanes; ++l) {  // the lanes' streams and fork / join events
         if (!m->lane_stream[l])
@@ -872,7 +878,7 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
     Ctx<T> c = ctx<T>(m);
     const ModelDev<T>* md = c.md;
     int nl = m->timing_mask == 0 ? m->run_lanes : 1;
-    if (!m->lanes_chosen && !m->any_air && m->n_etiles < LANES_MIN_TILES_FWD) {
+    if (!m->lanes_chosen && !m->any_air && lane_work<T>(m) < LANES_MIN_FWD) {
         bool forward = true;  // (a sequence of forward passes alone)
         for (const Launch& l : seq) forward = forward && l.op == OP_FWD;
         if (forward) nl = 1;
