@@ -45,6 +45,7 @@ constexpr int RROUND = 64 * RSLICE;  // triangles a round stages, and chunks a l
 constexpr int RBOX = 4;           // values per triangle box
 constexpr int RREC = 10;          // values per triangle record
 constexpr int RTERM = 16;         // values per staged record
+constexpr int RBOXED = 0x80;      // mark of a staged triangle (see unsafe_term)
 const double RCUT = 13.815510557964274;  // -ln(1e-6)
 
 // Per-triangle box and record, written once per frame.  Box: the bounding box widened by
@@ -77,6 +78,15 @@ __device__ __forceinline__ T cr2(T ax, T ay, T bx, T by) {
     return ax * by - ay * bx;
 }
 
+// Box of the corners q[0..5] widened by r.
+template <typename T>
+__device__ __forceinline__ void box_of(const T* q, T r, T* b) {
+    b[0] = fmin(fmin(q[0], q[2]), q[4]) - r;
+    b[1] = fmax(fmax(q[0], q[2]), q[4]) + r;
+    b[2] = fmin(fmin(q[1], q[3]), q[5]) - r;
+    b[3] = fmax(fmax(q[1], q[3]), q[5]) + r;
+}
+
 // A record as tri_term takes it: corners [0..5], edge vectors ab, bc, ca [6..11],
 // orientation [12], reciprocal squared edge lengths [13..15].
 template <typename T>
@@ -91,6 +101,18 @@ __device__ __forceinline__ void term_of(const T* q, T* r) {
         r[13 + k] = q[7 + k];
     }
     r[12] = q[6];
+}
+
+// Whether tri_term may take a pixel out of reach for one inside, or for one with no
+// distance at all: its coordinates are not finite or too far apart to be squared, or it is
+// so thin (twice its area against the square of its extent L, r the cut-off distance)
+// that the three orientations of a pixel r away may all be roundings.
+template <typename T>
+__device__ __forceinline__ bool unsafe_term(const T* q, T r) {
+    constexpr T eps = sizeof(T) == 4 ? T(0x1p-16) : T(0x1p-45);  // 2^8 roundings
+    const T L = (fmax(fmax(q[0], q[2]), q[4]) - fmin(fmin(q[0], q[2]), q[4])) +
+                (fmax(fmax(q[1], q[3]), q[5]) - fmin(fmin(q[1], q[3]), q[5]));
+    return !(fabs(cr2(q[2] - q[0], q[3] - q[1], q[4] - q[0], q[5] - q[1])) * r > eps * L * L * (L + r));
 }
 
 // Squared distance from a point at w from the segment's start to the segment e (inv: 1 /
@@ -171,10 +193,7 @@ __global__ __launch_bounds__(256) void k_raster_tri_prep(RasterArgs<T> A, const 
                 q[2 * k + 1] = u.y;
             }
             const T ax = q[0], ay = q[1], bx = q[2], by = q[3], cx = q[4], cy = q[5];
-            b[0] = fmin(fmin(ax, bx), cx) - r;
-            b[1] = fmax(fmax(ax, bx), cx) + r;
-            b[2] = fmin(fmin(ay, by), cy) - r;
-            b[3] = fmax(fmax(ay, by), cy) + r;
+            box_of(q, r, b);
             nan = b[0] != b[0] || b[2] != b[2];
             const T area = cr2(bx - ax, by - ay, cx - ax, cy - ay);
             q[6] = area > T(0) ? T(1) : (area < T(0) ? T(-1) : T(0));
@@ -223,6 +242,23 @@ __device__ __forceinline__ int rank_of(bool keep, int* count, int& total) {
     return base + __popcll(m & ((1ull << lane) - 1ull));
 }
 
+// Every fourth listed triangle from the group's on: Q *= 1 + e^x at its pixel.
+template <typename T, bool BOXED>
+__device__ __forceinline__ void take_terms(const RasterArgs<T>& A, const Vec<T, RTERM>* rec, const uint16_t* list,
+                                           int group, int n, T px, T py, T& Q) {
+    for (int k = group; k < n; k += 4) {
+        const Vec<T, RTERM> r = rec[list[k]];
+        if constexpr (BOXED) {
+            T b[RBOX];
+            box_of(r.v, sqrt(A.cut), b);
+            if ((px < b[0]) | (px > b[1]) | (py < b[2]) | (py > b[3])) continue;
+        }
+        T x, t;
+        int e;
+        if (tri_term(px, py, r.v, A.isigma, A.cut, x, e, t)) Q = fma(Q, exp(x), Q);  // Q (1 + e^x)
+    }
+}
+
 // One pixel tile of QUADS (4 or 1) quadrants of 4 x 4 pixels per workgroup of RSLICE
 // wavefronts; writes the transmittance and (if not null) the image.  RROUND chunk boxes at
 // a time are tested and the chunks that reach the tile listed in order; RSLICE listed
@@ -248,7 +284,7 @@ __global__ __launch_bounds__(64 * RSLICE) void k_raster_fwd(RasterArgs<T> A, T* 
     __shared__ T part[PARTS][RT * RT];
     __shared__ uint16_t hit[RROUND];
     __shared__ uint16_t mine[RSLICE][RROUND / SHARE];
-    __shared__ uint8_t reach[RROUND];
+    __shared__ uint8_t reach[RROUND];  // quadrants a triangle reaches | RBOXED
     __shared__ int count[RSLICE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int quad = wave & (QUADS - 1), turn = wave / QUADS, group = lane >> 4, pix = lane & 15;
@@ -290,26 +326,27 @@ __global__ __launch_bounds__(64 * RSLICE) void k_raster_fwd(RasterArgs<T> A, T* 
                 Vec<T, RTERM> r;
                 term_of(q, r.v);
                 rec[k0] = r;
-                reach[k0] = (uint8_t)to;
+                reach[k0] = (uint8_t)(unsafe_term(q, sqrt(A.cut)) ? to | RBOXED : to);
             }
             __syncthreads();
             // this wavefront's triangles
             int n = 0;
+            unsigned long long boxed = 0;
             for (int k = 0; k < total; k += 64) {
-                const bool in = k + lane < total && (reach[k + lane] >> quad & 1);
+                const int to = k + lane < total ? reach[k + lane] : 0;
+                const bool in = to >> quad & 1;
                 const unsigned long long m = __ballot(in);
+                boxed |= __ballot(to & RBOXED);
                 const int o = n + __popcll(m & ((1ull << lane) - 1ull));
                 if (in && o % SHARE == turn) mine[wave][o / SHARE] = (uint16_t)(k + lane);
                 n += __popcll(m);
             }
             n = (n + SHARE - 1 - turn) / SHARE;
             __builtin_amdgcn_wave_barrier();
-            for (int k = group; k < n; k += 4) {
-                const Vec<T, RTERM> r = rec[mine[wave][k]];
-                T x, t;
-                int e;
-                if (tri_term(px, py, r.v, A.isigma, A.cut, x, e, t)) Q = fma(Q, exp(x), Q);  // Q (1 + e^x)
-            }
+            // each pixel against the box too where a term may be wrong about its reach (tested in
+            // every round it takes 5-8 % of the kernel, chosen by round 1-4 %)
+            if (boxed) take_terms<T, true>(A, rec, mine[wave], group, n, px, py, Q);
+            else take_terms<T, false>(A, rec, mine[wave], group, n, px, py, Q);
         }
         __syncthreads();  // the list of chunks is no longer read
     }
