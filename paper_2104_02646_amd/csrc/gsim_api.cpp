@@ -180,11 +180,16 @@ void colour_elements(gsim_plan* P) {
 // Element tiles of the two-pass path.  Per body and element kind, consecutive
 // elements are cut into tiles of at most tile_elems elements, a tile ending early when
 // its adjoint LDS (8 words per tile particle, 4 per corner) would exceed
-// ETILE_WORDS, or what a corner code can hold (CODE_PARTICLES, CODE_CORNERS).  Per tile: its particles in increasing index order (the tile
+// ETILE_WORDS.  Per tile: its particles in increasing index order (the tile
 // particles); its corners ordered by (tile particle, element, corner), so each
 // tile particle's corners form one contiguous run; corner code = tile-local
 // particle | position in that order << 16.  The kernels sum each run into one
-// partial per (tile, particle).  Partials are stored sliced-ELL: each body's
+// partial per (tile, particle).
+// The records hold 16-bit codes: tile-local particle | rank in its run.  A particle of more
+// than CODE_CORNERS corners in the tile gets one more tile particle for each further
+// CODE_CORNERS, after all others: the same particle, staged with the slot where that part
+// of its run begins, and with an empty run of its own (nothing is summed for it).
+// Partials are stored sliced-ELL: each body's
 // particles are cut into slices of 64 from the body's first particle; slice g
 // holds width_g = max partials per particle of its particles, and the k-th tile
 // (plan order) touching the particle at lane j writes slot gbase[g] + 64 k + j.
@@ -203,11 +208,12 @@ int build_tiles(gsim_plan* P, bool wide) {
     P->corner[2].resize(P->nh);
     P->etile_words[0] = P->etile_words[1] = 0;
     // a particle in the tile being cut: the tile, its corners there (counted twice: when they
-    // are collected and when they are placed), its local index and first corner slot
+    // are collected and when they are placed), its local index and first corner slot, and
+    // the local index behind which its further entries follow
     struct InTile {
-        int32_t tile, corners, loc, first;
+        int32_t tile, corners, loc, first, more;
     };
-    std::vector<InTile> in(P->np, InTile{-1, 0, 0, 0});
+    std::vector<InTile> in(P->np, InTile{-1, 0, 0, 0, 0});
     std::vector<int32_t> parts;
     for (int b = 0; b < nb; ++b)
         for (int kind = 0; kind < 3; ++kind) {
@@ -227,15 +233,9 @@ int build_tiles(gsim_plan* P, bool wide) {
                 parts.clear();
                 while (e < off[b + 1] && e - s < P->tile_elems) {
                     int add = 0;
-                    bool full = false;  // a corner code could not hold the particle's next corner
-                    for (int c = 0; c < nc; ++c) {
-                        const int32_t p = idx[c * n + e];
-                        if (in[p].tile != tile) ++add;
-                        else full |= in[p].corners >= CODE_CORNERS;
-                    }
+                    for (int c = 0; c < nc; ++c) add += in[idx[c * n + e]].tile != tile;
                     const int64_t words = wp * (int64_t)(parts.size() + add) + wc * (int64_t)nc * (e - s + 1);
-                    full |= words > ETILE_WORDS || parts.size() + add > (size_t)CODE_PARTICLES;
-                    if (e > s && full) break;
+                    if (e > s && words > ETILE_WORDS) break;
                     for (int c = 0; c < nc; ++c) {
                         const int32_t p = idx[c * n + e];
                         if (in[p].tile != tile) {
@@ -263,22 +263,34 @@ int build_tiles(gsim_plan* P, bool wide) {
                         std::sort(parts.begin(), parts.end());
                     }
                 }
-                const int m = (int)parts.size();
-                for (int j = 0, at = 0; j < m; ++j) {
+                const int own = (int)parts.size();
+                for (int j = 0, at = 0; j < own; ++j) {
                     InTile& q = in[parts[j]];
                     q.loc = j;
                     q.first = at;
                     P->tp_run.push_back(at | (q.corners << 16));
                     at += q.corners;
+                }
+                for (int j = 0; j < own; ++j) {
+                    InTile& q = in[parts[j]];
+                    q.more = (int32_t)parts.size() - 1;
+                    for (int k = CODE_CORNERS; k < q.corners; k += CODE_CORNERS) {
+                        const int32_t p = parts[j];
+                        parts.push_back(p);
+                        P->tp_run.push_back(q.first + k);  // (an empty run)
+                    }
                     q.corners = 0;
                 }
+                const int m = (int)parts.size();
+                if (m > CODE_PARTICLES) return fail(GSIM_E_UNSUPPORTED, "a tile of %d particles", m);
                 for (int64_t l = s; l < e; ++l) {
                     uint64_t packed = 0;
                     for (int c = 0; c < nc; ++c) {
                         InTile& q = in[idx[c * n + l]];
                         const int rank = q.corners++;
                         if (wide) code[c * n + l] = (uint32_t)q.loc | ((uint32_t)(q.first + rank) << 16);
-                        packed |= (uint64_t)(q.loc | rank << CODE_BITS) << 16 * c;
+                        const int part = rank / CODE_CORNERS;
+                        packed |= (uint64_t)((part ? q.more + part : q.loc) | rank % CODE_CORNERS << CODE_BITS) << 16 * c;
                     }
                     P->corner[kind][l] = packed;
                 }
@@ -300,7 +312,8 @@ int build_tiles(gsim_plan* P, bool wide) {
         }
     // partial slots (sliced ELL)
     P->pdeg.assign(P->np, 0);
-    for (int32_t p : P->tp_id) P->pdeg[p]++;
+    for (size_t i = 0; i < P->tp_id.size(); ++i)
+        if (P->tp_run[i] >> 16) P->pdeg[P->tp_id[i]]++;
     P->gbase.clear();
     P->body_g0.assign(nb, 0);
     std::vector<int64_t> pbase(P->np);  // slot of partial 0 of each particle
@@ -319,8 +332,9 @@ int build_tiles(gsim_plan* P, bool wide) {
     }
     P->nslot = total;
     std::vector<int32_t> cur(P->np, 0);
-    P->tp_slot.resize(P->tp_id.size());
+    P->tp_slot.assign(P->tp_id.size(), 0);
     for (size_t i = 0; i < P->tp_id.size(); ++i) {
+        if (!(P->tp_run[i] >> 16)) continue;
         const int32_t p = P->tp_id[i];
         P->tp_slot[i] = (int32_t)(pbase[p] + 64 * (int64_t)cur[p]++);
     }
@@ -347,6 +361,7 @@ void build_resident(gsim_plan* P) {
         at.resize(4 * (size_t)t.count);
         for (int j = t.id; j < t.id + t.pad; ++j) {
             const uint32_t first = P->tp_run[j] & 0xffff, n = (uint32_t)P->tp_run[j] >> 16;
+            if (!n) continue;
             const uint32_t padded = (n + RES_PAD - 1) / RES_PAD * RES_PAD, base = (uint32_t)slots[t.body];
             for (uint32_t q = 0; q < n; ++q) at[first + q] = base + q;
             run[P->tp_slot[j]] = base | padded << 16;
@@ -1895,21 +1910,28 @@ int gsim_plan_colouring(const gsim_plan* P, int kind, int32_t* order, int32_t* b
 int gsim_plan_tiles(const gsim_plan* P, int64_t* tiles, int64_t* n_tiles, int32_t* tile_particles, int32_t* runs,
                     int32_t* slots, int64_t* n_tile_particles) {
     if (!P) return fail(GSIM_E_INVALID, "NULL plan");
-    if (tiles)
-        for (size_t i = 0; i < P->etiles.size(); ++i) {
-            const Tile& t = P->etiles[i];
+    // (without the further entries of particles of many corners, see build_tiles)
+    int64_t n = 0;
+    for (size_t i = 0; i < P->etiles.size(); ++i) {
+        const Tile& t = P->etiles[i];
+        if (tiles) {
             int64_t* r = tiles + 5 * i;
             r[0] = t.kind;
             r[1] = t.body;
             r[2] = t.begin;
             r[3] = t.count;
-            r[4] = t.id;
+            r[4] = n;
         }
+        for (int32_t j = t.id; j < t.id + t.pad; ++j) {
+            if (!(P->tp_run[j] >> 16)) continue;
+            if (tile_particles) tile_particles[n] = P->tp_id[j];
+            if (runs) runs[n] = P->tp_run[j];
+            if (slots) slots[n] = P->tp_slot[j];
+            ++n;
+        }
+    }
     if (n_tiles) *n_tiles = (int64_t)P->etiles.size();
-    if (tile_particles) std::copy(P->tp_id.begin(), P->tp_id.end(), tile_particles);
-    if (runs) std::copy(P->tp_run.begin(), P->tp_run.end(), runs);
-    if (slots) std::copy(P->tp_slot.begin(), P->tp_slot.end(), slots);
-    if (n_tile_particles) *n_tile_particles = (int64_t)P->tp_id.size();
+    if (n_tile_particles) *n_tile_particles = n;
     return GSIM_OK;
 }
 

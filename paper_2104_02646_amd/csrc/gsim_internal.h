@@ -93,7 +93,7 @@ struct ModelDev {
     // element records, 16-byte vectors SoA over elements (REC_WIDTH values each): tets Dm^-1
     // 0..8, volume, codes; triangles Dm^-1 0..3, area, codes; hinges rest angle, codes.  The
     // codes are 16 bits per corner, 8 bytes in the next value(s): tile-local particle | rank
-    // among the particle's corners in the tile << CODE_BITS
+    // among that tile particle's corners << CODE_BITS
     const T* tet_rec;
     const T* tri_rec;
     const T* hin_rec;
@@ -287,8 +287,12 @@ int launch_fused_adj(const ModelDev<T>* md, const StepDev<T>* sd, const int32_t*
 // body, and at most ETILE_WORDS words of adjoint LDS (8 per tile particle, 4 per
 // corner; triangle tiles of bodies with air: 12 and 8)
 const int ETILE = 256, ETILE_WORDS = 16384;
-// and what a corner code holds: particles of a tile, corners of a particle in a tile
-const int CODE_BITS = 10, CODE_PARTICLES = 1 << CODE_BITS, CODE_CORNERS = 1 << (16 - CODE_BITS);
+// A corner code: 11 bits of tile particle, 5 of rank in its run.  ETILE_WORDS bounds a tile
+// to 1365 particles and 4096 corners, so the 11 bits hold every particle and its further
+// entries.  (With 10 and 6 bits, and a tile ending at the 64th corner of a particle, a fan's
+// hub had four times the partials, which one thread sums: gradient of 20 steps of fans of
+// 5000 and 20000 tets 1003 and 3159 us; in tiles that end at their LDS 666 and 1172.)
+const int CODE_BITS = 11, CODE_PARTICLES = 1 << CODE_BITS, CODE_CORNERS = 1 << (16 - CODE_BITS);
 
 const int FUSED_FWD_BLOCK = 1024, FUSED_ADJ_BLOCK = 512;
 // dynamic LDS per particle of the largest body: x, v, f (forward); fbar, xbar-acc, f.fbar (adjoint)

@@ -806,6 +806,7 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDe
     for (int j = tid; j < m; j += nth) {
         const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int r0 = r.y & 0xffff, rn = r.y >> 16;
+        if (!rn) break;  // (further entries of particles of many corners: the last ones)
         V3<T> f = zero3<T>();
         for (int k = 0; k < rn; ++k) f += v3(cs[r0 + k]);
         st_fslot(M.fslots, r.z, f.x, f.y, f.z);
@@ -1023,6 +1024,7 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
     for (int j = tid; j < m; j += nth) {
         const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int r0 = r.y & 0xffff, rn = r.y >> 16;
+        if (!rn) break;  // (further entries of particles of many corners: the last ones)
         V3<T> xb = zero3<T>();
         T d = T(0);
         for (int k = 0; k < rn; ++k) {
