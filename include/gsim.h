@@ -69,7 +69,8 @@ enum { GSIM_F32 = 32, GSIM_F64 = 64 };
  * tets (at most 1536 tets and 512 particles each) run a call's steps in one launch that
  * keeps each body on one compute unit, under GSIM_EXEC_PLAIN, GRAPH and PERSIST alike:
  * bitwise the two-pass results.  They keep the launches below while a kernel is timed
- * (gsim_model_set_timing) and for particle passes of several particles per thread. */
+ * (gsim_model_set_timing), for particle passes of several particles per thread and, but for
+ * PERSIST, where the bodies take more turns on the card than the call's steps are worth. */
 enum {
     GSIM_EXEC_PLAIN = 0,   /* two kernel launches per step (element pass, particle pass) */
     GSIM_EXEC_GRAPH = 1,   /* the same launches captured once into a hipGraph and replayed

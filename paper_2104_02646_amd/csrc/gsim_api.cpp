@@ -697,6 +697,13 @@ int64_t lane_work(const gsim_model* m) {
 // known); none are made now.
 const int RUN_LANES = 3;
 
+// The lanes a sequence runs on (forward: one of forward passes alone).
+template <typename T>
+int sequence_lanes(const gsim_model* m, bool forward) {
+    if (m->timing_mask != 0) return 1;
+    return forward && !m->lanes_chosen && !m->any_air && lane_work<T>(m) < LANES_MIN_FWD ? 1 : m->run_lanes;
+}
+
 template <typename T>
 int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     std::vector<Tile> et, pt;
@@ -892,12 +899,9 @@ template <typename T>
 int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
     Ctx<T> c = ctx<T>(m);
     const ModelDev<T>* md = c.md;
-    int nl = m->timing_mask == 0 ? m->run_lanes : 1;
-    if (!m->lanes_chosen && !m->any_air && lane_work<T>(m) < LANES_MIN_FWD) {
-        bool forward = true;  // (a sequence of forward passes alone)
-        for (const Launch& l : seq) forward = forward && l.op == OP_FWD;
-        if (forward) nl = 1;
-    }
+    bool forward = true;  // a sequence of forward passes alone
+    for (const Launch& l : seq) forward = forward && l.op == OP_FWD;
+    const int nl = sequence_lanes<T>(m, forward);
     const bool one = m->etile_max <= m->block;  // every tile's elements fit one per thread
     hipStream_t s0 = (hipStream_t)stream;
     bool forked = false;
@@ -1157,15 +1161,40 @@ int check_params(const gsim_model* m, const gsim_params* p, const gsim_grads* g 
     return GSIM_OK;
 }
 
-// A call's steps go through the resident kernel: the model's bodies qualify, the particle
+// Whether a run of `fwd` forward and `adj` adjoint steps takes less time resident than as two
+// launches a step (overlap: the two-pass run would share launches between both), by an
+// estimate of both in us.  Resident, the card takes the bodies in rounds of res_bodies, and
+// a round lasts at least one body's chain however small the body, so what costs is the
+// rounds: of many bodies, or of many small ones beside a large one, whose LDS and threads
+// each of them then takes.  Two passes cost a launch pair per step (and, on more than one
+// lane, a fork and join a call), however many bodies share it.  Measured, resident / two
+// passes: 16 steps of 162-tet cubes (512 at a time) x 500 38 / 131, x 2000 127 / 188, x 4000
+// 247 / 274, x 8000 480 / 442, one step of them x 2000 29 / 23, x 8000 89 / 53; of 700-tet
+// bodies (256 at a time) x 256 61 / 152, x 1000 214 / 324, x 2000 415 / 438, one step of those
+// 68 / 57; of cubes beside one 1100-tet body (256 at a time) x 500 91 / 137, x 1000 149 / 142,
+// x 4000 492 / 291, and their gradients of 16 steps 312 / 350, 521 / 417, 1737 / 983.
+bool resident_pays(const gsim_model* m, int fwd, int adj, bool overlap) {
+    if (m->exec == GSIM_EXEC_PERSIST) return true;  // (the other path: a workgroup per body too)
+    const bool small = m->res_block == 256, forward = adj == 0, lanes = sequence_lanes<float>(m, forward) > 1;
+    const double n = fwd + adj, work = n * (double)m->ne, full = (double)m->nb / m->res_bodies;
+    const double rounds = full > 2 ? full : std::ceil(full);
+    // us a body and step of its chain, us a round of setting up, tets a us
+    const double chain = forward ? (small ? 0.9 : 1.7) : (small ? 1.5 : 2.0);
+    const double resident = rounds * (4.5 + n * chain) + work / (forward ? 107e3 : 86e3);
+    // us a launch pair, us of a fork and join, tets a us
+    const double pairs = overlap ? std::max(fwd, adj) : fwd + adj;
+    const double two_pass = 4 + (lanes ? 30 : 0) + 7 * pairs + work / (!forward ? 38e3 : lanes ? 75e3 : 60e3);
+    return resident < (rounds > 1 ? 0.95 : 1.0) * two_pass;
+}
+// A run of steps goes through the resident kernel: the model's bodies qualify, the particle
 // passes sum one particle per thread (a tile's contact sums are then whole wavefronts of
 // the resident workgroup), no kernel is being timed (the timed launches are the two-pass
-// ones), and per-step actuation gradients do not overlap (a tet's thread adds to its own
-// entries only, in its own time).
-bool runs_resident(const gsim_model* m, const gsim_grads* g = nullptr) {
+// ones), per-step actuation gradients do not overlap (a tet's thread adds to its own
+// entries only, in its own time), and it is the faster one.
+bool runs_resident(const gsim_model* m, int fwd, int adj = 0, const gsim_grads* g = nullptr, bool overlap = false) {
     return m->res_ept > 0 && m->exec != GSIM_EXEC_FUSED && m->timing_mask == 0 && m->pitems == 1 &&
            (m->res_block % m->pblock == 0 || m->max_body_np <= m->pblock) &&
-           (!g || !g->act || g->act_stride == 0 || g->act_stride >= m->ne);
+           (!g || !g->act || g->act_stride == 0 || g->act_stride >= m->ne) && resident_pays(m, fwd, adj, overlap);
 }
 // Graph key of a call whose steps do.
 const long long RES_KEY = 1LL << 36;
@@ -1346,7 +1375,7 @@ int do_step(gsim_model* m, const gsim_params* p, gsim_state in, gsim_state out, 
         }
         seq.push_back({OP_FWD, r0 + t});
     }
-    const bool res = runs_resident(m);
+    const bool res = runs_resident(m, n);
     if (res) make_resident(seq, rows, r0, m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, r0, rows, stream))) return rc;
     return execute<T>(m, (1LL << 40) | (res ? RES_KEY : 0) | n, seq, stream);
@@ -1378,7 +1407,7 @@ int do_step_backward(gsim_model* m, const gsim_params* p, gsim_state s, gsim_sta
     if (g && g->contact) seq.push_back({OP_FILL_CPART, r0});
     seq.push_back({OP_ADJ, r0});
     if (g && g->contact) seq.push_back({OP_CONTACT_REDUCE, r0});
-    const bool res = runs_resident(m, g);
+    const bool res = runs_resident(m, 0, 1, g);
     if (res) make_resident(seq, rows, r0, m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, r0, rows, stream))) return rc;
     if (m->exec == GSIM_EXEC_FUSED) {
@@ -1438,7 +1467,7 @@ int do_rollout(gsim_model* m, const gsim_params* p, gsim_state s0, int n, void* 
         }
         seq.push_back({OP_FWD, region_rollout(m) + t});
     }
-    const bool res = runs_resident(m);
+    const bool res = runs_resident(m, n);
     if (res) make_resident(seq, rows, region_rollout(m), m->ws, m->ws + m->L.total);
     if ((rc = upload_rows<T>(m, region_rollout(m), rows, stream))) return rc;
     if ((rc = execute<T>(m, (3LL << 40) | (res ? RES_KEY : 0) | ((long long)n << 1) | (ckpt ? 1 : 0), seq, stream)))
@@ -1483,9 +1512,11 @@ int do_rollout_backward(gsim_model* m, const gsim_params* p, const void* ckpt, i
     // buffer and it, and the recompute of segment s - 1 runs in the same launches as
     // segment s's adjoint steps.  When the rollout of these checkpoints left the last
     // segment's states in that buffer, that segment is not recomputed.
-    const bool res = runs_resident(m, g);
-    const bool two = uses_seg2(m), overlap = two && nseg > 1 && m->exec != GSIM_EXEC_PERSIST && !res;
+    const bool two = uses_seg2(m);
     const bool kept = two && m->tail_ckpt == ckpt && m->tail_seg2 == m->seg2 && m->tail_n == n;
+    const int recomputed = n - nseg - (kept ? n - 1 - (nseg - 1) * K : 0);
+    const bool share = two && nseg > 1 && m->exec != GSIM_EXEC_PERSIST;
+    const bool res = runs_resident(m, recomputed, n, g, share), overlap = share && !res;
     m->tail_ckpt = nullptr;  // this call overwrites the second buffer
     auto segbuf = [&](int s) -> T* { return two && ((nseg - 1 - s) & 1) == 0 ? (T*)m->seg2 : (T*)seg; };
     std::vector<std::vector<int64_t>> rec(nseg), adj(nseg);  // table rows of each segment's passes
@@ -1747,6 +1778,7 @@ int model_init(const gsim_plan* P, int max_steps, int K, void* d_ws, size_t byte
     m->res_ept = P->res_ept;
     m->res_block = P->res_block;
     m->res_lds = P->res_lds;
+    if (m->res_ept) chk(resident_bodies(m->res_block, m->res_ept, m->res_lds, &m->res_bodies));
     m->fused_ok = P->fused_ok;
     m->any_air = P->any_air;
     m->air_on = P->air_on;

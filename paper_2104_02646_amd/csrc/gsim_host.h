@@ -172,8 +172,8 @@ struct gsim_model {
     std::vector<Pending> pending;
     double timing_ms[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t timing_n[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    // resident execution: 0 tets per thread = not available
-    int res_ept = 0, res_block = 0;
+    // resident execution: 0 tets per thread = not available; bodies the card holds at a time
+    int res_ept = 0, res_block = 0, res_bodies = 0;
     size_t res_lds = 0;
     // fused path
     bool fused_ok = false;   // colouring succeeded for every body and kind

@@ -227,6 +227,8 @@ int launch_persist(const ModelDev<T>* md, const StepDev<T>* rows, int n_rows, co
 // thread).  pblock: the particle passes' block size (the contact sums' tree).
 int launch_resident(const ModelDev<float>* md, const StepDev<float>* rows, int n_rows, int n_bodies, int block, int ept,
                     int pblock, size_t lds, void* stream);
+// Bodies the card holds at a time in that launch.
+hipError_t resident_bodies(int block, int ept, size_t lds, int* bodies);
 // Bits of StepDev::res (set for the rows of one launch by the host).
 enum : int32_t {
     RES_ADJ = 1,         // an adjoint step

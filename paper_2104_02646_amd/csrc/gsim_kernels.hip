@@ -2340,22 +2340,34 @@ int launch_dual(const ModelDev<T>* md, const StepDev<T>* sd_adj, const StepDev<T
                  n_ptiles, pspan, sd_fwd, ptiles);
     return check_launch();
 }
+using ResidentKernel = void (*)(const ModelDev<float>*, const StepDev<float>*, int, int);
+// The kernel of `ept` tets per thread, allowed `lds` bytes of dynamic LDS.
 template <int EPT>
-int launch_resident_v(const ModelDev<float>* md, const StepDev<float>* rows, int n_rows, int n_bodies, int block,
-                      int pblock, size_t lds, void* stream) {
+ResidentKernel resident_variant(size_t lds) {
     static size_t allowed = 48 * 1024;
     allow_lds(reinterpret_cast<const void*>(&k_resident<float, EPT>), lds, allowed);
-    hipLaunchKernelGGL((k_resident<float, EPT>), dim3(n_bodies), dim3(block), lds, (hipStream_t)stream, md, rows, n_rows,
-                       pblock);
-    return check_launch();
+    return k_resident<float, EPT>;
+}
+ResidentKernel resident_kernel(int ept, size_t lds) {
+    static_assert(RES_EPT == 3, "one variant per tets-per-thread count");
+    return ept == 1 ? resident_variant<1>(lds) : ept == 2 ? resident_variant<2>(lds) : resident_variant<3>(lds);
 }
 int launch_resident(const ModelDev<float>* md, const StepDev<float>* rows, int n_rows, int n_bodies, int block, int ept,
                     int pblock, size_t lds, void* stream) {
     if (n_rows <= 0 || n_bodies <= 0) return 0;
-    if (ept == 1) return launch_resident_v<1>(md, rows, n_rows, n_bodies, block, pblock, lds, stream);
-    if (ept == 2) return launch_resident_v<2>(md, rows, n_rows, n_bodies, block, pblock, lds, stream);
-    static_assert(RES_EPT == 3, "one variant per tets-per-thread count");
-    return launch_resident_v<3>(md, rows, n_rows, n_bodies, block, pblock, lds, stream);
+    hipLaunchKernelGGL(resident_kernel(ept, lds), dim3(n_bodies), dim3(block), lds, (hipStream_t)stream, md, rows, n_rows,
+                       pblock);
+    return check_launch();
+}
+hipError_t resident_bodies(int block, int ept, size_t lds, int* bodies) {
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(resident_kernel(ept, lds)),
+                                                         block, lds);
+    *bodies = std::max(per_cu, 1) * std::max(cus, 1);
+    return e;
 }
 int launch_stage_copy(const StageSeg* segs, int n_segs, void* stream) {
     if (n_segs <= 0) return 0;
