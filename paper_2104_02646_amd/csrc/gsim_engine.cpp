@@ -618,10 +618,21 @@ int finish(gsim_engine* E, Live& L) {
     return GSIM_OK;
 }
 
+// Forgets the planned rounds that have not been issued (the live set has changed, or a round
+// failed and its queries stand where they stood before it); their slot stays in use up to
+// the launches so far.
+int drop_rounds(gsim_engine* E) {
+    if (E->rounds.empty()) return GSIM_OK;
+    E->rounds.clear();
+    E->next_round = 0;
+    HIP_TRY(hipEventRecord(E->blob_evt[E->round_slot], E->stream), "record tick");
+    return GSIM_OK;
+}
+
 // Plans the next rounds of the live queries and uploads their tables in one copy: as many
 // as the ring slot holds, up to PLAN_ROUNDS and to the first round in which a query
-// finishes, since the tables hold until the live set changes (after an admission what is
-// left of them is dropped).  A copy per round cost more host time than the round's two
+// finishes, since the tables hold until the live set changes (an admission drops what is
+// left of them).  A copy per round cost more host time than the round's two
 // launches: 12 queries of 64 to 120 steps (350 rounds) took 8.6 ms with one, 6.0 ms with
 // a copy for up to 8 rounds.
 int plan_rounds(gsim_engine* E) {
@@ -694,16 +705,10 @@ int plan_rounds(gsim_engine* E) {
 // (loss seeds, final reductions), then one element launch and one particle launch over
 // the forward and the adjoint tiles of every query together; finally advance the queries
 // and finish the completed ones.
-int micro_round(gsim_engine* E) {
+int issue_round(gsim_engine* E) {
     const int n = (int)E->live.size();
     E->ticks++;
     E->live_sum += n;
-    if (E->next_round < E->rounds.size() && (int)E->rounds[E->next_round].ops.size() != n) {
-        // queries were admitted: the rest of the plan is dropped, and its slot stays in use
-        // up to the launches so far
-        HIP_TRY(hipEventRecord(E->blob_evt[E->round_slot], E->stream), "record tick");
-        E->next_round = E->rounds.size();
-    }
     if (E->next_round == E->rounds.size())
         if (int rc = plan_rounds(E)) return rc;
     const Round R = std::move(E->rounds[E->next_round++]);
@@ -768,6 +773,13 @@ int micro_round(gsim_engine* E) {
     return GSIM_OK;
 }
 
+// (A round that fails has advanced no query: the next one is planned from where they stand.)
+int micro_round(gsim_engine* E) {
+    const int rc = issue_round(E);
+    if (rc) (void)drop_rounds(E);
+    return rc;
+}
+
 int tick(gsim_engine* E, int* n_live, int* n_queued) {
     if (int rc = retire(E, false)) return rc;
     // 1. admission, FIFO while the head fits; the admitted queries' set-up copies move
@@ -783,6 +795,7 @@ int tick(gsim_engine* E, int* n_live, int* n_queued) {
             E->pool.release(off, q ? q->lay.total : 0);
             return rc;
         }
+        if ((rc = drop_rounds(E))) return rc;
     }
     HIP_TRY(E->stage.flush(), "stage queries");
     // 2. micro-step rounds
