@@ -12,8 +12,9 @@ def lib(tmp_path_factory):
     return hosthip.build(str(tmp_path_factory.mktemp("host")))
 
 
-def rounds(hip, fail=None):
-    """The first query's input state of each round's launch (as a pool offset), and errors."""
+def calls(hip, fail=None):
+    """The kernel launches of two queries' rounds, each round's with the first query's input
+    state (as a pool offset) before its last one, and the number of errors."""
     from paper_2104_02646_amd import gsim as gs, serve
     e = serve.Engine(pool_bytes=128 << 20, max_live=4, device="cpu", stream=hip.stream)
     for k in range(2):
@@ -32,20 +33,20 @@ def rounds(hip, fail=None):
         done += e.poll()
         if nl == 0 and nq == 0:
             break
-    base = e.pool.data_ptr()
     assert len(done) == 2
-    return [int(w[2:]) - base for w in hip.names() if w.startswith("x=")], errors
+    base = e.pool.data_ptr()
+    return [int(w[2:]) - base if w.startswith("x=") else w for w in hip.names()
+            if w.startswith("x=") or w in ("mixed", "loss", "contact_reduce")], errors
 
 
-@pytest.mark.parametrize("fail", [("mixed", 1), ("mixed", 4), ("loss", 1), ("contact_reduce", 1)])
+@pytest.mark.parametrize("fail", [("mixed", 1), ("mixed", 3), ("mixed", 11), ("loss", 1), ("loss", 2),
+                                  ("contact_reduce", 2)])
 def test_failed_round_is_repeated(lib, monkeypatch, fail):
     hip = hosthip.use(lib, monkeypatch)
-    want, errors = rounds(hip)
-    assert errors == 0 and len(want) == 20
-    got, errors = rounds(hip, fail)
+    want, errors = calls(hip)
+    assert errors == 0 and want.count("mixed") == 20  # 9 forward, loss, 9 adjoint, end
+    got, errors = calls(hip, fail)
     assert errors == 1
-    if fail[0] == "mixed":  # the failed launch itself is among the calls
-        at = fail[1] - 1
-        assert got == want[:at + 1] + want[at:]
-    else:  # it failed before the round's launch
-        assert got == want
+    at = [i for i, w in enumerate(want) if w == fail[0]][fail[1] - 1]  # the call that fails
+    start = max([i + 1 for i, w in enumerate(want[:at]) if w == "mixed"], default=0)  # of its round
+    assert got == want[:at + 1] + want[start:]
