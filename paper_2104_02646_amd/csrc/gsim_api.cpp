@@ -2060,10 +2060,12 @@ int gsim_model_set_lanes(gsim_model* m, int lanes) {
     if (!m) return fail(GSIM_E_INVALID, "NULL model");
     if (lanes < 1 || lanes > MAX_LANES) return fail(GSIM_E_INVALID, "lanes must be 1..%d", MAX_LANES);
     if (lanes > m->nb) return fail(GSIM_E_UNSUPPORTED, "%d lanes need at least %d bodies", lanes, lanes);
-    m->lanes_chosen = true;
-    if (m->lanes == lanes && m->run_lanes == std::min(lanes, RUN_LANES)) return GSIM_OK;
+    // (the first choice also retiles where it names the lanes the model has: what runs on
+    // fewer while nobody chose runs on them from here on, captured graphs included)
+    if (m->lanes_chosen && m->lanes == lanes) return GSIM_OK;
     HIP_TRY(hipDeviceSynchronize(), "synchronize before retiling");
     m->lanes = lanes;
+    m->lanes_chosen = true;
     return guarded<double>([&]() { return m->dtype == GSIM_F64 ? upload_tiles<double>(m, nullptr) : upload_tiles<float>(m, nullptr); });
 }
 
