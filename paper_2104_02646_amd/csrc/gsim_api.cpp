@@ -707,18 +707,20 @@ int sequence_lanes(const gsim_model* m, bool forward) {
 template <typename T>
 int upload_tiles(gsim_model* m, void* stream, UploadSink* sink = nullptr) {
     std::vector<Tile> et, pt;
+    const int lanes = !m->lanes_chosen && lane_work<T>(m) < LANES_MIN ? 1 : std::min(m->lanes, RUN_LANES);
+    // (the lanes' streams and fork / join events first: until they are there nothing changes)
+    if (lanes > 1 && !m->ev_fork) HIP_TRY(hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming), "lane event");
+    for (int l = 1; l < lanes; ++l) {
+        if (!m->lane_stream[l])
+            HIP_TRY(hipStreamCreateWithFlags(&m->lane_stream[l], hipStreamNonBlocking), "lane stream");
+        if (!m->ev_join[l]) HIP_TRY(hipEventCreateWithFlags(&m->ev_join[l], hipEventDisableTiming), "lane event");
+    }
+    m->run_lanes = lanes;
     int rows_e = 0;
     natural_tiles(m, false, 0, m->etiles_nat, rows_e);
     natural_tiles(m, true, m->pblock * m->pitems, m->ptiles_nat, m->n_ptile_rows);
     // launch lanes: bodies assigned largest first to the lane with the least work so
     // far; each lane's tiles are XCD-ordered on their own and the lists concatenated
-    m->run_lanes = !m->lanes_chosen && lane_work<T>(m) < LANES_MIN ? 1 : std::min(m->lanes, RUN_LANES);
-    if (m->run_lanes > 1 && !m->ev_fork) HIP_TRY(hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming), "lane event");
-    for (int l = 1; l < m->run_lanes; ++l) {  // the lanes' streams and fork / join events
-        if (!m->lane_stream[l])
-            HIP_TRY(hipStreamCreateWithFlags(&m->lane_stream[l], hipStreamNonBlocking), "lane stream");
-        if (!m->ev_join[l]) HIP_TRY(hipEventCreateWithFlags(&m->ev_join[l], hipEventDisableTiming), "lane event");
-    }
     std::vector<int> lane(m->nb, 0);
     if (m->run_lanes > 1) {
         std::vector<int> order(m->nb);
@@ -2064,9 +2066,16 @@ int gsim_model_set_lanes(gsim_model* m, int lanes) {
     // fewer while nobody chose runs on them from here on, captured graphs included)
     if (m->lanes_chosen && m->lanes == lanes) return GSIM_OK;
     HIP_TRY(hipDeviceSynchronize(), "synchronize before retiling");
+    const int before = m->lanes;
+    const bool chosen = m->lanes_chosen;
     m->lanes = lanes;
     m->lanes_chosen = true;
-    return guarded<double>([&]() { return m->dtype == GSIM_F64 ? upload_tiles<double>(m, nullptr) : upload_tiles<float>(m, nullptr); });
+    const int rc = guarded<double>([&]() { return m->dtype == GSIM_F64 ? upload_tiles<double>(m, nullptr) : upload_tiles<float>(m, nullptr); });
+    if (rc) {
+        m->lanes = before;
+        m->lanes_chosen = chosen;
+    }
+    return rc;
 }
 
 int gsim_model_set_overlap(gsim_model* m, void* d_segment2, size_t bytes) {

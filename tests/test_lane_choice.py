@@ -31,3 +31,23 @@ def test_graphs_follow_the_choice(lib, monkeypatch):
     hip.reset()
     m.set_lanes(2)  # chosen already: nothing to do
     assert hip.names() == []
+
+
+@pytest.mark.parametrize("what,nth", [("stream", 1), ("event", 1), ("event", 2), ("device_sync", 1)])
+def test_failed_choice_changes_nothing(lib, monkeypatch, what, nth):
+    from paper_2104_02646_amd import gsim as gs
+    hip = hosthip.use(lib, monkeypatch)
+    m, p, x, v = hip.model([W.batch_body(k, lo=3000, hi=4000) for k in (1, 2)], max_steps=2, ckpt_every=2)
+    hip.reset()
+    hip.fail(what, nth)
+    with pytest.raises(gs.GsimError):
+        m.set_lanes(2)
+    hip.reset()
+    m.step(p, x, v, 2)
+    n = hip.count()
+    assert n["elem_fwd"] == 2 and n["wait_event"] == 0, n  # one lane, as before
+    m.set_lanes(2)
+    hip.reset()
+    m.step(p, x, v, 2)
+    n = hip.count()
+    assert n["elem_fwd"] == 4 and n["wait_event"] == 2, n
