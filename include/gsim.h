@@ -213,6 +213,11 @@ int gsim_model_get_launch(const gsim_model* model, int pass, int* block, int* it
 int gsim_model_set_lanes(gsim_model* model, int lanes);
 int gsim_model_get_lanes(const gsim_model* model, int* lanes);
 
+/* Whether a call of n_steps (gsim_step and gsim_rollout; backward != 0:
+ * gsim_rollout_backward) keeps the bodies resident, one launch for its steps (see
+ * GSIM_EXEC_*), with the model's present settings. */
+int gsim_model_runs_resident(const gsim_model* model, int n_steps, int backward, int* resident);
+
 /* Overlapped recompute in gsim_rollout_backward (the checkpointed reverse pass of
  * App. A.2: every segment's states are recomputed from its checkpoint before its
  * adjoint steps).  The recompute of segment s - 1 needs only its own checkpoint,

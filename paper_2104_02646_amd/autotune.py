@@ -11,7 +11,9 @@ built with the fastest configuration.
 ``tune`` chooses, for a given model, the launch shape of each pass: threads per
 workgroup (element passes: per planned element tile) and, for the particle passes,
 particles per thread, with HIP events around every launch
-(``gsim_model_set_timing``).
+(``gsim_model_set_timing``).  Timed launches are the two-pass ones, so a model whose calls
+run resident keeps its particle shape: the calls do not run what would be timed, and
+several particles per thread would take them off that path.
 
 Both cache their choice in a JSON file (``$GSIM_AUTOTUNE_CACHE``, default
 ``~/.cache/gsim_autotune.json``) per GPU architecture and size bucket, so later
@@ -88,10 +90,14 @@ def tune(model, params, x, v, steps=6, use_cache=True, stream=None):
     cache = _load_cache() if use_cache else {}
     exec_mode = model.get_exec()[0]
     model.set_exec(gsim.EXEC_PLAIN)
+    resident = model.runs_resident(model.max_steps) or model.runs_resident(model.max_steps, backward=True)
     report = {}
     for pass_, cands, names in ((0, ELEMENT_CANDIDATES, ("element_fwd", "element_adj")),
                                 (1, PARTICLE_CANDIDATES, ("particle_fwd", "particle_adj"))):
         key = bucket_key(model, pass_)
+        if pass_ == 1 and resident:
+            report[key] = {"shape": list(model.get_launch(1)), "resident": True, "cached": False}
+            continue
         if key in cache:
             b, i = cache[key]["shape"]
             model.set_launch(pass_, b, i)

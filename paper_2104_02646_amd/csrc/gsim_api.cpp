@@ -1250,6 +1250,11 @@ bool uses_seg2(const gsim_model* m) {
            (m->exec == GSIM_EXEC_PLAIN || m->exec == GSIM_EXEC_GRAPH || m->exec == GSIM_EXEC_PERSIST);
 }
 
+// A two-pass backward of nseg segments runs its recompute in the adjoint's launches.
+bool shares_launches(const gsim_model* m, int nseg) {
+    return uses_seg2(m) && nseg > 1 && m->exec != GSIM_EXEC_PERSIST;
+}
+
 // table regions
 int64_t region_rollout(const gsim_model*) { return 0; }
 int64_t region_backward(const gsim_model* m) { return m->max_steps + 2; }
@@ -1517,7 +1522,7 @@ int do_rollout_backward(gsim_model* m, const gsim_params* p, const void* ckpt, i
     const bool two = uses_seg2(m);
     const bool kept = two && m->tail_ckpt == ckpt && m->tail_seg2 == m->seg2 && m->tail_n == n;
     const int recomputed = n - nseg - (kept ? n - 1 - (nseg - 1) * K : 0);
-    const bool share = two && nseg > 1 && m->exec != GSIM_EXEC_PERSIST;
+    const bool share = shares_launches(m, nseg);
     const bool res = runs_resident(m, recomputed, n, g, share), overlap = share && !res;
     m->tail_ckpt = nullptr;  // this call overwrites the second buffer
     auto segbuf = [&](int s) -> T* { return two && ((nseg - 1 - s) & 1) == 0 ? (T*)m->seg2 : (T*)seg; };
@@ -2096,6 +2101,14 @@ int gsim_model_set_overlap(gsim_model* m, void* d_segment2, size_t bytes) {
 int gsim_model_get_lanes(const gsim_model* m, int* lanes) {
     if (!m || !lanes) return fail(GSIM_E_INVALID, "NULL argument");
     *lanes = m->lanes;
+    return GSIM_OK;
+}
+
+int gsim_model_runs_resident(const gsim_model* m, int n, int backward, int* resident) {
+    if (!m || !resident) return fail(GSIM_E_INVALID, "NULL argument");
+    if (n < 1 || n > m->max_steps) return fail(GSIM_E_INVALID, "n_steps must be in [1, %d]", m->max_steps);
+    const int nseg = (n + m->K - 1) / m->K;
+    *resident = backward ? runs_resident(m, n - nseg, n, nullptr, shares_launches(m, nseg)) : runs_resident(m, n);
     return GSIM_OK;
 }
 

@@ -33,6 +33,7 @@ ABI_SYMBOLS = ("gsim_last_error", "gsim_version", "gsim_plan_create", "gsim_plan
                "gsim_plan_counts", "gsim_plan_colouring", "gsim_plan_tiles", "gsim_plan_codes", "gsim_plan_partials",
                "gsim_model_init", "gsim_model_destroy", "gsim_model_set_exec", "gsim_model_get_exec",
                "gsim_model_set_launch", "gsim_model_get_launch", "gsim_model_set_lanes", "gsim_model_get_lanes",
+               "gsim_model_runs_resident",
                "gsim_model_set_overlap",
                "gsim_step", "gsim_step_backward", "gsim_rollout", "gsim_rollout_backward",
                "gsim_loss_mse", "gsim_model_set_timing", "gsim_model_read_timing", "gsim_model_check",
@@ -133,6 +134,7 @@ def load():
         lib.gsim_model_get_launch.argtypes = [vp, ip, C.POINTER(ip), C.POINTER(ip)]
         lib.gsim_model_set_lanes.argtypes = [vp, ip]
         lib.gsim_model_get_lanes.argtypes = [vp, C.POINTER(ip)]
+        lib.gsim_model_runs_resident.argtypes = [vp, ip, ip, C.POINTER(ip)]
         lib.gsim_model_set_overlap.argtypes = [vp, vp, C.c_size_t]
         lib.gsim_step.argtypes = [vp, C.POINTER(_Params), _State, _State, ip, vp]
         lib.gsim_step_backward.argtypes = [vp, C.POINTER(_Params), _State, _State, _State, C.POINTER(_Grads), vp]
@@ -444,6 +446,13 @@ class Model:
         n = C.c_int()
         _check(load().gsim_model_get_lanes(self._h, C.byref(n)))
         return n.value
+
+    def runs_resident(self, n_steps, backward=False):
+        """Whether a step or rollout call of n_steps (or the backward of such a rollout) keeps
+        the bodies resident, one launch for its steps, with the present settings."""
+        r = C.c_int()
+        _check(load().gsim_model_runs_resident(self._h, int(n_steps), int(bool(backward)), C.byref(r)))
+        return bool(r.value)
 
     def keeps_last_segment(self):
         """Whether the second segment buffer is in use (the library's rule: overlap on,
