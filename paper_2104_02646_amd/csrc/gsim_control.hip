@@ -201,14 +201,27 @@ int check_ctrl(int dtype, const gsim_controller* c, int64_t n, int64_t t0, int64
     return GSIM_OK;
 }
 
-// Layers of fewer elements than this (256 per compute unit) take CTRL_SPLIT wavefronts per
-// 64 elements.  Measured at 60 steps, 8 signals, float32 (one / eight wavefronts, us):
-// forward at 600 elements 11.4 / 5.3, 32000 13.3 / 7.2, 64000 14.5 / 11.0, 200000 19.4 /
-// 23.3; backward 14.4 / 6.5, 14.2 / 7.9, 15.2 / 13.0, 22.5 / 35.7.
-constexpr int64_t CTRL_SMALL = 65536;
-#define CTRL_LAUNCH(K, T, ...)                                                                                    \
+// CTRL_SPLIT wavefronts per 64 elements, or one.  Up to 16384 elements (one group of 64 per
+// compute unit) the split is never slower.  Each further such share puts another workgroup
+// on every compute unit, whose wavefronts compete, while a call of few steps leaves most of
+// the eight without one (they take the steps, backward eight at a time): so the split needs
+// more steps the more shares, and no number of steps makes up for a fourth share in FP64 or
+// a fifth in FP32.  Measured (8 signals, one / eight wavefronts, us): float32, 600 elements, 60
+// steps forward 11.1 / 4.4, backward 13.8 / 5.7; 32000, 60 steps 12.7 / 6.4, 13.1 / 7.0, 1 step
+// 3.5 / 4.1, 5.0 / 5.3; 48000, 8 steps 4.5 / 4.9, 5.7 / 8.9, 32 steps 8.4 / 6.3, 9.1 / 9.1; 65000, 60
+// steps 13.5 / 9.9, 14.6 / 12.4, 24 steps 7.4 / 7.3, 9.1 / 11.2; 200000, 60 steps 19.4 / 23.3, 22.5 /
+// 35.7.  float64, 32000, 24 steps 12.6 / 9.3, 14.7 / 13.3, 12 steps 8.3 / 6.9, 10.2 / 13.2; 48000, 60
+// steps 27.2 / 23.1, 31.0 / 27.7, 24 steps 13.1 / 12.7, 14.8 / 19.1; 65000, 60 steps 28.4 / 30.0,
+// 32.0 / 37.8, 300 steps 113 / 109, 131 / 130.
+template <typename T>
+bool ctrl_split(int64_t n, int64_t steps, bool backward) {
+    const bool f32 = sizeof(T) == 4;
+    const int64_t more = (n - 1) / 16384;  // shares beyond the first
+    return more < (f32 ? 4 : 3) && steps >= more * (f32 ? (backward ? 16 : 8) : (backward ? 32 : 12));
+}
+#define CTRL_LAUNCH(K, T, BACKWARD, ...)                                                                          \
     do {                                                                                                          \
-        if (n < CTRL_SMALL)                                                                                       \
+        if (ctrl_split<T>(n, n_steps, BACKWARD))                                                                  \
             hipLaunchKernelGGL((K<T, CTRL_SPLIT>), dim3((unsigned)((n + 63) / 64)), dim3(64 * CTRL_SPLIT), 0,      \
                                (hipStream_t)stream, a, __VA_ARGS__);                                              \
         else                                                                                                      \
@@ -232,8 +245,8 @@ int gsim_controller_forward(int dtype, const gsim_controller* ctrl, const void* 
     if (rc) return rc;
     if (n == 0 || n_steps == 0) return GSIM_OK;
     if (!W || !act) return gsim::fail(GSIM_E_INVALID, "NULL W or act");
-    if (dtype == GSIM_F32) CTRL_LAUNCH(k_ctrl_fwd, float, (const float*)W, (float*)act);
-    else CTRL_LAUNCH(k_ctrl_fwd, double, (const double*)W, (double*)act);
+    if (dtype == GSIM_F32) CTRL_LAUNCH(k_ctrl_fwd, float, false, (const float*)W, (float*)act);
+    else CTRL_LAUNCH(k_ctrl_fwd, double, false, (const double*)W, (double*)act);
     return launched("controller forward launch");
 }
 
@@ -244,8 +257,8 @@ int gsim_controller_backward(int dtype, const gsim_controller* ctrl, const void*
     if (rc) return rc;
     if (n == 0 || n_steps == 0) return GSIM_OK;
     if (!W || !act_grad || !W_grad) return gsim::fail(GSIM_E_INVALID, "NULL W, act_grad or W_grad");
-    if (dtype == GSIM_F32) CTRL_LAUNCH(k_ctrl_bwd, float, (const float*)W, (const float*)act_grad, (float*)W_grad);
-    else CTRL_LAUNCH(k_ctrl_bwd, double, (const double*)W, (const double*)act_grad, (double*)W_grad);
+    if (dtype == GSIM_F32) CTRL_LAUNCH(k_ctrl_bwd, float, true, (const float*)W, (const float*)act_grad, (float*)W_grad);
+    else CTRL_LAUNCH(k_ctrl_bwd, double, true, (const double*)W, (const double*)act_grad, (double*)W_grad);
     return launched("controller backward launch");
 }
 
