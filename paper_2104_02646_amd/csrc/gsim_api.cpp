@@ -1007,7 +1007,7 @@ int run_sequence(gsim_model* m, const std::vector<Launch>& seq, void* stream) {
             // not depend on the block size)
             LAUNCH_TRY(launch_persist<T>(md, sd, (int)(lj - li), nt, nt + m->n_etiles_nat,
                                          reinterpret_cast<const int32_t*>(m->ws + m->L.toff), m->nb, m->pblock, lds,
-                                         stream),
+                                         m->etile_max <= m->pblock, stream),
                        "persistent steps");
             li = lj - 1;
             continue;

@@ -220,7 +220,7 @@ int launch_fill(T* p, int64_t n, T value, void* stream);
 // adjoint where row.adj is set); `lds` covers the largest element tile of either kind.
 template <typename T>
 int launch_persist(const ModelDev<T>* md, const StepDev<T>* rows, int n_rows, const Tile* etiles, const Tile* ptiles,
-                   const int32_t* toff, int n_bodies, int block, size_t lds, void* stream);
+                   const int32_t* toff, int n_bodies, int block, size_t lds, bool one, void* stream);
 // Resident execution of steps rows[0 .. n_rows): workgroup b keeps body b on its compute
 // unit for the whole run (states and corner contributions in LDS, element records,
 // parameters and their gradients in registers: `ept` tets per thread, one particle per

@@ -55,7 +55,7 @@ template <typename T> int launch_part_fwd(const ModelDev<T>*, const StepDev<T>*,
 template <typename T> int launch_elem_adj(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, size_t, bool, bool, void*) { return launch("elem_adj"); }
 template <typename T> int launch_part_adj(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, int, bool, void*) { return launch("part_adj"); }
 template <typename T> int launch_fill(T*, int64_t, T, void*) { return launch("fill"); }
-template <typename T> int launch_persist(const ModelDev<T>*, const StepDev<T>*, int, const Tile*, const Tile*, const int32_t*, int, int, size_t, void*) { return launch("persist"); }
+template <typename T> int launch_persist(const ModelDev<T>*, const StepDev<T>*, int, const Tile*, const Tile*, const int32_t*, int, int, size_t, bool, void*) { return launch("persist"); }
 template <typename T> int launch_dual(const ModelDev<T>*, const StepDev<T>*, const StepDev<T>*, const Tile*, int, const Tile*, int, int, int, size_t, bool particles, bool, bool, void*) { return launch(particles ? "part_dual" : "elem_dual"); }
 template <typename T> int launch_mixed(const ModelDev<T>*, const StepDev<T>* sd, const TileSeg*, int, int, int, const TileSeg*, int, int, int, int, int, size_t, bool, void*) {
     calls += "x=" + std::to_string((unsigned long long)sd->x) + " ";  // the first query's input state
@@ -78,7 +78,7 @@ template <typename T> hipError_t fused_static_lds(bool, size_t* b) {
     template int launch_part_adj<T>(const ModelDev<T>*, const StepDev<T>*, const Tile*, int, int, int, bool, void*);         \
     template int launch_fill<T>(T*, int64_t, T, void*);                                                                     \
     template int launch_persist<T>(const ModelDev<T>*, const StepDev<T>*, int, const Tile*, const Tile*, const int32_t*, int, \
-                                   int, size_t, void*);                                                                     \
+                                   int, size_t, bool, void*);                                                               \
     template int launch_dual<T>(const ModelDev<T>*, const StepDev<T>*, const StepDev<T>*, const Tile*, int, const Tile*,     \
                                 int, int, int, size_t, bool, bool, bool, void*);                                            \
     template int launch_mixed<T>(const ModelDev<T>*, const StepDev<T>*, const TileSeg*, int, int, int, const TileSeg*, int,  \
