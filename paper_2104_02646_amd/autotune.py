@@ -37,7 +37,7 @@ from . import gsim
 
 ELEMENT_CANDIDATES = ((64, 1), (128, 1), (256, 1), (512, 1))
 TILE_CANDIDATES = (128, 256, 384, 512)
-LANE_CANDIDATES = (1, 2, 3, 4)
+LANE_CANDIDATES = (1, 2, 3)  # four run as three
 PARTICLE_CANDIDATES = ((64, 1), (128, 1), (256, 1), (512, 1), (256, 2), (128, 4))
 
 

@@ -51,3 +51,17 @@ def test_failed_choice_changes_nothing(lib, monkeypatch, what, nth):
     m.step(p, x, v, 2)
     n = hip.count()
     assert n["elem_fwd"] == 4 and n["wait_event"] == 2, n
+
+
+def test_tuner_times_no_lanes_twice(lib, monkeypatch):
+    """Each of the tuner's lane candidates runs a number of lanes of its own."""
+    from paper_2104_02646_amd import autotune
+    hip = hosthip.use(lib, monkeypatch)
+    m, p, x, v = hip.model([W.batch_body(k, lo=3000, hi=4000) for k in range(4)], max_steps=1)
+    ran = []
+    for lanes in autotune.LANE_CANDIDATES:
+        m.set_lanes(lanes)
+        hip.reset()
+        m.step(p, x, v, 1)
+        ran.append(hip.count()["elem_fwd"])
+    assert ran == sorted(set(ran)) and ran[0] == 1, ran
