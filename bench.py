@@ -62,31 +62,37 @@ def algorithmic_bytes(kernel, ne, np_, K):
     return None
 
 
+METHOD_TET = 64  # bytes of a tet by the method's own arrays (algorithmic_bytes)
+# ... as the element passes read one: a record of 48 (Dm^-1 36, volume 4, four 16-bit corner
+# codes 8), mu + lambda 8
+RECORD_TET = 56
 DUAL_PAIR_MIN_TILES = 2048  # the library pairs a tile's two passes from this many element tiles on
 
 
-def compulsory_per_launch(kernel, ne, np_, ntp, T, K, launches, paired=True):
+def compulsory_per_launch(kernel, ne, np_, ntp, T, K, launches, paired=True, tet=METHOD_TET):
     """Compulsory bytes of one launch: a two-pass kernel's bytes per pass (its
     kernel_bytes over the passes of that kind in one gradient, whether they run on their
     own or in shared launches), a shared launch the sum of its two passes' (the shared
-    element launch in the paired layout less one read of the element records, 64 B per
-    tet: its workgroups run both passes of a tile), a fused kernel's total over its
+    element launch in the paired layout less one read of the element records, `tet` bytes
+    a tet: its workgroups run both passes of a tile), a fused kernel's total over its
     launches."""
     nseg = -(-T // K)
     passes = {"element_fwd": T + (T - nseg), "particle_fwd": T + (T - nseg), "element_adj": T, "particle_adj": T}
     if kernel in passes:
-        return kernel_bytes(kernel, ne, np_, ntp, T, K) / passes[kernel]
+        return kernel_bytes(kernel, ne, np_, ntp, T, K, tet) / passes[kernel]
     if kernel in ("element_dual", "particle_dual"):
-        both = sum(compulsory_per_launch(kernel.replace("dual", x), ne, np_, ntp, T, K, None) for x in ("fwd", "adj"))
-        return both - (64 * ne if kernel == "element_dual" and paired else 0)
-    return kernel_bytes(kernel, ne, np_, ntp, T, K) / launches
+        both = sum(compulsory_per_launch(kernel.replace("dual", x), ne, np_, ntp, T, K, None, tet=tet)
+                   for x in ("fwd", "adj"))
+        return both - (tet * ne if kernel == "element_dual" and paired else 0)
+    return kernel_bytes(kernel, ne, np_, ntp, T, K, tet) / launches
 
 
-def kernel_bytes(kernel, ne, np_, ntp, T, K):
-    """Compulsory bytes of this design (FP32 / int32) that all launches of `kernel` in
+def kernel_bytes(kernel, ne, np_, ntp, T, K, tet=METHOD_TET):
+    """Compulsory bytes of this design (FP32) that all launches of `kernel` in
     one bench step move, each array touched once per pass.  Tet bodies only;
     ntp = tile particles (sum over element tiles of the particles each touches).
-      element pass, per tet: corner codes 16, D_m^-1 36, volume 4, mu + lambda 8
+      element pass, per tet: its record and mu + lambda, `tet` bytes (RECORD_TET as the
+        passes read them; METHOD_TET with the method's arrays in their place)
         (adjoint: + mu-bar, lambda-bar read-modify-write 16); per tile particle:
         record (index, run, partial slot) 12, positions 12 (adjoint: + the adjoint force
         12), partial write 12 (adjoint: 16);
@@ -97,14 +103,14 @@ def kernel_bytes(kernel, ne, np_, ntp, T, K):
     nseg = -(-T // K)
     fwd_passes = T + (T - nseg)  # rollout + segment recompute
     if kernel == "element_fwd":
-        return fwd_passes * (64 * ne + 36 * ntp)
+        return fwd_passes * (tet * ne + 36 * ntp)
     if kernel == "particle_fwd":
         return fwd_passes * (57 * np_ + 12 * ntp) + nseg * 24 * np_
     if kernel == "element_adj":
         # adjoint force handed over by the previous particle adjoint: x and fbar (24)
         # per tile particle, except for the first adjoint step (x, xbar+, vbar+, mass,
         # pinned: 41)
-        return T * (80 * ne + 52 * ntp) + 17 * ntp
+        return T * ((tet + 16) * ne + 52 * ntp) + 17 * ntp
     if kernel == "particle_adj":
         # + the adjoint force of the previous step written (12 per particle)
         return T * (101 * np_ + 16 * ntp) - 12 * np_
@@ -175,7 +181,7 @@ def kernel_table(timing, ne, np_, ntp, T, K, paired=True):
         if n:
             avg = ms / n
             alg = algorithmic_bytes(k, ne, np_, K)
-            comp = compulsory_per_launch(k, ne, np_, ntp, T, K, n, paired)
+            comp = compulsory_per_launch(k, ne, np_, ntp, T, K, n, paired, RECORD_TET)
             kern[k] = {"launches": n, "avg_us": avg * 1e3, "total_ms": ms, "compulsory_bytes_per_launch": comp,
                        "compulsory_GBps": comp / (avg * 1e-3) / 1e9}
             if alg is not None:
@@ -184,16 +190,16 @@ def kernel_table(timing, ne, np_, ntp, T, K, paired=True):
 
 
 def roofline(d, name, traffic):
-    """Roofline object of the dominant kernel: achieved = algorithmic bytes per launch /
-    average launch duration; the design's compulsory bytes and the HBM counter traffic
-    (per launch, null when not taken for this source) beside it, each as a ratio to
-    the algorithmic bytes."""
-    alg = d["algorithmic_bytes_per_launch"]
-    return {"bound": "hbm", "kernel": name, "achieved": d["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": d["GBps"] / HBM_PEAK_GBS, "traffic": traffic,
-            "traffic_over_algorithmic": None if traffic is None else traffic / alg,
-            "algorithmic_bytes_per_launch": alg, "compulsory_bytes_per_launch": d["compulsory_bytes_per_launch"],
-            "compulsory_over_algorithmic": d["compulsory_bytes_per_launch"] / alg, "avg_launch_us": d["avg_us"]}
+    """Roofline object of the dominant kernel: achieved = the design's compulsory bytes per
+    launch (what the launch cannot move less of) / average launch duration; beside it the
+    HBM counter traffic (per launch, null when not taken for this source) and the bytes of
+    the method's own arrays, which are more where the records are packed, with their rate."""
+    alg, comp = d["algorithmic_bytes_per_launch"], d["compulsory_bytes_per_launch"]
+    return {"bound": "hbm", "kernel": name, "achieved": d["compulsory_GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": d["compulsory_GBps"] / HBM_PEAK_GBS, "traffic": traffic,
+            "traffic_over_compulsory": None if traffic is None else traffic / comp,
+            "algorithmic_bytes_per_launch": alg, "compulsory_bytes_per_launch": comp, "algorithmic_GBps": d["GBps"],
+            "compulsory_over_algorithmic": comp / alg, "avg_launch_us": d["avg_us"]}
 
 
 def cpu_baseline(bodies, targets, T, budget_tets):
@@ -251,7 +257,7 @@ def gradient_line(bodies, dtype, T, K, exec_mode, lanes=1, reps=3, timing=False,
     """One model of `bodies`: median ms of a checkpointed gradient (rollout, loss, zeroed
     gradients, adjoint) and of a forward rollout, HIP events on the launch stream; with
     `timing`, also one gradient in plain execution with per-kernel events and the
-    dominant kernel's roofline on the algorithmic bytes."""
+    dominant kernel's roofline."""
     import torch
     from paper_2104_02646_amd import gsim
     stream = torch.cuda.Stream()
@@ -367,7 +373,7 @@ def config_lines(W, log):
     out["large_blob"] = c3
     log("configs: large blob done")
     big = [b.round_to(np.float32) for b in W.batch_bodies(20, 2048)]
-    ch = tuned(big, 100, 10, (512,), (2, 3, 4), False)
+    ch = tuned(big, 100, 10, (512,), (2, 3), False)
     out["batch_2048"] = dict(gradient_line(big, torch.float32, 100, 10, gsim.EXEC_GRAPH, lanes=ch["lanes"], timing=True,
                                            tile=ch["tile_elems"]),
                              autotuned=ch,
@@ -640,7 +646,7 @@ def main():
     ap.add_argument("--exec", choices=("fused", "graph", "plain", "persist"), default="graph")
     ap.add_argument("--block", type=int, default=256)
     ap.add_argument("--items", type=int, default=1)
-    ap.add_argument("--lanes", type=int, default=3, help="concurrent launch lanes of the two-pass path (1..4)")
+    ap.add_argument("--lanes", type=int, default=3, help="concurrent launch lanes of the two-pass path (1..3)")
     ap.add_argument("--tile", type=int, default=0, help="elements per element tile (0 = the library default)")
     ap.add_argument("--cpu-tets", type=int, default=15000, help="oracle sample size (tets)")
     ap.add_argument("--no-cpu", action="store_true")
