@@ -92,7 +92,8 @@ __device__ __forceinline__ double dpp(double x) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-// a + (a of the other half-wave) in lanes 0-31 and the same of b in lanes 32-63.
+// Exchanges lanes 32-63 of a with lanes 0-31 of b (HALF), or in each half its upper 16 lanes
+// of a with its lower 16 of b.
 template <bool HALF>
 __device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
     if constexpr (HALF) {
@@ -105,6 +106,8 @@ __device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
         b = r[1];
     }
 }
+// a + (a of the other half-wave) in lanes 0-31 and the same of b in lanes 32-63 (HALF; else
+// by the two 16-lane rows of each half).
 template <bool HALF>
 __device__ __forceinline__ float swap_add(float a, float b) {
     uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);

@@ -5,19 +5,18 @@
 //     buffer the library owns (internal ping-pong states, checkpoints, segments)
 //     are displacements u = x - X, so deformation is resolved in FP32 however far
 //     the body is from the origin; the caller's states are absolute;
-//   element records, SoA over elements of each kind:
-//     tets    idx[4][ne] (int32, model-global particle index), dinv[9][ne] (Dm^-1
-//             row-major), vol[ne], slot[4][ne] (corner -> gather slot)
-//     tris    idx[3][nt], dinv[4][nt], area[nt], slot[3][nt]
-//     hinges  idx[4][nh] (wing0, wing1, edge0, edge1), phi0[nh], slot[4][nh]
-//   gather table in sliced-ELL form: the particles of a body are cut into
-//     slices of 64 (one wavefront); slice g stores its particles' corner slots
-//     interleaved, so corner k of lane j sits at gbase[g] + 64 k + j and one
-//     wavefront load of "corner k" is one contiguous 1 KB (FP32) access;
-//     pdeg[p] = number of element corners of particle p (summed in order k = 0..);
-//   slots[nslot][4]: one 4-vector per element corner, written once per pass by
-//     the element kernel (forward: the corner force; adjoint: the corner's
-//     position-adjoint contribution and f_corner . fbar for the mass gradient).
+//   element records of each kind in 16-byte vectors, SoA over elements (see ModelDev):
+//     rest shape and 16-bit corner codes;
+//   element tiles, and per tile particle its index, its run of the tile's corners and the
+//     slot of the tile's partial for it;
+//   partials in sliced-ELL form: the particles of a body are cut into slices of 64
+//     (one wavefront); slice g stores its particles' partials interleaved, so partial k
+//     of lane j sits at gbase[g] + 64 k + j and one wavefront load of "partial k" is one
+//     contiguous access; pdeg[p] = number of partials of particle p, one per tile that
+//     touches it (summed in order k = 0..);
+//   fslots[nslot][3], slots[nslot][4]: the partials, written once per pass by the element
+//     kernel (forward: the tile's force on the particle; adjoint: its position-adjoint
+//     contribution and f . fbar for the mass gradient).
 // Each kernel launch reads its per-launch pointers (state in/out, adjoints,
 // parameters, gradients) from a StepDev record in device memory, so a launch
 // sequence can be captured once into a hipGraph and replayed with new buffers.
@@ -97,8 +96,8 @@ struct ModelDev {
     const T* tet_rec;
     const T* tri_rec;
     const T* hin_rec;
-    // tile particles (Tile.id = first, Tile.pad = count), one 16-byte record each:
-    // particle index, corner run (first sorted corner | count << 16), partial slot, 0
+    // tile particles (Tile.id = first, Tile.pad = count), one 12-byte record each:
+    // particle index, corner run (first sorted corner | count << 16), partial slot
     const int32_t* tp;
     const int32_t* gbase;  // [n_slices] first partial slot of each 64-particle slice
     const int32_t* pdeg;   // [np] partials per particle

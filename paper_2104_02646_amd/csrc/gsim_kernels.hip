@@ -1201,9 +1201,9 @@ __device__ __forceinline__ T* row_ptr(uint32_t words, int lane) {
 // and one particle per thread of RES_BLOCK, and its LDS.  One compute unit then has up to
 // six wavefronts of tets per SIMD and step to run, which takes as long as the two-pass
 // launches' overhead; beyond it a body's tets are better spread over compute units.
-// What bounds it now: instruction issue and LDS latency of the few wavefronts (a forward
-// step of the 162-tet cube is 1.7 us, of which 570 of 1034 issue slots of its busiest
-// wavefront are used).  Measured, two-pass launches -> resident: gradient of 100 steps of
+// What bounds it now: instruction issue and LDS latency of the few wavefronts (by the counters
+// the four of the 162-tet cube issue in 33 % of their cycles in forward steps and wait in 63 %,
+// the eight of a body of 1152 tets in 48 % and 36 %).  Measured, two-pass launches -> resident: gradient of 100 steps of
 // the 162-tet cube 1604 -> 676 us; 50 steps of one body of 432 tets 791 -> 454 us, of
 // 1200 tets 883 -> 652 us; of 256 bodies of up to 1260 tets 1467 -> 690 us.
 template <typename T, int EPT>

@@ -438,8 +438,10 @@ class Model:
         return b.value, i.value
 
     def set_lanes(self, lanes):
-        """Launch lanes of the two-pass path (1..4, at most one per body; the bodies are
-        split into that many concurrent groups of about equal work; default 2)."""
+        """Launch lanes of the two-pass path (1..4, at most one per body): the bodies are
+        split into that many concurrent groups of about equal work (four run as three).  A
+        model of two bodies or more says 2 until they are set, and runs on one while its
+        launches are too small to gain from two."""
         _check(load().gsim_model_set_lanes(self._h, int(lanes)))
 
     def get_lanes(self):
