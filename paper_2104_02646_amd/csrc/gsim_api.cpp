@@ -208,12 +208,14 @@ int build_tiles(gsim_plan* P, bool wide) {
     P->corner[2].resize(P->nh);
     P->etile_words[0] = P->etile_words[1] = 0;
     // a particle in the tile being cut: the tile, its corners there (counted twice: when they
-    // are collected and when they are placed), its local index and first corner slot, and
-    // the local index behind which its further entries follow
+    // are collected and when they are placed), its local index and first corner slot
     struct InTile {
-        int32_t tile, corners, loc, first, more;
+        int32_t tile, corners, loc, first;
     };
-    std::vector<InTile> in(P->np, InTile{-1, 0, 0, 0, 0});
+    std::vector<InTile> in(P->np, InTile{-1, 0, 0, 0});
+    // (local indices) particles with further entries, and the entry before a particle's first
+    std::vector<int32_t> many, more(CODE_PARTICLES);
+    bool any_more = false;
     std::vector<int32_t> parts;
     for (int b = 0; b < nb; ++b)
         for (int kind = 0; kind < 3; ++kind) {
@@ -269,28 +271,30 @@ int build_tiles(gsim_plan* P, bool wide) {
                     q.loc = j;
                     q.first = at;
                     P->tp_run.push_back(at | (q.corners << 16));
+                    if (q.corners > (int32_t)CODE_CORNERS) many.push_back(j);
                     at += q.corners;
-                }
-                for (int j = 0; j < own; ++j) {
-                    InTile& q = in[parts[j]];
-                    q.more = (int32_t)parts.size() - 1;
-                    for (int k = CODE_CORNERS; k < q.corners; k += CODE_CORNERS) {
-                        const int32_t p = parts[j];
-                        parts.push_back(p);
-                        P->tp_run.push_back(q.first + k);  // (an empty run)
-                    }
                     q.corners = 0;
                 }
+                for (int j : many) {
+                    const int32_t p = parts[j], run = P->tp_run[P->tp_id.size() + j], first = run & 0xffff, n = run >> 16;
+                    more[j] = (int32_t)parts.size() - 1;
+                    for (int32_t k = CODE_CORNERS; k < n; k += (int32_t)CODE_CORNERS) {
+                        parts.push_back(p);
+                        P->tp_run.push_back(first + k);  // (an empty run)
+                    }
+                }
+                any_more |= !many.empty();
+                many.clear();
                 const int m = (int)parts.size();
                 if (m > CODE_PARTICLES) return fail(GSIM_E_UNSUPPORTED, "a tile of %d particles", m);
                 for (int64_t l = s; l < e; ++l) {
                     uint64_t packed = 0;
                     for (int c = 0; c < nc; ++c) {
                         InTile& q = in[idx[c * n + l]];
-                        const int rank = q.corners++;
-                        if (wide) code[c * n + l] = (uint32_t)q.loc | ((uint32_t)(q.first + rank) << 16);
-                        const int part = rank / CODE_CORNERS;
-                        packed |= (uint64_t)((part ? q.more + part : q.loc) | rank % CODE_CORNERS << CODE_BITS) << 16 * c;
+                        const uint32_t rank = (uint32_t)q.corners++;
+                        if (wide) code[c * n + l] = (uint32_t)q.loc | (((uint32_t)q.first + rank) << 16);
+                        const uint32_t entry = rank < CODE_CORNERS ? q.loc : more[q.loc] + rank / CODE_CORNERS;
+                        packed |= (uint64_t)(entry | rank % CODE_CORNERS << CODE_BITS) << 16 * c;
                     }
                     P->corner[kind][l] = packed;
                 }
@@ -301,7 +305,7 @@ int build_tiles(gsim_plan* P, bool wide) {
                 t.count = (int32_t)(e - s);
                 t.begin = s;
                 t.id = (int32_t)P->tp_id.size();
-                t.pad = m;
+                t.pad = own | (m - own) << 16;
                 P->etiles.push_back(t);
                 P->tp_id.insert(P->tp_id.end(), parts.begin(), parts.end());
                 const int64_t corners = (int64_t)nc * (e - s);
@@ -312,8 +316,11 @@ int build_tiles(gsim_plan* P, bool wide) {
         }
     // partial slots (sliced ELL)
     P->pdeg.assign(P->np, 0);
-    for (size_t i = 0; i < P->tp_id.size(); ++i)
-        if (P->tp_run[i] >> 16) P->pdeg[P->tp_id[i]]++;
+    if (!any_more)
+        for (int32_t p : P->tp_id) P->pdeg[p]++;
+    else
+        for (size_t i = 0; i < P->tp_id.size(); ++i)
+            if (P->tp_run[i] >> 16) P->pdeg[P->tp_id[i]]++;
     P->gbase.clear();
     P->body_g0.assign(nb, 0);
     std::vector<int64_t> pbase(P->np);  // slot of partial 0 of each particle
@@ -332,9 +339,9 @@ int build_tiles(gsim_plan* P, bool wide) {
     }
     P->nslot = total;
     std::vector<int32_t> cur(P->np, 0);
-    P->tp_slot.assign(P->tp_id.size(), 0);
+    P->tp_slot.resize(P->tp_id.size());
     for (size_t i = 0; i < P->tp_id.size(); ++i) {
-        if (!(P->tp_run[i] >> 16)) continue;
+        if (any_more && !(P->tp_run[i] >> 16)) continue;  // (0: nothing is stored for it)
         const int32_t p = P->tp_id[i];
         P->tp_slot[i] = (int32_t)(pbase[p] + 64 * (int64_t)cur[p]++);
     }
@@ -359,9 +366,8 @@ void build_resident(gsim_plan* P) {
     for (const Tile& t : P->etiles) {
         // sorted corner position -> padded slot of the body
         at.resize(4 * (size_t)t.count);
-        for (int j = t.id; j < t.id + t.pad; ++j) {
+        for (int j = t.id; j < t.id + tile_own(t); ++j) {
             const uint32_t first = P->tp_run[j] & 0xffff, n = (uint32_t)P->tp_run[j] >> 16;
-            if (!n) continue;
             const uint32_t padded = (n + RES_PAD - 1) / RES_PAD * RES_PAD, base = (uint32_t)slots[t.body];
             for (uint32_t q = 0; q < n; ++q) at[first + q] = base + q;
             run[P->tp_slot[j]] = base | padded << 16;
@@ -1961,8 +1967,7 @@ int gsim_plan_tiles(const gsim_plan* P, int64_t* tiles, int64_t* n_tiles, int32_
             r[3] = t.count;
             r[4] = n;
         }
-        for (int32_t j = t.id; j < t.id + t.pad; ++j) {
-            if (!(P->tp_run[j] >> 16)) continue;
+        for (int32_t j = t.id; j < t.id + tile_own(t); ++j) {
             if (tile_particles) tile_particles[n] = P->tp_id[j];
             if (runs) runs[n] = P->tp_run[j];
             if (slots) slots[n] = P->tp_slot[j];

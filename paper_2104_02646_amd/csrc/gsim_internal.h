@@ -46,9 +46,14 @@ struct Tile {
     int64_t begin;  // first item (model-global element or particle index)
     int32_t id;     // particle tiles: row of the contact-gradient partial buffer;
                     // element tiles: first tile particle
-    int32_t pad;    // element tiles: number of tile particles; particle tiles: first slice of the
-                    // gather table (tiles start on a 64-particle slice of their body)
+    int32_t pad;    // element tiles: number of tile particles | of further entries << 16 (see
+                    // tile_own); particle tiles: first slice of the gather table (tiles
+                    // start on a 64-particle slice of their body)
 };
+// An element tile's particles, each with a run of corners to sum, and all its entries: behind
+// them come the further ones of particles of many corners (CODE_CORNERS), which are only staged.
+constexpr int tile_own(const Tile& t) { return t.pad & 0xffff; }
+constexpr int tile_entries(const Tile& t) { return (t.pad & 0xffff) + (t.pad >> 16); }
 
 // Serving: one query's share of a round's pass: its `count` tiles (resident on the
 // device since admission) become the round's tiles [begin, begin + count), with the
@@ -96,7 +101,7 @@ struct ModelDev {
     const T* tet_rec;
     const T* tri_rec;
     const T* hin_rec;
-    // tile particles (Tile.id = first, Tile.pad = count), one 12-byte record each:
+    // tile particles (Tile.id = first, tile_entries of them), one 12-byte record each:
     // particle index, corner run (first sorted corner | count << 16), partial slot
     const int32_t* tp;
     const int32_t* gbase;  // [n_slices] first partial slot of each 64-particle slice
@@ -293,7 +298,8 @@ const int ETILE = 256, ETILE_WORDS = 16384;
 // entries.  (With 10 and 6 bits, and a tile ending at the 64th corner of a particle, a fan's
 // hub had four times the partials, which one thread sums: gradient of 20 steps of fans of
 // 5000 and 20000 tets 1003 and 3159 us; in tiles that end at their LDS 666 and 1172.)
-const int CODE_BITS = 11, CODE_PARTICLES = 1 << CODE_BITS, CODE_CORNERS = 1 << (16 - CODE_BITS);
+const int CODE_BITS = 11, CODE_PARTICLES = 1 << CODE_BITS;
+const uint32_t CODE_CORNERS = 1u << (16 - CODE_BITS);
 
 const int FUSED_FWD_BLOCK = 1024, FUSED_ADJ_BLOCK = 512;
 // dynamic LDS per particle of the largest body: x, v, f (forward); fbar, xbar-acc, f.fbar (adjoint)

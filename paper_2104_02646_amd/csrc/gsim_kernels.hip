@@ -737,7 +737,7 @@ template <typename T, bool AIR, bool ONE>
 __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDev<T>& S, const Tile tl,
                                               unsigned char* smem) {
     const int64_t np = M.np;
-    const int m = tl.pad, tid = threadIdx.x, nth = blockDim.x;
+    const int own = tile_own(tl), m = tile_entries(tl), tid = threadIdx.x, nth = blockDim.x;
     // triangle tiles of bodies with air also stage the velocities (lift/drag)
     const bool air = AIR && tl.kind == TILE_TRI && M.bodies[tl.body].air_on != 0;
     L4<T>* xs = reinterpret_cast<L4<T>*>(smem);  // [m] tile-particle positions
@@ -803,10 +803,9 @@ __device__ __forceinline__ void elem_fwd_tile(const ModelDev<T>& M, const StepDe
         if constexpr (ONE) break;
     }
     __syncthreads();
-    for (int j = tid; j < m; j += nth) {
+    for (int j = tid; j < own; j += nth) {
         const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int r0 = r.y & 0xffff, rn = r.y >> 16;
-        if (!rn) break;  // (further entries of particles of many corners: the last ones)
         V3<T> f = zero3<T>();
         for (int k = 0; k < rn; ++k) f += v3(cs[r0 + k]);
         st_fslot(M.fslots, r.z, f.x, f.y, f.z);
@@ -905,7 +904,7 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
                                               unsigned char* smem) {
     const int64_t np = M.np;
     const T dt = M.bodies[tl.body].dt;
-    const int m = tl.pad, tid = threadIdx.x, nth = blockDim.x;
+    const int own = tile_own(tl), m = tile_entries(tl), tid = threadIdx.x, nth = blockDim.x;
     const bool air_body = AIR && M.bodies[tl.body].air_on != 0;
     const bool air = air_body && tl.kind == TILE_TRI;
     L4<T>* xs = reinterpret_cast<L4<T>*>(smem);  // [m] tile-particle positions
@@ -1021,10 +1020,9 @@ __device__ __forceinline__ void elem_adj_tile(const ModelDev<T>& M, const StepDe
         if constexpr (ONE) break;
     }
     __syncthreads();
-    for (int j = tid; j < m; j += nth) {
+    for (int j = tid; j < own; j += nth) {
         const gi4 r = j == tid ? mine : ld_tp(tp, (uint32_t)j);
         const int r0 = r.y & 0xffff, rn = r.y >> 16;
-        if (!rn) break;  // (further entries of particles of many corners: the last ones)
         V3<T> xb = zero3<T>();
         T d = T(0);
         for (int k = 0; k < rn; ++k) {
