@@ -133,10 +133,10 @@ def kernel_bytes(kernel, ne, np_, ntp, T, K, tet=METHOD_TET):
 # (of gsim_kernels.hip followed by gsim_device.h) and 512-element tiles only; for any other
 # source or tile size the traffic is reported as null.
 MEASURED_TRAFFIC = {
-    "source_sha1": "3d05ef10ad73b646266638641f7adf5421e2a62a",
+    "source_sha1": "ff10fe61f1d41b4d0c39569ab62e9ae69f52442d",
     "workload": (256, 100, 10, 512),  # bodies, steps, checkpoint interval, elements per tile
-    "per_launch": {"element_fwd": 106.21e6, "particle_fwd": 27.68e6, "element_adj": 134.20e6,
-                   "particle_adj": 42.67e6, "element_dual": 206.37e6, "particle_dual": 68.50e6},
+    "per_launch": {"element_fwd": 95.23e6, "particle_fwd": 27.69e6, "element_adj": 123.18e6,
+                   "particle_adj": 42.67e6, "element_dual": 174.99e6, "particle_dual": 68.24e6},
 }
 
 
